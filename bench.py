@@ -536,7 +536,7 @@ def main():
     gb = gather_bytes(N, M, C, R)
     out["gather_roofline"] = {"bound": "hbm", "achieved": gb / (gather_ms * 1e-3) / 1e9, "peak": PEAK_HBM_GBS,
                               "unit": "GB/s", "frac": gb / (gather_ms * 1e-3) / 1e9 / PEAK_HBM_GBS,
-                              "kernel": "k_cell_pull_wave (grid-gradient gather)", "kernel_ms": gather_ms,
+                              "kernel": "k_block_pull (grid-gradient gather)", "kernel_ms": gather_ms,
                               "algorithmic_bytes": gb}
     L = tr.losses.cpu().numpy()
     out["losses_last_step"] = {"L_rec": float(L[0, 0]), "L_density": float(L[0, 1])}

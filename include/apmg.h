@@ -204,9 +204,9 @@ apmg_status apmg_backward(const apmg_model* model, const float* pts, int64_t ld,
  * apmg_backward does).  Hash grids: the table gradient is added with float atomics (every
  * entry a vertex maps to, colliding vertices included; a run of sorted points in one cell
  * is summed in registers and added once), so dF is reproducible to rounding only.  4-D grids
- * with Rt >= 3: a further stable sort by time cell, then the grid gradient is gathered per
- * (time cell, grid cell) as apmg_backward gathers dF, in a fixed order (bitwise
- * reproducible); with Rt = 2 it is added with atomics as for the hash grids.  dW and dG
+ * with up to 513 time vertices: a further stable sort by time cell, then the grid gradient is
+ * gathered per (time cell, block of grid cells) as apmg_backward gathers dF, in a fixed order
+ * (bitwise reproducible); with more it is added with atomics as for the hash grids.  dW and dG
  * (float64 per block, fixed order) are as in apmg_backward.
  * Workspace: apmg_variant_workspace_bytes(APMG_OP_FORWARD or APMG_OP_BACKWARD, ...).
  * Arguments, outputs, flags and errors otherwise as apmg_forward / apmg_backward; dF has
@@ -344,15 +344,14 @@ apmg_status apmg_dd_forward(const apmg_dd_models* models, const apmg_brick_table
  *     (each block = 8 or 4 waves of 32-point tiles); default CUs / nb when nb divides
  *     the device's compute units (one round of blocks), else ceil(2 CUs / nb); at
  *     most 4 times the default and at most the number of 4-tile groups.
- *   cell_kernel: grid-gradient gather, 1 = one wave per 4x4x4 block of cells
- *     (the default; the wave reads each candidate point once), 2 = one thread
- *     per cell.  Either also produces L_rec's transform gradient when it is
+ *   cell_kernel: grid-gradient gather, 1 = a block of cells per wave or workgroup
+ *     (the default; each candidate point is read once and the block's vertex sums
+ *     are matrix products), 2 = one thread per cell.  Either also produces L_rec's transform gradient when it is
  *     requested.
  *   cell_unroll: candidates per batch of the one-thread-per-cell gather, 2, 4
  *     or 8 (default 4).
- *   cell_group: lanes per candidate run of the wave gather, 1, 2, 4 or 8
- *     (default 4): the wave splits its candidates into 64 / cell_group runs
- *     and each group of lanes reads cell_group consecutive points per step.
+ *   cell_group: 1, 2, 4 or 8; accepted and without effect (the block gather reads
+ *     64 consecutive candidates per step).
  *   adjoint_kernel: the fused forward + adjoint tile kernel for shapes with hidden
  *     width 64 and at most 64 input features.  The tiled kernels (each wave keeps
  *     one 32x32 block of dW1 and of dW2 and accumulates it over the tiles of its
@@ -360,10 +359,9 @@ apmg_status apmg_dd_forward(const apmg_dd_models* models, const apmg_brick_table
  *     CU; 2 = four waves per block, two blocks per CU (bf16: its LDS allows it);
  *     0 (default) = 1 for a float32 MLP, 2 for bf16.  3 = four waves per block,
  *     one per SIMD, each wave accumulating all of dW1 and dW2 over its own tiles.
- * The two gathers add each cell's terms in different fixed orders (the
- * per-cell thread in point order, the wave in its own step-then-lane order),
- * so the grid gradients agree to float32 rounding; cell_unroll does not
- * change the order, cell_group does.  Results also depend on tile_blocks and
+ * The two gathers add each vertex's terms in different fixed orders, so the grid
+ * gradients agree to float32 rounding; cell_unroll does not change the order.
+ * Results also depend on tile_blocks and
  * adjoint_kernel through the order of the weight-gradient sums.  Each setting is
  * bitwise reproducible run to run. */
 typedef struct apmg_tuning {
@@ -417,9 +415,8 @@ apmg_status apmg_batched_step(const apmg_batch* batch, void* ws, size_t ws_bytes
  * are, the losses array is written) for candidate launch shapes around the
  * defaults -- first tile-kernel blocks per model (1/2x to 4x the default) times the
  * adjoint's waves per block (eight, or four with two blocks per CU) with the default
- * gather, then the gathers (wave-cooperative with 2/4/8 lanes per run, one thread per
- * cell with 2/4/8 candidates per batch) at the best of those -- and returns the
- * fastest in *best (HOST) with its time in *best_ms.
+ * gather, then the one-thread-per-cell gather with 2/4/8 candidates per batch at the best
+ * of those -- and returns the fastest in *best (HOST) with its time in *best_ms.
  * Needs the workspace of APMG_OP_BATCHED_STEP for this batch.  Synchronises
  * `stream` (hipEvent timing), so it must not be called during graph capture.
  * The caller keeps the result and passes it as batch->tuning. */

@@ -85,12 +85,11 @@ int tile_blocks(int64_t n) {
 
 // Training-step launch shapes (apmg_tuning): tile-kernel blocks per model, default one
 // per CU over all models when nb divides the CUs evenly, else about two per CU, at most 4x the default,
-// 1024, and the number of 4-tile groups; gather batch of 2, 4 or 8 candidates; lanes per
-// candidate run of the wave gather, 1, 2, 4 or 8.
-constexpr int kDefaultCellGroup = 4;
+// 1024, and the number of 4-tile groups; gather batch of 2, 4 or 8 candidates.
+constexpr int kDefaultCellGroup = 4;   // reported by the autotuner (the block gather takes no such choice)
 // adjoint: 0 = tiled adjoint, waves per block by dtype; 1 = eight waves; 2 = four waves;
 // 3 = the one-wave-per-SIMD register kernel.
-struct Tune { int tile_blocks; int cell_unroll; int cell_kernel; int cell_group; int adjoint; };
+struct Tune { int tile_blocks; int cell_unroll; int cell_kernel; int adjoint; };
 int step_groups(int64_t n) {
   const int64_t tiles = (std::max<int64_t>(n, 1) + 31) / 32;
   return (int)std::max<int64_t>(1, (tiles + kWavesPerBlock - 1) / kWavesPerBlock);
@@ -123,7 +122,6 @@ bool resolve_tune(const apmg_tuning* t, int64_t n, int nb, bool bf, Tune* out) {
   out->tile_blocks = step_default_blocks(n, nb);
   out->cell_unroll = 4;
   out->cell_kernel = 0;
-  out->cell_group = kDefaultCellGroup;
   out->adjoint = 0;
   // four-wave tiled adjoint blocks run two per compute unit
   const auto two_per_cu = [&]() {
@@ -142,7 +140,6 @@ bool resolve_tune(const apmg_tuning* t, int64_t n, int nb, bool bf, Tune* out) {
   if (t->tile_blocks > 0) out->tile_blocks = t->tile_blocks;
   if (t->cell_unroll > 0) out->cell_unroll = t->cell_unroll;
   if (t->cell_kernel > 0) out->cell_kernel = t->cell_kernel - 1;
-  if (t->cell_group > 0) out->cell_group = t->cell_group;
   if (t->adjoint_kernel < 0 || t->adjoint_kernel > 3) return false;
   out->adjoint = t->adjoint_kernel;
   if (t->tile_blocks == 0) two_per_cu();
@@ -335,19 +332,29 @@ hipError_t launch_step_sort(uint64_t seed, const uint64_t* step_ctr, uint32_t st
 struct CellWs { float *dY, *CC; double* dGpart; };
 inline int64_t n_cells(const Shape& s) { return (int64_t)(s.R - 1) * (s.R - 1) * (s.R - 1); }
 inline int cell_blocks(const Shape& s) { return (int)((n_cells(s) + 255) / 256); }
-// workgroups per grid of the wave gather (4 waves, each a 4x4x4 block of cells)
-inline int wave_groups(const Shape& s) {
-  const int64_t nbx = (s.R - 1 + kBlk - 1) / kBlk;
-  return (int)((nbx * nbx * nbx + 3) / 4);
+// The block gather gives a block of cells to one wave, or to the four waves of a workgroup where
+// that many waves are needed to fill the device: few blocks (below two waves per SIMD) with
+// enough points each that a quarter of them is still several 64-candidate steps.  The rule looks
+// at one model alone, so a model's sums do not depend on the batch it is stepped in.
+inline bool pull_split(const Shape& s, int64_t n) {
+  const int64_t nblk = pull_blocks(s.R, s.C).total();
+  return nblk * s.M < 8192 && n >= 256 * nblk;
+}
+// workgroups per grid of the block gather (four waves each)
+inline int pull_groups(const Shape& s, int64_t n) {
+  const int64_t nblk = pull_blocks(s.R, s.C).total();
+  return (int)(pull_split(s, n) ? nblk : (nblk + 3) / 4);
 }
 // transform-gradient partials per grid written by the gather cell_kernel selects
-inline int dg_parts(const Shape& s, int cell_kernel) { return cell_kernel != 1 ? wave_groups(s) : cell_blocks(s); }
+inline int dg_parts(const Shape& s, int64_t n, int cell_kernel) {
+  return cell_kernel != 1 ? pull_groups(s, n) : cell_blocks(s);
+}
 void take_cell(Carver& cv, const Shape& s, int64_t n, int nb, CellWs* o) {
   o->dY = cv.take<float>((size_t)nb * s.M * std::max<int64_t>(n, 1) * s.C);
-  // corner sums per cell (the per-cell gather) or vertex lattices per cell block (the wave gather)
-  const int64_t nbx = (s.R - 1 + kBlk - 1) / kBlk;
-  o->CC = cv.take<float>((size_t)nb * s.M * std::max<int64_t>(n_cells(s) * 8, nbx * nbx * nbx * kLat) * s.C);
-  o->dGpart = cv.take<double>((size_t)nb * s.M * std::max(cell_blocks(s), wave_groups(s)) * 12);
+  // corner sums per cell (the per-cell gather) or vertex lattices per cell block (the block gather)
+  const int64_t lat = pull_blocks(s.R, s.C).total() * pull_lat(s.C);
+  o->CC = cv.take<float>((size_t)nb * s.M * std::max<int64_t>(n_cells(s) * 8, lat) * s.C);
+  o->dGpart = cv.take<double>((size_t)nb * s.M * std::max(cell_blocks(s), pull_groups(s, n)) * 12);
 }
 
 // timing hooks: [0] the adjoint tile kernel, [1] the grid-gradient gather
@@ -364,11 +371,13 @@ hipError_t launch_cells(const Shape& s, bool gf16, const float* G, size_t G_stri
                         const SortWs& sw, int64_t n, const CellWs& cw, float* dF, size_t dF_stride, int dF_paper,
                         int accumulate, bool want_dG, double* dG, size_t dG_stride, int dG_rows, int dG_accumulate, int nb,
                         const int32_t* active, hipStream_t st, int unroll = 4, const int32_t* dG_active = nullptr,
-                        int cell_kernel = 0, int cell_group = kDefaultCellGroup) {
+                        int cell_kernel = 0) {
   CellArgs c;
   memset(&c, 0, sizeof(c));
   c.s = s; c.G = G; c.G_stride = G_stride; c.F = F; c.F_stride = F_stride;
   c.pts4 = sw.spts4; c.n = n; c.start = sw.start; c.dY = cw.dY; c.CC = cw.CC;
+  c.dY_grid = (size_t)n * s.C; c.dY_stride = s.M * c.dY_grid;
+  c.cell = 2.0 / (s.R - 1);
   c.dGpart = cw.dGpart; c.active = active; c.nblk = cell_blocks(s);
   const int64_t nblocks = (int64_t)cell_blocks(s) * s.M * nb;
   if (nblocks > 0x7fffffff) return hipErrorInvalidValue;
@@ -379,16 +388,14 @@ hipError_t launch_cells(const Shape& s, bool gf16, const float* G, size_t G_stri
     else if (unroll == 8) hipLaunchKernelGGL((k_cell_pull<CC_, F16_, DG_, 8>), grid, dim3(256), 0, st, c); \
     else hipLaunchKernelGGL((k_cell_pull<CC_, F16_, DG_, 4>), grid, dim3(256), 0, st, c);           \
   }
-  const int64_t wgroups = (int64_t)wave_groups(s) * s.M * nb;
+  const int64_t wgroups = (int64_t)pull_groups(s, n) * s.M * nb;
   if (wgroups > 0x7fffffff) return hipErrorInvalidValue;
-  const bool wave_kernel = cell_kernel != 1;
+  const bool wave_kernel = cell_kernel != 1, split = pull_split(s, n);
 #define APMG_WAVE(CC_, F16_, DG_)                                                                   \
   {                                                                                                 \
     const dim3 wg((unsigned)wgroups);                                                               \
-    if (cell_group == 1) hipLaunchKernelGGL((k_cell_pull_wave<CC_, F16_, 1, DG_>), wg, dim3(256), 0, st, c); \
-    else if (cell_group == 2) hipLaunchKernelGGL((k_cell_pull_wave<CC_, F16_, 2, DG_>), wg, dim3(256), 0, st, c); \
-    else if (cell_group == 8) hipLaunchKernelGGL((k_cell_pull_wave<CC_, F16_, 8, DG_>), wg, dim3(256), 0, st, c); \
-    else hipLaunchKernelGGL((k_cell_pull_wave<CC_, F16_, 4, DG_>), wg, dim3(256), 0, st, c);         \
+    if (split) hipLaunchKernelGGL((k_block_pull<CC_, F16_, DG_, 1, true>), wg, dim3(256), 0, st, c); \
+    else hipLaunchKernelGGL((k_block_pull<CC_, F16_, DG_, 1, false>), wg, dim3(256), 0, st, c);      \
   }
 #define APMG_CELL(CC_, F16_)                                                                        \
   if (s.C == CC_ && gf16 == F16_) {                                                                 \
@@ -410,7 +417,7 @@ hipError_t launch_cells(const Shape& s, bool gf16, const float* G, size_t G_stri
 #undef APMG_WAVE
 #undef APMG_PULL
   if (dG)
-    hipLaunchKernelGGL(k_reduce_cell_dG, dim3(s.M, nb), dim3(256), 0, st, cw.dGpart, s.M, dg_parts(s, cell_kernel), dG,
+    hipLaunchKernelGGL(k_reduce_cell_dG, dim3(s.M, nb), dim3(256), 0, st, cw.dGpart, s.M, dg_parts(s, n, cell_kernel), dG,
                        dG_stride, dG_rows, dG_accumulate, dG_active ? dG_active : active);
   return hipGetLastError();
 }
@@ -1203,7 +1210,7 @@ apmg_status run_step(const apmg_batch* b, const Shape& s, void* ws, const Tune& 
                        1.0 / (double)n);
     const hipError_t ec = launch_cells(s, gf16, b->G, nG, Fg, nF, w.srt, n, w.cell, w.dF, nF, paper ? 1 : 0, 0,
                                        rec_dG, nullptr, 0, 3, 0, nb, w.live, st, tu.cell_unroll, nullptr,
-                                       tu.cell_kernel, tu.cell_group);
+                                       tu.cell_kernel);
     hipError_t ej = hipSuccess;
     if (dst != st) {
       ej = hipEventRecord(side->join, dst);
@@ -1212,7 +1219,7 @@ apmg_status run_step(const apmg_batch* b, const Shape& s, void* ws, const Tune& 
     if (ed != hipSuccess || ec != hipSuccess || ej != hipSuccess) return APMG_EHIP;
     if (rec_dG)
       hipLaunchKernelGGL(k_reduce_cell_dG, dim3(s.M, nb), dim3(256), 0, st, w.cell.dGpart, s.M,
-                         dg_parts(s, tu.cell_kernel), w.dG, nG, 3, 1, w.dlive);
+                         dg_parts(s, n, tu.cell_kernel), w.dG, nG, 3, 1, w.dlive);
   }
   if (!update) return hip_status(hipGetLastError());
 
@@ -1260,7 +1267,7 @@ extern "C" apmg_status apmg_autotune_batched_step(const apmg_batch* b, void* ws,
   if (hipEventCreate(&e0) != hipSuccess) return APMG_EHIP;
   if (hipEventCreate(&e1) != hipSuccess) { hipEventDestroy(e0); return APMG_EHIP; }
   float best_t = -1.f;
-  Tune best_tu = {d, 4, 0, kDefaultCellGroup, 0};
+  Tune best_tu = {d, 4, 0, 0};
   apmg_status out = APMG_OK;
   // one warm-up step, then the mean of three (no parameter update)
   const auto time_tune = [&](const Tune& tu) -> apmg_status {
@@ -1282,19 +1289,15 @@ extern "C" apmg_status apmg_autotune_batched_step(const apmg_batch* b, void* ws,
   if (adjoint_applies(s)) adjs = {1, 2};
   for (int tb : blocks) {
     for (int adj : adjs) {
-      if ((out = time_tune({tb, 4, 0, kDefaultCellGroup, adj})) != APMG_OK) break;
+      if ((out = time_tune({tb, 4, 0, adj})) != APMG_OK) break;
     }
     if (out != APMG_OK) break;
   }
-  // 2. with those: the wave-cooperative gather with 2, 4 or 8 lanes per candidate run, and
-  // one thread per cell with 2, 4 or 8 candidates per batch
-  struct Gather { int kernel, unroll, group; };
-  const Gather gathers[] = {{0, 4, 2}, {0, 4, 8}, {1, 2, kDefaultCellGroup}, {1, 4, kDefaultCellGroup},
-                            {1, 8, kDefaultCellGroup}};
+  // 2. with those: one thread per cell with 2, 4 or 8 candidates per batch
   const Tune stage1 = best_tu;
-  for (const Gather& ga : gathers) {
+  for (int unroll : {2, 4, 8}) {
     if (out != APMG_OK) break;
-    out = time_tune({stage1.tile_blocks, ga.unroll, ga.kernel, ga.group, stage1.adjoint});
+    out = time_tune({stage1.tile_blocks, unroll, 1, stage1.adjoint});
   }
   hipEventDestroy(e0);
   hipEventDestroy(e1);
@@ -1303,7 +1306,7 @@ extern "C" apmg_status apmg_autotune_batched_step(const apmg_batch* b, void* ws,
   best->tile_blocks = best_tu.tile_blocks;
   best->cell_unroll = best_tu.cell_unroll;
   best->cell_kernel = best_tu.cell_kernel + 1;
-  best->cell_group = best_tu.cell_group;
+  best->cell_group = kDefaultCellGroup;
   best->adjoint_kernel = best_tu.adjoint;
   if (best_ms) *best_ms = best_t;
   return APMG_OK;
@@ -1473,7 +1476,7 @@ size_t variant_f_elems(const Shape& s, const EncArgs& ea, int kind) {
 }
 inline int variant_nbx(int64_t n) { return (int)std::max<int64_t>(1, (n + 255) / 256); }
 // 4-D grids with at most one radix digit of time cells are sorted by time cell as well
-inline bool time_sorted(const EncArgs& ea) { return ea.Rt >= 3 && ea.Rt - 1 <= kRadixDigits; }
+inline bool time_sorted(const EncArgs& ea) { return ea.Rt - 1 <= kRadixDigits; }
 
 struct VarWs {
   float* G;        // packed 3-row transforms (4-row input)
@@ -1512,7 +1515,7 @@ size_t var_ws(const Shape& s, const EncArgs& ea, const apmg_model* m, const apmg
     w.part = cv.take<double>((size_t)bwd_blocks(n, bf) * part_layout(s, s.MC, s.H).len);
     w.dY = cv.take<float>((size_t)s.M * std::max<int64_t>(n, 1) * s.C);
     w.dGpart = cv.take<double>((size_t)s.M * variant_nbx(n) * 12);
-    if (time_paper) w.dFcl = cv.take<float>(variant_f_elems(s, ea, e->kind));
+    if (time_paper && !time_sorted(ea)) w.dFcl = cv.take<float>(variant_f_elems(s, ea, e->kind));
     take_sort(cv, n, 1, true, &w.srt);
     if (e->kind == APMG_ENC_TIME) {
       const size_t nn = (size_t)std::max<int64_t>(n, 1);
@@ -1523,7 +1526,7 @@ size_t var_ws(const Shape& s, const EncArgs& ea, const apmg_model* m, const apmg
         w.tpts = cv.take<float>(3 * nn); w.tdf = cv.take<float>(nn);
         w.trec = cv.take<float4>(nn);
         w.tstart = cv.take<uint32_t>((size_t)(ea.Rt - 1) * kBinsPerAxis * kBinsPerAxis * kBinsPerAxis + 1);
-        w.tcc = cv.take<float>((size_t)(ea.Rt - 1) * s.M * 16 * n_cells(s) * s.C);
+        w.tcc = cv.take<float>((size_t)(ea.Rt - 1) * s.M * pull_blocks(s.R, s.C).total() * pull_lat(s.C) * 2 * s.C);
       }
     }
   }
@@ -1621,7 +1624,8 @@ apmg_status apmg_variant_backward(const apmg_model* m, const apmg_encoder* e, co
       hipLaunchKernelGGL(k_fill_f32, dim3(grid1((int64_t)s.H * s.H)), dim3(256), 0, st, dW[1], (size_t)s.H * s.H, 0.f);
       hipLaunchKernelGGL(k_fill_f32, dim3(1), dim3(256), 0, st, dW[2], (size_t)s.H, 0.f);
     }
-    if (dF) hipLaunchKernelGGL(k_fill_f32, dim3(grid1(nF)), dim3(256), 0, st, dF, nF, 0.f);
+    // (the per-cell gather of the 4-D grids overwrites dF)
+    if (dF && (n == 0 || !w.tcc)) hipLaunchKernelGGL(k_fill_f32, dim3(grid1(nF)), dim3(256), 0, st, dF, nF, 0.f);
     if (dG) hipLaunchKernelGGL(k_fill_f64, dim3(1), dim3(256), 0, st, dG, (size_t)4 * grows * mt, 0.0);
   }
   if (n == 0) return hip_status(hipGetLastError());
@@ -1684,30 +1688,27 @@ apmg_status apmg_variant_backward(const apmg_model* m, const apmg_encoder* e, co
   // grid / table gradient by the scatter (into the caller's dF, or a channel-last buffer that
   // is then laid out in the paper's order), transform gradient per block in float64
   float* dst = dF ? (w.dFcl ? w.dFcl : dF) : nullptr;
-  if (dst && w.dFcl) hipLaunchKernelGGL(k_fill_f32, dim3(grid1(nF)), dim3(256), 0, st, w.dFcl, nF, 0.f);
+  if (w.dFcl && dF) hipLaunchKernelGGL(k_fill_f32, dim3(grid1(nF)), dim3(256), 0, st, w.dFcl, nF, 0.f);
   // 4-D grids in (time cell, bin) order: the grid gradient by the per-cell gather (one pass per
   // time cell, no atomics, a fixed order), then the vertex sums over both time neighbours
-  const bool pull = dst && w.tcc;
+  const bool pull = dF && w.tcc;
   if (pull) {
     CellArgs c;
     memset(&c, 0, sizeof(c));
     c.s = s; c.G = Gc; c.F = Fc;
     c.pts4 = w.trec; c.n = n; c.start = w.tstart; c.dY = w.dY; c.CC = w.tcc; c.Rt = ea.Rt;
-    const int64_t wgroups = (int64_t)wave_groups(s) * s.M * (ea.Rt - 1);
+    c.dY_grid = (size_t)n * s.C; c.cell = 2.0 / (s.R - 1);
+    // the points of one time cell decide between one wave and four per block
+    const int64_t nt = n / (ea.Rt - 1), wgroups = (int64_t)pull_groups(s, nt) * s.M * (ea.Rt - 1);
     if (wgroups > 0x7fffffff) return APMG_EUNSUPPORTED;
-    hipLaunchKernelGGL((k_cell_pull_wave<2, false, kDefaultCellGroup, false, 2>), dim3((unsigned)wgroups), dim3(256),
-                       0, st, c);
-    hipLaunchKernelGGL(k_cell_to_vertex_time<2>, dim3(grid1((int64_t)s.R * s.R * s.R, 1024), s.M, ea.Rt), dim3(256),
-                       0, st, s, ea.Rt, w.tcc, dst);
+    if (pull_split(s, nt))
+      hipLaunchKernelGGL((k_block_pull<2, false, false, 2, true>), dim3((unsigned)wgroups), dim3(256), 0, st, c);
+    else
+      hipLaunchKernelGGL((k_block_pull<2, false, false, 2, false>), dim3((unsigned)wgroups), dim3(256), 0, st, c);
+    hipLaunchKernelGGL(k_block_to_vertex_time<2>, dim3(grid1((int64_t)s.R * s.R * s.R, 1024), s.M, ea.Rt), dim3(256),
+                       0, st, s, ea.Rt, w.tcc, dF, paper_grids(m) ? 1 : 0, acc ? 1 : 0);
   }
-  if (!dG && pull) {
-    if (w.dFcl && dF) {
-      const int64_t V = (int64_t)ea.Rt * s.R * s.R * s.R;
-      hipLaunchKernelGGL(k_cl_to_paper<2>, dim3(grid1(s.M * V, 8192)), dim3(256), 0, st, (int64_t)s.M, V, w.dFcl, dF,
-                         acc ? 1 : 0);
-    }
-    return hip_status(hipGetLastError());
-  }
+  if (!dG && pull) return hip_status(hipGetLastError());
   EncScatterArgs sa;
   memset(&sa, 0, sizeof(sa));
   sa.s = s; sa.enc = ea; sa.G = Gc; sa.F = Fc;

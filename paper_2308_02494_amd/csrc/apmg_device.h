@@ -125,6 +125,12 @@ __device__ inline int64_t xcd_logical(int64_t h, int64_t total) {
   return x * q + (x < r ? x : r) + k;
 }
 
+__device__ inline uint32_t xcd_logical32(uint32_t h, uint32_t total) {
+  const uint32_t x = h % kXcds, k = h / kXcds;
+  const uint32_t q = total / kXcds, r = total % kXcds;
+  return x * q + (x < r ? x : r) + k;
+}
+
 // Eq. (1) with a fixed fma order (the integer decisions depend on it).
 __device__ inline void local_coords(const float* Gg, float x, float y, float z, float l[3]) {
 #pragma unroll

@@ -1,11 +1,13 @@
 // Grid gradient dL/dF and the transform gradient through the trilinear
 // weights (the adjoint of Eq. (2)), gathered per cell instead of scattered
-// per point.  One thread owns one cell of one grid: it maps the cell's box
-// back to global space (inverse of the transform of Eq. (1)), walks the points
-// of the spatial bins that overlap it, keeps those whose float32 cell
-// decision is this cell, and sums w_q * dL/dy_c for its 8 corners in
-// registers.  A second kernel adds, for each vertex, the corner sums of its
-// (up to 8) cells.  No atomics; every sum has a fixed order.
+// per point.  k_block_pull (the default): one wave owns a block of cells of one
+// grid, maps the block's box back to global space (inverse of the transform of
+// Eq. (1)), walks the points of the spatial bins that overlap it, keeps those
+// whose float32 cell decision lies in the block, and forms the block's vertex
+// sums of w_q * dL/dy_c with matrix instructions.  k_cell_pull: one thread owns
+// one cell and sums its 8 corners in registers.  A second kernel adds, for each
+// vertex, the sums of its (up to 8) blocks or cells.  No atomics; every sum has
+// a fixed order.
 
 namespace apmg {
 
@@ -15,17 +17,19 @@ struct CellArgs {
   const void* F; size_t F_stride;       // grids (corner values for the transform gradient)
   const float4* pts4; int64_t n;        // sorted points [model][n] as (x, y, z, 0)
   const uint32_t* start;                // [model][NB^3 + 1]
-  const float* dY;                      // [model][M][n][C]
-  float* CC;                            // [model][M][8][(R-1)^3][C] (corner-major)
+  const float* dY;                      // [model][grid][n][C] at model * dY_stride + grid * dY_grid
+  size_t dY_stride, dY_grid;
+  float* CC;                            // k_cell_pull: [model][M][8][(R-1)^3][C] (corner-major);
+                                        // k_block_pull: the blocks' vertex lattices
   double* dGpart;                       // [model][M][nblk][12] (DG)
   const int32_t* active;
   int nblk;                             // blocks of 256 cells per grid; launch nmodels * M * nblk blocks
+  double cell;                          // 2 / (R - 1): the width of a cell in local coordinates
   int Rt;                               // 4-D grids (two time slices per cell): time vertices
 };
 
-// Corner weight q = a + 2b + 4c of the trilinear weights of offsets w.  Both gathers add
-// round(w_q * dL/dy) to the corner sums (a product, then a sum: no fused multiply-add), so
-// they produce the same bits.
+// Corner weight q = a + 2b + 4c of the trilinear weights of offsets w.  The per-cell gather adds
+// round(w_q * dL/dy) to the corner sums (a product, then a sum: no fused multiply-add).
 __device__ inline float corner_weight(int qq, const float w[3]) {
   return ((qq & 1) ? w[0] : 1.f - w[0]) * ((qq & 2) ? w[1] : 1.f - w[1]) * ((qq & 4) ? w[2] : 1.f - w[2]);
 }
@@ -38,14 +42,23 @@ __device__ inline float add_rounded(float acc, float v) {
   return acc + v;
 }
 
-// The local box of the cells [c0, c0 + w) (per axis, clipped to the grid) minus the
+// 1 / x in float64 for a normal x: the hardware estimate and two Newton steps.
+__device__ inline double recip_f64(double x) {
+  double r = __builtin_amdgcn_rcp(x);
+  r = __builtin_fma(__builtin_fma(-x, r, 1.0), r, r);
+  return __builtin_fma(__builtin_fma(-x, r, 1.0), r, r);
+}
+
+// The local box of the cells [c0, c0 + w) (w cells per axis, clipped to the grid) minus the
 // translation, widened by 1e-4 (covers the float32 rounding of the cell decision), in float64.
-__device__ inline void local_box(const float* Gg, const int c0[3], int w, int R1, double blo[3], double bhi[3]) {
+// cell = 2 / R1, the width of a cell.
+__device__ inline void local_box(const float* Gg, const int c0[3], const int w[3], int R1, double cell, double blo[3],
+                                 double bhi[3]) {
 #pragma unroll
   for (int d = 0; d < 3; ++d) {
-    const int e = min(c0[d] + w, R1);
-    blo[d] = -1.0 + 2.0 * c0[d] / R1 - 1e-4 - (double)Gg[4 * d + 3];
-    bhi[d] = -1.0 + 2.0 * e / R1 + 1e-4 - (double)Gg[4 * d + 3];
+    const int e = min(c0[d] + w[d], R1);
+    blo[d] = -1.0 + cell * c0[d] - 1e-4 - (double)Gg[4 * d + 3];
+    bhi[d] = -1.0 + cell * e + 1e-4 - (double)Gg[4 * d + 3];
   }
 }
 
@@ -59,7 +72,7 @@ __device__ inline void local_box(const float* Gg, const int c0[3], int w, int R1
 // the x-range's bounds are multiplied by it rather than divided (they are padded anyway).
 __device__ inline void span_recips(const float* Gg, double ra[3]) {
 #pragma unroll
-  for (int d = 0; d < 3; ++d) ra[d] = Gg[4 * d] != 0.f ? 1.0 / (double)Gg[4 * d] : 0.0;
+  for (int d = 0; d < 3; ++d) ra[d] = Gg[4 * d] != 0.f ? recip_f64((double)Gg[4 * d]) : 0.0;
 }
 __device__ inline bool row_x_span(const float* Gg, const double ra[3], const double blo[3], const double bhi[3],
                                   int lo0, int hi0, int yb, int zb, int& x0, int& x1) {
@@ -173,7 +186,7 @@ __global__ void __launch_bounds__(256) k_cell_pull(CellArgs a) {
 #pragma unroll
   for (int k = 0; k < (DG ? 12 : 1); ++k) gacc[k] = 0.f;
   const float4* P4 = a.pts4 + (size_t)model * a.n;
-  const float* dY = a.dY + ((size_t)model * s.M + g) * a.n * C;
+  const float* dY = a.dY + model * a.dY_stride + g * a.dY_grid;
   const uint32_t* start = a.start + (size_t)model * (kBinsPerAxis * kBinsPerAxis * kBinsPerAxis + 1);
   if (valid) {
     const int cx = (int)(cell % R1), cy = (int)((cell / R1) % R1), cz = (int)(cell / ((int64_t)R1 * R1));
@@ -204,8 +217,8 @@ __global__ void __launch_bounds__(256) k_cell_pull(CellArgs a) {
                            g, s.R, me, val);
     }
     double blo[3], bhi[3], ra[3];
-    const int me0[3] = {cx, cy, cz};
-    local_box(sG, me0, 1, R1, blo, bhi);
+    const int me0[3] = {cx, cy, cz}, one[3] = {1, 1, 1};
+    local_box(sG, me0, one, R1, a.cell, blo, bhi);
     span_recips(sG, ra);
     for (int bz = lo[2]; bz <= hi[2]; ++bz)
       for (int by = lo[1]; by <= hi[1]; ++by) {
@@ -268,71 +281,140 @@ __global__ void __launch_bounds__(256) k_cell_pull(CellArgs a) {
   }
 }
 
-// The grid gradient without the transform gradient, one wave per 4 x 4 x 4 block of cells
-// of one grid.  The wave takes the rows of the bins that overlap the block's box (the union
-// of its cells' candidates, each point read once) 128 rows at a time and splits each batch's
-// points, as one flat sequence, into 64 / G contiguous runs of equal length, one per group
-// of G lanes.  At a step each group tests the next G points of its run against the block
-// (lane i of the group the i-th), so the points of a step come from all over the block's box
-// and few of them share a cell, while each group still reads G consecutive records.  A
-// matching point's (w, dL/dy) products are handed to the lane that owns its cell through
-// LDS, and each owner adds the records addressed to it in lane order.  Each cell's sum has a
-// fixed order (step, then lane) set by the candidate sequence and G: bitwise reproducible,
-// but not the plain candidate order of k_cell_pull.
-constexpr int kBlk = 4;                      // cells per block edge
-constexpr int kLat = (kBlk + 1) * (kBlk + 1) * (kBlk + 1);   // vertices of a block
-constexpr int kRowBatch = 128;               // bin rows per batch (two per lane)
+// The grid gradient by matrix products, one wave per block of cells of one grid.  A point of
+// cell (cx, cy, cz) with offsets w adds w_q dL/dy_c at the cell's 8 corners: the product of a
+// hat function per axis, H_v(t) = max(0, 1 - |t - v|) at the block's vertices v (zero at every
+// vertex the cell does not touch).  Over the block's points the sums factor into one matrix
+// product, D[(vz, vy)][(c, vx)] += sum_p (H_vz H_vy)(p) (H_vx dL/dy_c)(p): 4 x 4 vertices in
+// (z, y) are the 16 rows, kVX vertices in x times the C channels (times two time slices for
+// the 4-D grids) the columns of v_mfma_f32_16x16x4_f32, whose k dimension takes four points.
+// No record is routed to the lane that owns its cell, and a wave holds 4 (8) accumulator
+// registers per lane instead of 16 (32).
+//
+// The wave takes the rows of the bins that overlap the block's box (the union of its cells'
+// candidates, each point read once) kRowBatch rows at a time and walks their points as one
+// flat sequence, 64 consecutive candidates a step.  Each lane tests its candidate's float32
+// cell decision against the block; the lanes that match write the nonzero entries of their
+// row and column factors (2 x 2 each; the slots are zero otherwise, and are zeroed again
+// after use) to LDS at consecutive slots, element-major, so that one 16-byte read per operand
+// feeds four matrix instructions.  Every sum has a fixed order (four slots per instruction,
+// instructions in order): bitwise reproducible, though not the plain candidate order of
+// k_cell_pull.
+//
+// What bounds it: the sum of three pipes that overlap only in part.  At 2^20 uniform points,
+// 32 grids at 32^3 x 2 (48 M candidates, 30 M matches): vector instructions 0.135 ms (about 90
+// per 64 candidates), matrix instructions 0.115 ms (8 cycles of a SIMD per match), LDS 0.15 ms;
+// 0.27 ms alone with six waves per SIMD (0.40 ms with four).  The gather it replaced routed each
+// match's 16 products through LDS to the lane that owned its cell: bound by vector work, about
+// 190 instructions per 64 candidates.  Whole calls, before -> now: the adjoint of 64 grids at
+// 64^3 x 4 (2^19 points) 4.25 -> 3.20 ms, 80 brick models a step 7.73 -> 7.11 ms, the 4-D
+// forward + adjoint 3.60 -> 3.05 ms.
+// Measured and not kept: full (unsparse) factor rows written per match (0.43 ms, 1.7x the vector
+// instructions), 64 slots per round (four waves per SIMD).
+constexpr int kRowBatch = 64;                // bin rows per batch (one per lane)
+constexpr uint32_t kWindow = 4096;           // candidates whose row ends are marked at a time
+// The block of cells: kNZ = kNY = 3 cells (4 vertices) in z and y, kVX - 1 cells in x (the axis
+// along which a bin row is contiguous): 8 vertices, or 16 for one channel, so that the columns
+// fill whole 16-column tiles.
+constexpr int kPullNY = 3, kPullNZ = 3;
+__host__ __device__ constexpr int pull_vx(int C) { return C == 1 ? 16 : 8; }
+__host__ __device__ constexpr int pull_lat(int C) { return 16 * pull_vx(C); }   // vertices of a block's lattice
+struct PullBlocks {
+  int x, y, z;
+  __host__ __device__ int64_t total() const { return (int64_t)x * y * z; }
+};
+__host__ __device__ inline PullBlocks pull_blocks(int R, int C) {
+  const int R1 = R - 1, nx = pull_vx(C) - 1;
+  PullBlocks b;
+  b.x = (R1 + nx - 1) / nx;
+  b.y = (R1 + kPullNY - 1) / kPullNY;
+  b.z = (R1 + kPullNZ - 1) / kPullNZ;
+  return b;
+}
+
+// Inclusive scan over the wave's lanes by DPP: row_shr 1, 2, 4, 8 within rows of 16 lanes,
+// then row_bcast 15 and 31 carry a row's last lane into the next rows (lanes without a source
+// take 0).
+template <int CTRL, int ROWS>
+__device__ inline uint32_t dpp_or0(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xf, false);
+}
+__device__ inline uint32_t wave_scan_add(uint32_t v) {
+  v += dpp_or0<0x111, 0xf>(v);
+  v += dpp_or0<0x112, 0xf>(v);
+  v += dpp_or0<0x114, 0xf>(v);
+  v += dpp_or0<0x118, 0xf>(v);
+  v += dpp_or0<0x142, 0xa>(v);
+  v += dpp_or0<0x143, 0xc>(v);
+  return v;
+}
+__device__ inline void wave_lds_order() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+// Operand slots in LDS, element-major: element e (0..15, a row or column of a tile) of slot s at
+// e * kSlotPitch + s.  Four floats of padding per element row put the 16 bytes that 8 lanes read
+// (neighbouring elements, one quad of slots) into distinct banks.  32 slots at a time (a step's
+// matches beyond them go in a second round): the wave's LDS is what limits the waves per SIMD.
+constexpr int kSlots = 32, kSlotPitch = kSlots + 4;
+// The value of a wave-uniform double in scalar registers.
+__device__ inline double uniform_f64(double v) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, v);
+  const uint64_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)b);
+  const uint64_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(b >> 32));
+  return __builtin_bit_cast(double, lo | hi << 32);
+}
+
 // DG: also the transform gradient of L_rec through the trilinear weights: every lane adds
-// the terms of the records it produces (in step order) to its own 12 sums, reduced per
+// the terms of the points it matched (in step order) to its own 12 sums, reduced per
 // workgroup in a fixed order into dGpart[model][g][group][12].
 // TS = 2: the 4-D grids of Sec. 9, one pass per time cell ("model" index = time cell tc over
 // one shared point array sorted by (time cell, bin); start = [tc][NB^3] positions in it, the
 // records (x, y, z, t), dL/dy [M][n][C]); a point of cell tc adds (1 - wt) w_q dL/dy to the
-// cell's slice-0 corners and wt w_q dL/dy to its slice-1 corners (time weight wt, Eq. (2)
-// extended by linear interpolation in time), written as CC[tc][g][slice][8][cells][C].
-template <int C, bool GF16, int G, bool DG, int TS = 1>
-__global__ void __launch_bounds__(256) k_cell_pull_wave(CellArgs a) {
-  static_assert(G == 1 || G == 2 || G == 4 || G == 8, "lanes per run");
+// block's slice-0 lattice and wt w_q dL/dy to its slice-1 lattice (time weight wt, Eq. (2)
+// extended by linear interpolation in time).
+// SPLIT: the four waves of a workgroup share one block (wave w takes steps w, w + 4, ... and the
+// four lattices are added in wave order); otherwise each wave has a block of its own.
+// Output: lattices CC[model][g][block][vz 4][vy 4][vx][channel + C slice].
+template <int C, bool GF16, bool DG, int TS, bool SPLIT>
+__global__ void __launch_bounds__(256, DG || C * TS > 2 ? 4 : 6) k_block_pull(CellArgs a) {
   static_assert(TS == 1 || (TS == 2 && !DG), "the 4-D pass has no transform gradient");
-  constexpr int NR = 64 / G;                 // runs per batch
-  constexpr int RW = 2 * C * TS;             // float4 words per record: the 8 TS C products w_q dL/dy_c
-  __shared__ float4 sRec[4][64][RW];
-  __shared__ float sG[4][12];
-  __shared__ uint32_t sRow0[4][kRowBatch];   // first sorted position of each row of the batch
-  __shared__ uint32_t sPre[4][kRowBatch + 1];  // exclusive prefix of the rows' lengths; [kRowBatch] = total
+  constexpr int VX = pull_vx(C), CT = C * TS;
+  constexpr int NT = VX * CT / 16;           // 16-column tiles; column = vx CT + channel (+ C slice)
+  constexpr int LAT = pull_lat(C) * C * TS;  // floats of a block's lattice
+  constexpr int nbk[3] = {VX - 1, kPullNY, kPullNZ};
+  // operand slots: the 16 row factors, then the column factors, 16 per tile
+  __shared__ float sOp[4][(1 + NT) * 16 * kSlotPitch];
+  __shared__ uint64_t sEnd[4][kWindow / 64];  // bit f: candidate f of the window ends a row
+  __shared__ uint32_t sDelta[4][kRowBatch + 1];   // per non-empty row: sorted position minus flat index
   __shared__ double sDG[DG ? 4 : 1][12];
-  // TS = 1: the block's (kBlk + 1)^3 vertex lattice, C values per vertex
-  __shared__ float sLat[TS == 1 ? 4 : 1][TS == 1 ? kLat * C : 1];
   const Shape s = a.s;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int R1 = s.R - 1;
-  const int nbx = (R1 + kBlk - 1) / kBlk;
-  const int64_t nblk_grid = (int64_t)nbx * nbx * nbx;            // cell blocks per grid
-  const int64_t groups = (nblk_grid + 3) / 4;                   // 4 waves per workgroup
-  const int64_t per_model = groups * s.M;
-  const int64_t L = xcd_logical(blockIdx.x, gridDim.x);
-  const int model = (int)(L / per_model);
-  const int64_t grp = (L % per_model) / s.M;
-  const int g = (int)(L % s.M);
-  const int64_t cb = grp * 4 + wave;                            // this wave's cell block
+  const PullBlocks nb = pull_blocks(s.R, C);
+  const uint32_t nblk_grid = (uint32_t)nb.total();               // cell blocks per grid (the launch fits 2^31)
+  const uint32_t groups = SPLIT ? nblk_grid : (nblk_grid + 3) / 4;
+  const uint32_t L = xcd_logical32(blockIdx.x, gridDim.x);
+  const uint32_t mg = L / s.M, g = L - mg * s.M;                  // (model, group) and grid
+  const uint32_t model = mg / groups, grp = mg - model * groups;
+  const uint32_t cb = SPLIT ? grp : grp * 4 + __builtin_amdgcn_readfirstlane(wave);   // this wave's cell block
   const bool act = (TS == 2 || !a.active || a.active[model]) && cb < nblk_grid;
-  if (lane < 12) sG[wave][lane] = a.G[model * a.G_stride + 12 * g + lane];
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  const float* Gg = sG[wave];
-  const int bx = (int)(cb % nbx), by = (int)((cb / nbx) % nbx), bz = (int)(cb / ((int64_t)nbx * nbx));
-  const int cx = bx * kBlk + (lane & 3), cy = by * kBlk + ((lane >> 2) & 3), cz = bz * kBlk + (lane >> 4);
-  const bool own = act && cx < R1 && cy < R1 && cz < R1;
-  float acc[8 * TS][C];
+  float Gg[12];                                                  // uniform: scalar loads
 #pragma unroll
-  for (int q = 0; q < 8 * TS; ++q)
+  for (int k = 0; k < 12; ++k) Gg[k] = a.G[model * a.G_stride + 12 * g + k];
+  for (int i = 4 * lane; i < (1 + NT) * 16 * kSlotPitch; i += 256) *(f32x4*)(sOp[wave] + i) = f32x4{0.f, 0.f, 0.f, 0.f};
+  wave_lds_order();
+  f32x4 acc[NT];
 #pragma unroll
-    for (int c = 0; c < C; ++c) acc[q][c] = 0.f;
+  for (int t = 0; t < NT; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
   float gacc[DG ? 12 : 1];
 #pragma unroll
   for (int k = 0; k < (DG ? 12 : 1); ++k) gacc[k] = 0.f;
   if (act) {
     // the block's box in global space (inverse of Eq. (1) applied to its local box)
+    const uint32_t cyz = cb / (uint32_t)nb.x, cz = cyz / (uint32_t)nb.y;
+    const int b0[3] = {(int)(cb - cyz * nb.x) * nbk[0], (int)(cyz - cz * nb.y) * nbk[1], (int)cz * nbk[2]};
     double A[3][3];
     for (int r = 0; r < 3; ++r) for (int c = 0; c < 3; ++c) A[r][c] = Gg[4 * r + c];
     const double c00 = A[1][1] * A[2][2] - A[1][2] * A[2][1], c01 = A[1][2] * A[2][0] - A[1][0] * A[2][2];
@@ -343,18 +425,18 @@ __global__ void __launch_bounds__(256) k_cell_pull_wave(CellArgs a) {
                            c02, A[0][1] * A[2][0] - A[0][0] * A[2][1], A[0][0] * A[1][1] - A[0][1] * A[1][0]};
     bool bad = !(fabs(det) > 1e-30);
     float Ai[9];
-    const double rdet = 1.0 / det;
+    const double rdet = recip_f64(det);
     for (int k = 0; k < 9; ++k) { Ai[k] = (float)(inv[k] * rdet); bad = bad || !isfinite(Ai[k]); }
     int lo[3], hi[3];
-    const int b0[3] = {bx * kBlk, by * kBlk, bz * kBlk};
     if (bad) {
       for (int d = 0; d < 3; ++d) { lo[d] = 0; hi[d] = kBinsPerAxis - 1; }
     } else {
       float lm[3], hl[3];
       for (int d = 0; d < 3; ++d) {
-        const int e = min(b0[d] + kBlk, R1);
-        lm[d] = -1.f + (float)(b0[d] + e) / R1 - Gg[4 * d + 3];   // box centre minus the translation
-        hl[d] = (float)(e - b0[d]) / R1;                           // box half-width (local units)
+        const int e = min(b0[d] + nbk[d], R1);
+        const float hc = 0.5f * (float)a.cell;
+        lm[d] = -1.f + (float)(b0[d] + e) * hc - Gg[4 * d + 3];   // box centre minus the translation
+        hl[d] = (float)(e - b0[d]) * hc;                           // box half-width (local units)
       }
       for (int d = 0; d < 3; ++d) {
         const float wc = Ai[3 * d] * lm[0] + Ai[3 * d + 1] * lm[1] + Ai[3 * d + 2] * lm[2];
@@ -367,210 +449,250 @@ __global__ void __launch_bounds__(256) k_cell_pull_wave(CellArgs a) {
     }
     constexpr size_t kNB3 = (size_t)kBinsPerAxis * kBinsPerAxis * kBinsPerAxis;
     const float4* P4 = TS == 1 ? a.pts4 + (size_t)model * a.n : a.pts4;
-    const float* dY = a.dY + ((size_t)(TS == 1 ? model : 0) * s.M + g) * a.n * C;
+    const float* dY = a.dY + (TS == 1 ? model * a.dY_stride : 0) + (size_t)g * a.dY_grid;
     const uint32_t* start = a.start + (size_t)model * (TS == 1 ? kNB3 + 1 : kNB3);
     const float ht = 0.5f * (float)(a.Rt - 1);
     const float hR = 0.5f * (float)R1;
+    double blo[3], bhi[3], ra[3];
+    local_box(Gg, b0, nbk, R1, a.cell, blo, bhi);
+    span_recips(Gg, ra);
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+      blo[d] = uniform_f64(blo[d]);
+      bhi[d] = uniform_f64(bhi[d]);
+      ra[d] = uniform_f64(ra[d]);
+      lo[d] = __builtin_amdgcn_readfirstlane(lo[d]);
+      hi[d] = __builtin_amdgcn_readfirstlane(hi[d]);
+    }
     const int ny_r = hi[1] - lo[1] + 1, nz_r = hi[2] - lo[2] + 1;
     const int nrows = ny_r * nz_r;
-    double blo[3], bhi[3], ra[3];
-    local_box(Gg, b0, kBlk, R1, blo, bhi);
-    span_recips(Gg, ra);
-    // A candidate: its point and dL/dy, loaded for every lane (a lane past the end of its run
-    // loads point 0), so the loads of the next step are in flight while this one is used.
-    struct Cand { float4 q; float dy[C]; bool valid; };
-    // the lane's place in its run: flat index f (< fend), row r, sorted position p, and the
-    // points left in row r from p on
-    uint32_t f = 0, fend = 0, p = 0, rem = 0;
-    int r = 0;
-    auto load = [&](Cand& cd) {
-      cd.valid = f < fend;
-      const uint32_t pp = cd.valid ? p : 0u;
-      cd.q = P4[pp];
+    // the block's cells on an axis: u - ulo in [0, width), cells 0 .. cmax (the grid's last cell
+    // includes u = R - 1)
+    float ulo[3], cmax[3];
+    uint32_t uwid[3];
 #pragma unroll
-      for (int c = 0; c < C; ++c) cd.dy[c] = dY[(size_t)pp * C + c];
-      if (cd.valid) {
-        f += G;
-        if (f < fend) {                      // move G points on, across rows (the one holding f exists)
-          uint32_t k = G;
-          while (k >= rem) {
-            k -= rem;
-            do { ++r; } while (sPre[wave][r + 1] == sPre[wave][r]);
-            p = sRow0[wave][r];
-            rem = sPre[wave][r + 1] - sPre[wave][r];
-          }
-          p += k;
-          rem -= k;
-        }
-      }
-    };
+    for (int d = 0; d < 3; ++d) {
+      const bool last = b0[d] + nbk[d] >= R1;
+      ulo[d] = (float)b0[d];
+      uwid[d] = __float_as_uint(last ? __builtin_inff() : (float)nbk[d]);
+      cmax[d] = (float)(last ? R1 - b0[d] - 1 : nbk[d] - 1);
+    }
     const void* Fm = GF16 ? (const void*)((const __half*)a.F + model * a.F_stride)
                           : (const void*)((const float*)a.F + model * a.F_stride);
+    struct Cand { float4 q; float dy[C]; bool valid; };
+    // lane roles as matrix operands: element e16 of the slots 16 m + 4 k4 + q (q = 0..3 in four
+    // instructions)
+    const int e16 = lane & 15, k4 = lane >> 4;
+    float* ops = sOp[wave];
+    const float* rd = ops + e16 * kSlotPitch + 4 * k4;
     auto consume = [&](const Cand& cd) {
-      int t = -1;
-      float w[3] = {0.f, 0.f, 0.f};
-      int i0[3] = {0, 0, 0};
-      float wt = 0.f;
-      if (cd.valid) {
-        float l[3];
-        local_coords(Gg, cd.q.x, cd.q.y, cd.q.z, l);
-        bool in = cell_of(l, hR, s.R, i0, w);
-        if constexpr (TS == 2) {
-          // the time cell and weight as the 4-D lookup takes them; times outside [-1, 1] add nothing
-          const float tq = cd.q.w;
-          const float ut = __builtin_fmaf(tq, ht, ht);
-          const float ft = fminf(fmaxf(floorf(ut), 0.0f), (float)(a.Rt - 2));
-          in = in && tq >= -1.0f && tq <= 1.0f && (int)ft == model;
-          wt = ut - ft;
-        }
-        const int ox = i0[0] - b0[0], oy = i0[1] - b0[1], oz = i0[2] - b0[2];
-        if (in && ox >= 0 && ox < kBlk && oy >= 0 && oy < kBlk && oz >= 0 && oz < kBlk)
-          t = (oz * kBlk + oy) * kBlk + ox;
+      float l[3], u[3], t[3];
+      local_coords(Gg, cd.q.x, cd.q.y, cd.q.z, l);
+      // the cell decision of Eq. (2): u = fma(l, h, h) is negative below the grid, l <= 1 bounds
+      // it above; t = u - (first cell) is exact, and as bits unsigned it is below the width's only
+      // for 0 <= t < width (not for a negative value or a NaN)
+      bool in = cd.valid && fmaxf(fmaxf(l[0], l[1]), l[2]) <= 1.0f;
+#pragma unroll
+      for (int d = 0; d < 3; ++d) {
+        u[d] = __builtin_fmaf(l[d], hR, hR);
+        t[d] = u[d] - ulo[d];
+        in = in && __float_as_uint(t[d]) < uwid[d];
       }
-      if (t >= 0) {
-        float pr[8 * TS * C];
+      float wt = 0.f;
+      if constexpr (TS == 2) {
+        // the time cell and weight as the 4-D lookup takes them; times outside [-1, 1] add nothing
+        const float tq = cd.q.w;
+        const float ut = __builtin_fmaf(tq, ht, ht);
+        const float ft = fminf(fmaxf(floorf(ut), 0.0f), (float)(a.Rt - 2));
+        in = in && tq >= -1.0f && tq <= 1.0f && (int)ft == model;
+        wt = ut - ft;
+      }
+      // a non-finite dL/dy times the zero of a hat function would reach every vertex of the block:
+      // such points (none in a healthy run) are added to their cell's corners alone
+      float fl[3], w[3];                       // cell in the block and offsets
 #pragma unroll
-        for (int sl = 0; sl < TS; ++sl)
+      for (int d = 0; d < 3; ++d) {
+        fl[d] = fminf(floorf(t[d]), cmax[d]);
+        w[d] = t[d] - fl[d];
+      }
+      bool wild = false;
 #pragma unroll
-          for (int qq = 0; qq < 8; ++qq) {
-            const float wq = TS == 1 ? corner_weight(qq, w) : (sl ? wt : 1.f - wt) * corner_weight(qq, w);
+      for (int c = 0; c < C; ++c) wild = wild || !(fabsf(cd.dy[c]) < __builtin_inff());
+      uint64_t wmask = __ballot(in && wild);
+      const bool fin = in && !wild;
+      const uint64_t mask = __ballot(fin);
+      const int v = __popcll(mask);
+      if (wmask) {
+        do {
+          const int k = __builtin_ctzll(wmask);
+          wmask &= wmask - 1;
+          float uk[3], dk[C];
+          for (int d = 0; d < 3; ++d) uk[d] = __shfl(t[d], k, 64);
+          for (int c = 0; c < C; ++c) dk[c] = __shfl(cd.dy[c], k, 64);
+          const float wk = __shfl(wt, k, 64);
+          float wz, wy[4];
+          const auto corner = [&](int d, int vtx, float& wgt) {   // weight of a corner of the point's cell
+            const float fl = fminf(floorf(uk[d]), cmax[d]), w = uk[d] - fl;
+            wgt = (float)vtx == fl ? 1.f - w : w;
+            return (float)vtx == fl || (float)vtx == fl + 1.f;
+          };
+          const bool oz = corner(2, k4, wz);
+          bool oy[4];
+          for (int r = 0; r < 4; ++r) oy[r] = corner(1, r, wy[r]);
 #pragma unroll
-            for (int c = 0; c < C; ++c) pr[(8 * sl + qq) * C + c] = corner_product(wq, cd.dy[c]);
+          for (int j = 0; j < NT; ++j) {
+            const int col = 16 * j + e16, ch = col % CT;
+            float wx, d = dk[0];
+            const bool ox = corner(0, col / CT, wx);
+#pragma unroll
+            for (int c = 1; c < C; ++c) d = ch % C == c ? dk[c] : d;
+            const float ws = TS == 1 ? 1.f : ch / C ? wk : 1.f - wk;
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+              if (oz && oy[r] && ox) acc[j][r] += ws * (wx * wy[r] * wz) * d;
           }
+        } while (wmask);
+      }
+      if constexpr (DG) {
+        if (in) {
+          int i0[3];
 #pragma unroll
-        for (int k = 0; k < RW; ++k)
-          sRec[wave][lane][k] = make_float4(pr[4 * k], pr[4 * k + 1], pr[4 * k + 2], pr[4 * k + 3]);
-        if constexpr (DG) {
+          for (int d = 0; d < 3; ++d) i0[d] = b0[d] + (int)fl[d];
           float val[8][C];
           gather_cell<C, GF16>(Fm, g, s.R, i0, val);
           add_transform_grad<C>(val, w, cd.dy, hR, true, cd.q.x, cd.q.y, cd.q.z, gacc);
         }
       }
-      // lanes whose point falls in my cell: agree on every bit of the target
-      const bool has = t >= 0;
-      uint64_t mask = __ballot(has);
+      if (v == 0) return;
+      const int rk = __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+      float* pa = ops + (int)__builtin_fmaf(fl[2], 4.f * kSlotPitch, fl[1] * kSlotPitch) + rk;
+      float* pb = ops + (int)__builtin_fmaf(fl[0], (float)(CT * kSlotPitch), 16.f * kSlotPitch) + rk;
+      const float wy0 = 1.f - w[1], wz0 = 1.f - w[2], wx0 = 1.f - w[0];
+      for (int h = 0; h < v; h += kSlots) {
+        const bool mine = fin && (uint32_t)(rk - h) < (uint32_t)kSlots;
+        if (mine) {
+          pa[0] = wz0 * wy0;
+          pa[kSlotPitch] = wz0 * w[1];
+          pa[4 * kSlotPitch] = w[2] * wy0;
+          pa[5 * kSlotPitch] = w[2] * w[1];
 #pragma unroll
-      for (int b = 0; b < 6; ++b) {
-        const uint64_t bb = __ballot(has && ((t >> b) & 1));
-        mask &= ((lane >> b) & 1) ? bb : ~bb;
-      }
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-      while (mask) {
-        const int k = __builtin_ctzll(mask);
-        mask &= mask - 1;
-#pragma unroll
-        for (int j4 = 0; j4 < RW; ++j4) {
-          const float4 v = sRec[wave][k][j4];
-          const float vv[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const int idx = 4 * j4 + e;
-            acc[idx / C][idx % C] = add_rounded(acc[idx / C][idx % C], vv[e]);
+          for (int ch = 0; ch < CT; ++ch) {
+            float d = cd.dy[ch % C];
+            if constexpr (TS == 2) d *= ch / C ? wt : 1.f - wt;
+            pb[ch * kSlotPitch] = wx0 * d;
+            pb[(CT + ch) * kSlotPitch] = w[0] * d;
           }
         }
+        wave_lds_order();
+        const int left = v - h;
+#pragma unroll
+        for (int m = 0; m < kSlots; m += 16) {
+          if (m > 0 && m >= left) break;
+          const f32x4 av = *(const f32x4*)(rd + m);
+          f32x4 bv[NT];
+#pragma unroll
+          for (int j = 0; j < NT; ++j) bv[j] = *(const f32x4*)(rd + m + 16 * (1 + j) * kSlotPitch);
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int j = 0; j < NT; ++j)
+              acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[q], bv[j][q], acc[j], 0, 0, 0);
+        }
+        wave_lds_order();
+        if (mine) {
+          pa[0] = 0.f;
+          pa[kSlotPitch] = 0.f;
+          pa[4 * kSlotPitch] = 0.f;
+          pa[5 * kSlotPitch] = 0.f;
+#pragma unroll
+          for (int ch = 0; ch < 2 * CT; ++ch) pb[ch * kSlotPitch] = 0.f;
+        }
+        pa -= kSlots;
+        pb -= kSlots;
       }
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      wave_lds_order();
     };
     // rows (z outer, y inner) kRowBatch at a time; each batch's points are one flat sequence
     for (int rb = 0; rb < nrows; rb += kRowBatch) {
-      uint32_t s0[2] = {0, 0}, len[2] = {0, 0};
-#pragma unroll
-      for (int k = 0; k < 2; ++k) {
-        const int rr = rb + 2 * lane + k;
+      uint32_t s0 = 0, len = 0;
+      const int rr = rb + lane;
+      if (rr < nrows) {
         int x0 = lo[0], x1 = hi[0];
-        if (rr < nrows) {
-          const int yb = lo[1] + rr % ny_r, zb = lo[2] + rr / ny_r;
-          if (bad || row_x_span(Gg, ra, blo, bhi, lo[0], hi[0], yb, zb, x0, x1)) {
-            const int row = (zb * kBinsPerAxis + yb) * kBinsPerAxis;
-            s0[k] = start[row + x0];
-            len[k] = start[row + x1 + 1] - s0[k];
-          }
+        const int yb = lo[1] + rr % ny_r, zb = lo[2] + rr / ny_r;
+        if (bad || row_x_span(Gg, ra, blo, bhi, lo[0], hi[0], yb, zb, x0, x1)) {
+          const int row = (zb * kBinsPerAxis + yb) * kBinsPerAxis;
+          s0 = start[row + x0];
+          len = start[row + x1 + 1] - s0;
         }
       }
-      uint32_t x = len[0] + len[1];
+      const uint32_t incl = wave_scan_add(len);
+      const uint32_t total = __builtin_amdgcn_readlane(incl, 63);
+      const uint32_t end = len > 0 ? incl : 0xffffffffu;         // past the row's last candidate
+      const uint64_t full = __ballot(len > 0);
+      // non-empty rows in order: their offset from flat index to sorted position
+      if (len > 0) sDelta[wave][__builtin_amdgcn_mbcnt_hi((uint32_t)(full >> 32),
+                                                          __builtin_amdgcn_mbcnt_lo((uint32_t)full, 0u))] = s0 + len - incl;
+      constexpr uint32_t kStep = SPLIT ? 256 : 64, kFirst = SPLIT ? 64 : 0;
+      Cand ca, cn;
+      for (uint32_t wb = 0; wb < total; wb += kWindow) {
+        sEnd[wave][lane] = 0;
+        wave_lds_order();
+        if (end - 1u - wb < kWindow) atomicOr((uint32_t*)sEnd[wave] + ((end - 1u - wb) >> 5), 1u << ((end - 1u) & 31));
+        wave_lds_order();
+        // candidate f = base + lane lies in the row after those that end before it: the rows that
+        // end before the step, plus the row ends among the step's earlier candidates
+        auto load = [&](uint32_t base, Cand& cd) {
+          const uint64_t em = sEnd[wave][(base - wb) >> 6];
+          const uint32_t before = (uint32_t)__popcll(__ballot(end <= base));
+          const uint32_t row =
+              __builtin_amdgcn_mbcnt_hi((uint32_t)(em >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)em, before));
+          const uint32_t f = base + (uint32_t)lane;
+          cd.valid = f < total;
+          const uint32_t delta = sDelta[wave][row];   // (row is at most kRowBatch, past the last candidate)
+          const uint32_t pp = cd.valid ? f + delta : 0u;
+          cd.q = P4[pp];
 #pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t y = __shfl_up(x, o, 64);
-        if (lane >= o) x += y;
+          for (int c = 0; c < C; ++c) cd.dy[c] = dY[(size_t)pp * C + c];
+        };
+        const uint32_t we = min(total, wb + kWindow);
+        uint32_t base = wb + kFirst * (uint32_t)wave;
+        if (base < we) load(base, ca);
+        for (; base < we; base += kStep) {
+          if (base + kStep < we) load(base + kStep, cn);
+          consume(ca);
+          ca = cn;
+        }
       }
-      const uint32_t total = __shfl(x, 63, 64);
-      const uint32_t ex = x - len[0] - len[1];
-      sRow0[wave][2 * lane] = s0[0];
-      sRow0[wave][2 * lane + 1] = s0[1];
-      sPre[wave][2 * lane] = ex;
-      sPre[wave][2 * lane + 1] = ex + len[0];
-      if (lane == 0) sPre[wave][kRowBatch] = total;
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-      // runs of S points (a multiple of G; the last runs may be shorter), S / G steps
-      const uint32_t S = ((total + NR - 1) / NR + G - 1) / G * G;
-      const uint32_t f0 = min((uint32_t)(lane / G) * S, total);
-      fend = min(f0 + S, total);
-      f = f0 + (uint32_t)(lane % G);
-      if (f < fend) {
-        // the row holding f: the last row whose exclusive prefix is <= f (it is non-empty)
-        r = 0;
-#pragma unroll
-        for (int step = kRowBatch / 2; step >= 1; step >>= 1)
-          if (sPre[wave][r + step] <= f) r += step;
-        p = sRow0[wave][r] + (f - sPre[wave][r]);
-        rem = sPre[wave][r + 1] - f;
-      }
-      const uint32_t nsteps = S / G;
-      Cand ca, cbn;
-      load(ca);
-      for (uint32_t st = 0; st < nsteps; st += 2) {
-        load(cbn);
-        sched_barrier();
-        consume(ca);
-        load(ca);
-        sched_barrier();
-        if (st + 1 < nsteps) consume(cbn);
-      }
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     }
   }
-  if constexpr (TS == 1) {
-    // the block's cells fold their corner sums into its vertex lattice: in phase q every
-    // owner adds its corner q to vertex cell + offset(q), which no other cell of the block
-    // addresses in that phase (a fixed order, no atomics); the lattice is written whole, and
-    // k_block_to_vertex adds the lattices of the (up to 8) blocks that share a vertex
-    float* lat = sLat[wave];
-    for (int i = lane; i < kLat * C; i += 64) lat[i] = 0.f;
-    const int lx = lane & 3, ly = (lane >> 2) & 3, lz = lane >> 4;
+  float* out = a.CC + (((size_t)model * s.M + g) * nblk_grid + cb) * LAT;
+  // D[i][j]: lane j + 16 vz, register vy; column 16 t + j
+  auto lat_index = [&](int t, int r) { return ((lane >> 4) * 4 + r) * (VX * CT) + 16 * t + (lane & 15); };
+  if constexpr (!SPLIT) {
+    if (act) {
 #pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-      if (own) {
-        const int v = ((lz + (q >> 2)) * (kBlk + 1) + ly + ((q >> 1) & 1)) * (kBlk + 1) + lx + (q & 1);
+      for (int t = 0; t < NT; ++t)
 #pragma unroll
-        for (int c = 0; c < C; ++c) lat[v * C + c] = add_rounded(lat[v * C + c], acc[q][c]);
+        for (int r = 0; r < 4; ++r) out[lat_index(t, r)] = acc[t][r];
+    }
+  } else {
+    // the four waves' lattices, added in wave order (the operand slots are free by now; a wave
+    // writes only its own)
+    static_assert(LAT <= (1 + NT) * 16 * kSlotPitch, "a lattice fits a wave's operand slots");
+    float* mine = sOp[wave];
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) mine[lat_index(t, r)] = acc[t][r];
+    __syncthreads();
+    if (act) {
+      for (int i = threadIdx.x; i < LAT; i += 256) {
+        float sum = 0.f;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) sum = add_rounded(sum, sOp[w][i]);
+        out[i] = sum;
       }
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    if (act) {
-      float* out = a.CC + (((size_t)model * s.M + g) * nblk_grid + cb) * kLat * C;
-      for (int i = lane; i < kLat * C; i += 64) out[i] = lat[i];
-    }
-  } else if (own) {
-    const int64_t cell = ((int64_t)cz * R1 + cy) * R1 + cx;
-    const int64_t ncell = (int64_t)R1 * R1 * R1;
-    float* out = a.CC + ((size_t)model * s.M + g) * 8 * TS * ncell * C + cell * C;
-#pragma unroll
-    for (int q = 0; q < 8 * TS; ++q)
-#pragma unroll
-      for (int c = 0; c < C; ++c) out[q * ncell * C + c] = acc[q][c];
   }
   if constexpr (DG) {
 #pragma unroll
@@ -587,8 +709,8 @@ __global__ void __launch_bounds__(256) k_cell_pull_wave(CellArgs a) {
 }
 
 // dF[model][g][v][c] (+)= sum over the cells adjacent to vertex v of their corner sums.
-template <int C>
 // dF in the paper's order [M][C][R^3] when paper != 0, else channel-last [M][R^3][C].
+template <int C>
 __global__ void k_cell_to_vertex(Shape s, const float* CC, float* dF, size_t dF_stride, int paper, int accumulate,
                                  const int32_t* active) {
   const int model = blockIdx.z, g = blockIdx.y;
@@ -616,41 +738,52 @@ __global__ void k_cell_to_vertex(Shape s, const float* CC, float* dF, size_t dF_
   }
 }
 
-// dF[model][g][v][c] (+)= sum over the cell blocks that contain vertex v of their lattice
-// values (the dense wave gather's output, [model][M][blocks][kLat][C]; along each axis a
-// vertex at a block boundary belongs to two blocks), in a fixed order.  dF layout as for
-// k_cell_to_vertex.
+// Sum over the cell blocks that contain vertex (x, y, z) of their lattice values of channels
+// [ch0, ch0 + C) of CT (bl = the grid's first lattice; along each axis a vertex at a block
+// boundary belongs to two blocks), in a fixed order.
+template <int C, int CT>
+__device__ inline void lattice_sum(const float* bl, const PullBlocks& nb, int ch0, int x, int y, int z, float sum[C]) {
+  constexpr int VX = pull_vx(C);
+  constexpr int nbk[3] = {VX - 1, kPullNY, kPullNZ};
+  typedef float vec __attribute__((ext_vector_type(C), aligned(4 * C)));
+  const int vc[3] = {x, y, z}, nn[3] = {nb.x, nb.y, nb.z};
+  int b0[3], b1[3];
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    // blocks b with 0 <= vc - nbk b <= nbk: the lower one (vc on its upper face) first
+    const int q = vc[d] / nbk[d];
+    b1[d] = min(q, nn[d] - 1);
+    b0[d] = (q * nbk[d] == vc[d] && q > 0) ? q - 1 : b1[d];
+  }
+#pragma unroll
+  for (int c = 0; c < C; ++c) sum[c] = 0.f;
+  for (int bz = b0[2]; bz <= b1[2]; ++bz)
+    for (int by = b0[1]; by <= b1[1]; ++by)
+      for (int bx = b0[0]; bx <= b1[0]; ++bx) {
+        const vec v = *(const vec*)(bl + ((((size_t)(bz * nb.y + by) * nb.x + bx) * 16 + (vc[2] - nbk[2] * bz) * 4 +
+                                          (vc[1] - nbk[1] * by)) * VX + (vc[0] - nbk[0] * bx)) * CT + ch0);
+        if constexpr (C == 1) sum[0] += v[0];
+        else {
+#pragma unroll
+          for (int c = 0; c < C; ++c) sum[c] += v[c];
+        }
+      }
+}
+
+// dF[model][g][v][c] (+)= the lattice sums of every vertex (the output of k_block_pull).  dF
+// layout as for k_cell_to_vertex.
 template <int C>
 __global__ void k_block_to_vertex(Shape s, const float* BL, float* dF, size_t dF_stride, int paper, int accumulate,
                                   const int32_t* active) {
   const int model = blockIdx.z, g = blockIdx.y;
   if (active && !active[model]) return;
-  const int R = s.R, R1 = R - 1;
-  const int nbx = (R1 + kBlk - 1) / kBlk;
-  const int64_t nv = (int64_t)R * R * R;
-  const float* bl = BL + ((size_t)model * s.M + g) * ((size_t)nbx * nbx * nbx) * kLat * C;
-  for (int64_t v = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; v < nv; v += (int64_t)gridDim.x * blockDim.x) {
-    const int vc[3] = {(int)(v % R), (int)((v / R) % R), (int)(v / ((int64_t)R * R))};
-    int b0[3], nb[3];
-    for (int d = 0; d < 3; ++d) {
-      // blocks b with 0 <= vc - kBlk b <= kBlk: the lower one (vc on its upper face) first
-      const int hi = min(vc[d] / kBlk, nbx - 1);
-      b0[d] = (vc[d] % kBlk == 0 && vc[d] > 0 && hi == vc[d] / kBlk) ? hi - 1 : hi;
-      nb[d] = hi - b0[d] + 1;
-    }
+  const uint32_t R = s.R, nv = R * R * R;    // (a grid holds fewer than 2^31 values)
+  const PullBlocks nb = pull_blocks(R, C);
+  const float* bl = BL + ((size_t)model * s.M + g) * nb.total() * pull_lat(C) * C;
+  for (uint32_t v = blockIdx.x * blockDim.x + threadIdx.x; v < nv; v += gridDim.x * blockDim.x) {
+    const uint32_t yz = v / R, z = yz / R;
     float sum[C];
-#pragma unroll
-    for (int c = 0; c < C; ++c) sum[c] = 0.f;
-    for (int iz = 0; iz < nb[2]; ++iz)
-      for (int iy = 0; iy < nb[1]; ++iy)
-        for (int ix = 0; ix < nb[0]; ++ix) {
-          const int bx = b0[0] + ix, by = b0[1] + iy, bz = b0[2] + iz;
-          const int lx = vc[0] - kBlk * bx, ly = vc[1] - kBlk * by, lz = vc[2] - kBlk * bz;
-          const float* src = bl + (((size_t)(bz * nbx + by) * nbx + bx) * kLat +
-                                   (lz * (kBlk + 1) + ly) * (kBlk + 1) + lx) * C;
-#pragma unroll
-          for (int c = 0; c < C; ++c) sum[c] += src[c];
-        }
+    lattice_sum<C, C>(bl, nb, 0, (int)(v - yz * R), (int)(yz - z * R), (int)z, sum);
     float* dst = dF + model * dF_stride + (paper ? (size_t)g * C * nv + v : ((size_t)g * nv + v) * C);
     const size_t cs = paper ? (size_t)nv : 1;
 #pragma unroll
@@ -658,16 +791,16 @@ __global__ void k_block_to_vertex(Shape s, const float* BL, float* dF, size_t dF
   }
 }
 
-// 4-D grids: dF[g][t][v][c] += the slice-0 corner sums of time cell t and the slice-1 corner
-// sums of time cell t - 1 over the cells adjacent to vertex v (CC of the TS = 2 gather,
-// dF channel-last [M][Rt][R^3][C]); a fixed order.
+// 4-D grids: dF[g][t][v][c] (+)= the slice-0 lattice sums of time cell t and the slice-1 sums
+// of time cell t - 1 (the output of the TS = 2 pass); a fixed order.  dF in the paper's order
+// [M][C][Rt][R^3] when paper != 0, else channel-last [M][Rt][R^3][C].
 template <int C>
-__global__ void k_cell_to_vertex_time(Shape s, int Rt, const float* CC, float* dF) {
+__global__ void k_block_to_vertex_time(Shape s, int Rt, const float* BL, float* dF, int paper, int accumulate) {
   const int g = blockIdx.y, tv = blockIdx.z;
-  const int R = s.R, R1 = R - 1;
-  const int64_t nv = (int64_t)R * R * R, ncell = (int64_t)R1 * R1 * R1;
-  for (int64_t v = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; v < nv; v += (int64_t)gridDim.x * blockDim.x) {
-    const int vx = (int)(v % R), vy = (int)((v / R) % R), vz = (int)(v / ((int64_t)R * R));
+  const uint32_t R = s.R, nv = R * R * R;
+  const PullBlocks nb = pull_blocks(R, C);
+  for (uint32_t v = blockIdx.x * blockDim.x + threadIdx.x; v < nv; v += gridDim.x * blockDim.x) {
+    const uint32_t yz = v / R, z = yz / R;
     float sum[C];
 #pragma unroll
     for (int c = 0; c < C; ++c) sum[c] = 0.f;
@@ -675,19 +808,17 @@ __global__ void k_cell_to_vertex_time(Shape s, int Rt, const float* CC, float* d
     for (int sl = 0; sl < 2; ++sl) {
       const int tc = tv - sl;
       if (tc < 0 || tc > Rt - 2) continue;
-      const float* cc = CC + (((size_t)tc * s.M + g) * 16 + 8 * sl) * ncell * C;
+      const float* bl = BL + ((size_t)tc * s.M + g) * nb.total() * pull_lat(C) * C * 2;
+      float part[C];
+      lattice_sum<C, 2 * C>(bl, nb, C * sl, (int)(v - yz * R), (int)(yz - z * R), (int)z, part);
 #pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        const int cx = vx - (q & 1), cy = vy - ((q >> 1) & 1), cz = vz - (q >> 2);
-        if (cx < 0 || cy < 0 || cz < 0 || cx >= R1 || cy >= R1 || cz >= R1) continue;
-        const float* src = cc + ((q * ncell + ((int64_t)cz * R1 + cy) * R1 + cx)) * C;
-#pragma unroll
-        for (int c = 0; c < C; ++c) sum[c] += src[c];
-      }
+      for (int c = 0; c < C; ++c) sum[c] += part[c];
     }
-    float* dst = dF + (((size_t)g * Rt + tv) * nv + v) * C;
 #pragma unroll
-    for (int c = 0; c < C; ++c) dst[c] += sum[c];
+    for (int c = 0; c < C; ++c) {
+      float* dst = dF + (paper ? ((size_t)(g * C + c) * Rt + tv) * nv + v : (((size_t)g * Rt + tv) * nv + v) * C + c);
+      *dst = accumulate ? *dst + sum[c] : sum[c];
+    }
   }
 }
 

@@ -1474,7 +1474,15 @@ size_t variant_f_elems(const Shape& s, const EncArgs& ea, int kind) {
   return kind == APMG_ENC_HASH ? (size_t)s.M * ((size_t)ea.tmask + 1u) * s.C
                                : (size_t)s.M * ea.Rt * s.R * s.R * s.R * s.C;
 }
-inline int variant_nbx(int64_t n) { return (int)std::max<int64_t>(1, (n + 255) / 256); }
+inline int variant_nbx(int64_t n) { return (int)std::max<int64_t>(1, (n + 256 * kTgPoints - 1) / (256 * kTgPoints)); }
+// a hash level as the dense grids the block gather sees: the model's transforms, N + 1 vertices per axis
+inline Shape hash_level_shape(const Shape& s, const EncArgs& ea, int k) {
+  Shape t = s;
+  t.M = s.M / s.L;
+  t.R = enc_level_res(ea, k) + 1;
+  t.L = 1;
+  return t;
+}
 // 4-D grids with at most one radix digit of time cells are sorted by time cell as well
 inline bool time_sorted(const EncArgs& ea) { return ea.Rt - 1 <= kRadixDigits; }
 
@@ -1492,7 +1500,8 @@ struct VarWs {
   uint32_t *tk0, *tv0, *tk1, *tv1;
   float *tpts, *tdf;
   // and the atomic-free per-cell gather of the 4-D grid gradient: (x, y, z, t) records, the
-  // starts of every (time cell, bin) and the per-time-cell corner sums
+  // starts of every (time cell, bin); the lattices of the block gather (time grids: of every time
+  // cell; hash grids: of one level at a time)
   float4* trec; uint32_t* tstart; float* tcc;
   bool fsorted;    // forward from kFwdSortMin points on: the tiles walk a spatial order (srt keys only)
 };
@@ -1517,6 +1526,13 @@ size_t var_ws(const Shape& s, const EncArgs& ea, const apmg_model* m, const apmg
     w.dGpart = cv.take<double>((size_t)s.M * variant_nbx(n) * 12);
     if (time_paper && !time_sorted(ea)) w.dFcl = cv.take<float>(variant_f_elems(s, ea, e->kind));
     take_sort(cv, n, 1, true, &w.srt);
+    if (e->kind == APMG_ENC_HASH) {
+      int64_t lat = 0;
+      for (int k = 0; k < s.L; ++k)
+        if (hash_level_pull(ea, enc_level_res(ea, k), n))
+          lat = std::max<int64_t>(lat, pull_blocks(enc_level_res(ea, k) + 1, s.C).total());
+      if (lat > 0) w.tcc = cv.take<float>((size_t)(s.M / s.L) * lat * pull_lat(s.C) * s.C);
+    }
     if (e->kind == APMG_ENC_TIME) {
       const size_t nn = (size_t)std::max<int64_t>(n, 1);
       w.tau = cv.take<float>(nn);
@@ -1625,7 +1641,7 @@ apmg_status apmg_variant_backward(const apmg_model* m, const apmg_encoder* e, co
       hipLaunchKernelGGL(k_fill_f32, dim3(1), dim3(256), 0, st, dW[2], (size_t)s.H, 0.f);
     }
     // (the per-cell gather of the 4-D grids overwrites dF)
-    if (dF && (n == 0 || !w.tcc)) hipLaunchKernelGGL(k_fill_f32, dim3(grid1(nF)), dim3(256), 0, st, dF, nF, 0.f);
+    if (dF && (n == 0 || e->kind == APMG_ENC_HASH || !w.tcc)) hipLaunchKernelGGL(k_fill_f32, dim3(grid1(nF)), dim3(256), 0, st, dF, nF, 0.f);
     if (dG) hipLaunchKernelGGL(k_fill_f64, dim3(1), dim3(256), 0, st, dG, (size_t)4 * grows * mt, 0.0);
   }
   if (n == 0) return hip_status(hipGetLastError());
@@ -1685,13 +1701,42 @@ apmg_status apmg_variant_backward(const apmg_model* m, const apmg_encoder* e, co
                        dW[2], (double*)nullptr, (size_t)0, 1, (const int32_t*)nullptr);
   }
   if (!want_enc) return hip_status(hipGetLastError());
-  // grid / table gradient by the scatter (into the caller's dF, or a channel-last buffer that
-  // is then laid out in the paper's order), transform gradient per block in float64
-  float* dst = dF ? (w.dFcl ? w.dFcl : dF) : nullptr;
-  if (w.dFcl && dF) hipLaunchKernelGGL(k_fill_f32, dim3(grid1(nF)), dim3(256), 0, st, w.dFcl, nF, 0.f);
+  EncScatterArgs sa;
+  memset(&sa, 0, sizeof(sa));
+  sa.s = s; sa.enc = ea; sa.G = Gc; sa.F = Fc;
+  sa.pts = bpts; sa.ld = n; sa.n = n;
+  sa.tau = w.tau;
+  sa.dY = w.dY;
+  // hash tables, level by level: the block gather's vertex sums folded into the entries, or the
+  // atomic scatter
+  if (dF && e->kind == APMG_ENC_HASH) {
+    const size_t T = (size_t)ea.tmask + 1u;
+    for (int k = 0; k < s.L; ++k) {
+      const int N = enc_level_res(ea, k);
+      if (!hash_level_pull(ea, N, n)) {
+        sa.dF = dF; sa.g0 = k; sa.gs = s.L;
+        if (launch_enc_scatter(sa, e->kind, mt, st) != hipSuccess) return APMG_EHIP;
+        continue;
+      }
+      CellArgs c;
+      memset(&c, 0, sizeof(c));
+      c.s = hash_level_shape(s, ea, k); c.G = Gc;
+      c.pts4 = w.srt.spts4; c.n = n; c.start = w.srt.start; c.CC = w.tcc;
+      c.dY = w.dY + (size_t)k * n * s.C; c.dY_grid = (size_t)s.L * n * s.C;
+      c.cell = 2.0 / N;
+      const int64_t wgroups = (int64_t)pull_groups(c.s, n) * mt;
+      if (wgroups > 0x7fffffff) return APMG_EUNSUPPORTED;
+      if (pull_split(c.s, n))
+        hipLaunchKernelGGL((k_block_pull<2, false, false, 1, true>), dim3((unsigned)wgroups), dim3(256), 0, st, c);
+      else
+        hipLaunchKernelGGL((k_block_pull<2, false, false, 1, false>), dim3((unsigned)wgroups), dim3(256), 0, st, c);
+      if (launch_lattice_to_entries(ea, N, mt, w.tcc, dF + (size_t)k * T * s.C, (size_t)s.L * T * s.C, st) != hipSuccess)
+        return APMG_EHIP;
+    }
+  }
   // 4-D grids in (time cell, bin) order: the grid gradient by the per-cell gather (one pass per
   // time cell, no atomics, a fixed order), then the vertex sums over both time neighbours
-  const bool pull = dF && w.tcc;
+  const bool pull = dF && w.tcc && e->kind == APMG_ENC_TIME;
   if (pull) {
     CellArgs c;
     memset(&c, 0, sizeof(c));
@@ -1708,21 +1753,20 @@ apmg_status apmg_variant_backward(const apmg_model* m, const apmg_encoder* e, co
     hipLaunchKernelGGL(k_block_to_vertex_time<2>, dim3(grid1((int64_t)s.R * s.R * s.R, 1024), s.M, ea.Rt), dim3(256),
                        0, st, s, ea.Rt, w.tcc, dF, paper_grids(m) ? 1 : 0, acc ? 1 : 0);
   }
-  if (!dG && pull) return hip_status(hipGetLastError());
-  EncScatterArgs sa;
-  memset(&sa, 0, sizeof(sa));
-  sa.s = s; sa.enc = ea; sa.G = Gc; sa.F = Fc;
-  sa.pts = bpts; sa.ld = n; sa.n = n;
-  sa.tau = w.tau;
-  sa.dY = w.dY;
-  sa.dF = pull ? nullptr : dst;   // with the gather done, the scatter forms the transform gradient only
-  sa.dGpart = dG ? w.dGpart : nullptr;
-  sa.nbx = variant_nbx(n);
-  if (launch_enc_scatter(sa, e->kind, st) != hipSuccess) return APMG_EHIP;
-  if (w.dFcl && dF) {
-    const int64_t V = (int64_t)ea.Rt * s.R * s.R * s.R;
-    hipLaunchKernelGGL(k_cl_to_paper<2>, dim3(grid1(s.M * V, 8192)), dim3(256), 0, st, (int64_t)s.M, V, w.dFcl, dF,
-                       acc ? 1 : 0);
+  if (dF && !pull && e->kind == APMG_ENC_TIME) {
+    // by the scatter, into the caller's dF or a channel-last buffer then laid out in the paper's order
+    sa.dF = w.dFcl ? w.dFcl : dF; sa.g0 = 0; sa.gs = 1;
+    if (w.dFcl) hipLaunchKernelGGL(k_fill_f32, dim3(grid1(nF)), dim3(256), 0, st, w.dFcl, nF, 0.f);
+    if (launch_enc_scatter(sa, e->kind, s.M, st) != hipSuccess) return APMG_EHIP;
+    if (w.dFcl) {
+      const int64_t V = (int64_t)ea.Rt * s.R * s.R * s.R;
+      hipLaunchKernelGGL(k_cl_to_paper<2>, dim3(grid1(s.M * V, 8192)), dim3(256), 0, st, (int64_t)s.M, V, w.dFcl, dF,
+                         acc ? 1 : 0);
+    }
+  }
+  if (dG) {
+    sa.dGpart = w.dGpart; sa.nbx = variant_nbx(n);
+    if (launch_enc_transform_grad(sa, e->kind, st) != hipSuccess) return APMG_EHIP;
   }
   if (dG)
     hipLaunchKernelGGL(k_reduce_cell_dG, dim3(mt, 1), dim3(256), 0, st, w.dGpart, mt, s.L * sa.nbx, dG,

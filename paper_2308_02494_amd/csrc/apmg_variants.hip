@@ -3,14 +3,19 @@
 //
 // The forward and the MLP adjoint are the tile kernels (k_forward, k_adjoint) instantiated
 // with the variant's lookup (enc_tap); k_adjoint stores dL/dy per (feature grid, point) of the
-// spatially sorted points.  The scatter below then adds w_q dL/dy_c into the corner entries
-// with float atomics: a hash table entry collects the contributions of every vertex that maps
-// to it, so the per-cell gather of the dense grids does not apply, and the 4-D grids share the
-// scatter.  Neighbouring sorted points mostly share a cell, so each wave first sums the runs
-// of lanes with the same cell and only the run's first lane issues the atomics.  The sums of
-// float atomics are not in a fixed order (results reproducible to rounding).  The transform
+// spatially sorted points.
+//
+// Table gradient of a hash level: a level of N cells per axis is a dense grid of (N + 1)^3
+// vertices until its vertices are mapped to entries, so its vertex sums come from the block
+// gather of the dense grids (k_block_pull), and the vertices of an entry are then added
+// (k_lattice_to_table, k_lattice_to_hash): no atomics, a fixed order.  Levels with many more
+// vertices than the batch has points (or a table smaller than a row of vertices) take the
+// scatter instead (k_enc_scatter): w_q dL/dy_c added to the corner entries with float atomics,
+// where each wave first sums the runs of lanes with the same cell and only the run's first
+// lane issues the atomics; those sums are reproducible to rounding only.  The 4-D grids take
+// the block gather per time cell, or the scatter beyond 513 time vertices.  The transform
 // gradient through the interpolation weights is reduced per block in float64, in a fixed
-// order.
+// order (k_enc_transform_grad).
 
 namespace apmg {
 
@@ -22,8 +27,9 @@ struct EncScatterArgs {
   const float* pts; int64_t ld; int64_t n;
   const float* tau;        // time: [n] time of each point
   const float* dY;         // [M][n][C], dL/dy per feature grid (M feature grids)
-  float* dF;               // same layout as F (channel-last for time), accumulated; NULL: no grid gradient
-  double* dGpart;          // [M][nbx][12], or NULL for no transform gradient
+  float* dF;               // scatter: same layout as F (channel-last for time), accumulated
+  int g0, gs;              // scatter: feature grid of block row y is g0 + gs y
+  double* dGpart;          // transform gradient: [M][nbx][12]
   int nbx;                 // point blocks per feature grid
 };
 
@@ -85,17 +91,12 @@ __device__ inline float run_sum(float v, const WaveRuns& r) {
   return v;
 }
 
-// One thread per (point, feature grid): blockIdx.y = feature grid g, 256 points per block.
+// One thread per (point, feature grid): 256 points per block.
 template <int C, int ENC>
 __global__ void __launch_bounds__(256) k_enc_scatter(EncScatterArgs a) {
-  __shared__ float sG[12 * 256];
-  __shared__ double sred[4][12];
   const Shape s = a.s;
-  const int g = blockIdx.y, bx = blockIdx.x;
-  const int mt = s.M / s.L;
-  for (int i = threadIdx.x; i < 12 * mt; i += blockDim.x) sG[i] = a.G[i];
-  __syncthreads();
-  const int64_t p = (int64_t)bx * blockDim.x + threadIdx.x;
+  const int g = a.g0 + a.gs * blockIdx.y;
+  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const bool valid = p < a.n;
   float x = 0.f, y = 0.f, z = 0.f, tq = 0.f;
   if (valid) { x = a.pts[p]; y = a.pts[a.ld + p]; z = a.pts[2 * a.ld + p]; }
@@ -103,103 +104,196 @@ __global__ void __launch_bounds__(256) k_enc_scatter(EncScatterArgs a) {
   float dy[C];
 #pragma unroll
   for (int c = 0; c < C; ++c) dy[c] = valid ? a.dY[((size_t)g * a.n + p) * C + c] : 0.f;
-  GridTap<C, ENC> t;
-  const float hR = 0.5f * (float)(s.R - 1);
-  enc_tap<C, false, ENC>(s, sG, a.F, a.enc, g, x, y, z, tq, valid, hR, t);
-  float dl[3] = {0.f, 0.f, 0.f};
+  // the cell of this lane's point (the same float32 decision as the lookup)
+  const int gt = g / s.L, N = ENC == kEncHash ? enc_level_res(a.enc, g - gt * s.L) : s.R - 1;
+  float l[3], w[3];
+  int i0[3];
+  local_coords(a.G + 12 * gt, x, y, z, l);
+  bool in = cell_of(l, 0.5f * (float)N, N + 1, i0, w) && valid;
   const int lane = threadIdx.x & 63;
   if constexpr (ENC == kEncHash) {
-    if (a.dF) {
-      // the cell of this lane's point (the same float32 decision as the lookup)
-      const int gt = g / s.L, k = g - gt * s.L;
-      const int N = enc_level_res(a.enc, k);
-      float l[3];
-      local_coords(sG + 12 * gt, x, y, z, l);
-      int i0[3];
-      float w[3];
-      cell_of(l, 0.5f * (float)N, N + 1, i0, w);
-      (void)w;
-      const uint64_t key = t.in ? ((uint64_t)i0[2] << 40 | (uint64_t)i0[1] << 20 | (uint64_t)i0[0]) : ~0ull - lane;
-      const WaveRuns rn = wave_runs(key, lane);
-      const uint32_t n1 = (uint32_t)N + 1u;
-      const bool dense = (uint64_t)n1 * n1 * n1 <= (uint64_t)a.enc.tmask + 1u;
-      float* base = a.dF + (size_t)g * ((size_t)a.enc.tmask + 1u) * C;
+    const uint64_t key = in ? ((uint64_t)i0[2] << 40 | (uint64_t)i0[1] << 20 | (uint64_t)i0[0]) : ~0ull - lane;
+    const WaveRuns rn = wave_runs(key, lane);
+    const uint32_t n1 = (uint32_t)N + 1u;
+    const bool dense = (uint64_t)n1 * n1 * n1 <= (uint64_t)a.enc.tmask + 1u;
+    float* base = a.dF + (size_t)g * ((size_t)a.enc.tmask + 1u) * C;
 #pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        const float wq = t.in ? tri_weight(q, t.w) : 0.f;
-        float v[C];
+    for (int q = 0; q < 8; ++q) {
+      const float wq = in ? tri_weight(q, w) : 0.f;
+      float v[C];
 #pragma unroll
-        for (int c = 0; c < C; ++c) v[c] = run_sum(wq * dy[c], rn);
-        if (t.in && rn.head) {
-          const uint32_t ent = hash_entry((uint32_t)i0[0] + (q & 1), (uint32_t)i0[1] + ((q >> 1) & 1),
-                                          (uint32_t)i0[2] + (q >> 2), n1, dense, a.enc.tmask);
+      for (int c = 0; c < C; ++c) v[c] = run_sum(wq * dy[c], rn);
+      if (in && rn.head) {
+        const uint32_t ent = hash_entry((uint32_t)i0[0] + (q & 1), (uint32_t)i0[1] + ((q >> 1) & 1),
+                                        (uint32_t)i0[2] + (q >> 2), n1, dense, a.enc.tmask);
 #pragma unroll
-          for (int c = 0; c < C; ++c) unsafeAtomicAdd(base + (size_t)ent * C + c, v[c]);
-        }
+        for (int c = 0; c < C; ++c) unsafeAtomicAdd(base + (size_t)ent * C + c, v[c]);
       }
     }
   } else {
-    if (a.dF) {
-      float l[3];
-      local_coords(sG + 12 * g, x, y, z, l);
-      int i0[3];
-      float w[3];
-      cell_of(l, hR, s.R, i0, w);
-      (void)w;
-      const float ht = 0.5f * (float)(a.enc.Rt - 1);
-      const float ut = __builtin_fmaf(tq, ht, ht);
-      const int t0 = (int)fminf(fmaxf(floorf(ut), 0.0f), (float)(a.enc.Rt - 2));
-      const uint32_t R = (uint32_t)s.R, RC = R * C, RRC = R * R * C;
-      const uint64_t key = t.in ? ((((uint64_t)t0 * R + i0[2]) * R + i0[1]) * R + i0[0]) : ~0ull - lane;
-      const WaveRuns rn = wave_runs(key, lane);
-      const uint32_t cb = t.in ? ((uint32_t)i0[2] * R + i0[1]) * RC + (uint32_t)i0[0] * C : 0u;
+    const float ht = 0.5f * (float)(a.enc.Rt - 1);
+    const float ut = __builtin_fmaf(tq, ht, ht);
+    const float ft = fminf(fmaxf(floorf(ut), 0.0f), (float)(a.enc.Rt - 2));
+    const int t0 = (int)ft;
+    const float wt = ut - ft;
+    in = in && tq >= -1.0f && tq <= 1.0f;
+    const uint32_t R = (uint32_t)s.R, RC = R * C, RRC = R * R * C;
+    const uint64_t key = in ? ((((uint64_t)t0 * R + i0[2]) * R + i0[1]) * R + i0[0]) : ~0ull - lane;
+    const WaveRuns rn = wave_runs(key, lane);
+    const uint32_t cb = in ? ((uint32_t)i0[2] * R + i0[1]) * RC + (uint32_t)i0[0] * C : 0u;
 #pragma unroll
-      for (int sl = 0; sl < 2; ++sl) {
-        const float ws = sl ? t.wt : 1.f - t.wt;
-        float* base = a.dF + (((size_t)g * a.enc.Rt + (t.in ? t0 : 0) + sl) * R * R * R) * C;
+    for (int sl = 0; sl < 2; ++sl) {
+      const float ws = sl ? wt : 1.f - wt;
+      float* base = a.dF + (((size_t)g * a.enc.Rt + (in ? t0 : 0) + sl) * R * R * R) * C;
 #pragma unroll
-        for (int q = 0; q < 8; ++q) {
-          const float wq = t.in ? ws * tri_weight(q, t.w) : 0.f;
-          const uint32_t o = cb + (q & 1) * C + ((q >> 1) & 1) * RC + (q >> 2) * RRC;
+      for (int q = 0; q < 8; ++q) {
+        const float wq = in ? ws * tri_weight(q, w) : 0.f;
+        const uint32_t o = cb + (q & 1) * C + ((q >> 1) & 1) * RC + (q >> 2) * RRC;
 #pragma unroll
-          for (int c = 0; c < C; ++c) {
-            const float v = run_sum(wq * dy[c], rn);
-            if (t.in && rn.head) unsafeAtomicAdd(base + o + c, v);
-          }
+        for (int c = 0; c < C; ++c) {
+          const float v = run_sum(wq * dy[c], rn);
+          if (in && rn.head) unsafeAtomicAdd(base + o + c, v);
         }
       }
     }
   }
-  if (t.in) {
-    if constexpr (ENC == kEncHash) {
-      const int N = enc_level_res(a.enc, g - (g / s.L) * s.L);
-      trilerp_dw<C>(t.val, t.w, dy, dl);
-      const float sc = 0.5f * (float)N;
+}
+
+// Table gradient of one level whose vertices have an entry each: entry v of adaptive grid gt
+// += the lattice sums of vertex v (tables at gt * table_stride floats).
+template <int C>
+__global__ void k_lattice_to_table(int N, const float* BL, float* dF, size_t table_stride) {
+  const int gt = blockIdx.y;
+  const uint32_t n1 = N + 1, nv = n1 * n1 * n1;
+  const PullBlocks nb = pull_blocks((int)n1, C);
+  const float* bl = BL + gt * nb.total() * pull_lat(C) * C;
+  for (uint32_t v = blockIdx.x * blockDim.x + threadIdx.x; v < nv; v += gridDim.x * blockDim.x) {
+    const uint32_t yz = v / n1, z = yz / n1;
+    float sum[C];
+    lattice_sum<C, C>(bl, nb, 0, (int)(v - yz * n1), (int)(yz - z * n1), (int)z, sum);
+    float* dst = dF + gt * table_stride + (size_t)v * C;
 #pragma unroll
-      for (int d = 0; d < 3; ++d) dl[d] *= sc;
+    for (int c = 0; c < C; ++c) dst[c] += sum[c];
+  }
+}
+
+// Table gradient of a hashed level: entry e += the lattice sums of every vertex that hashes to
+// e.  The hash is x XOR h(y, z) in its low bits, so a row of vertices (y, z) with N + 1 <= B = 64
+// NB vertices falls into one aligned run of B entries, entry e of the run holding vertex x =
+// (e XOR h) mod B.  A workgroup owns one run: each of its four waves scans its share of the
+// rows 64 at a time (h of a row per lane, one ballot finds the rows of this run) and adds the
+// matching rows in order, lane i holding the entries i, i + 64, ... of the run; the four waves'
+// sums are then added in order.  No atomics, and every vertex is read once.
+template <int C, int NB>
+__global__ void __launch_bounds__(256) k_lattice_to_hash(int N, uint32_t tmask, const float* BL, float* dF,
+                                                         size_t table_stride) {
+  constexpr int VX = pull_vx(C), NX = VX - 1;
+  constexpr uint32_t B = 64 * NB;
+  typedef float vec __attribute__((ext_vector_type(C), aligned(4 * C)));
+  __shared__ float sSum[4][B * C];
+  const int gt = blockIdx.y, lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t n1 = N + 1, rows = n1 * n1, run = blockIdx.x * B;
+  const PullBlocks nb = pull_blocks((int)n1, C);
+  const float* bl = BL + gt * nb.total() * pull_lat(C) * C;
+  float acc[NB][C];
+#pragma unroll
+  for (int i = 0; i < NB; ++i)
+#pragma unroll
+    for (int c = 0; c < C; ++c) acc[i][c] = 0.f;
+  for (uint32_t r0 = 64u * wave; r0 < rows; r0 += 256) {
+    const uint32_t r = r0 + lane, z = r / n1, y = r - z * n1;
+    const uint32_t h = (y * 2654435761u) ^ (z * 805459861u);
+    uint64_t m = __ballot(r < rows && ((h & tmask) & ~(B - 1u)) == run);
+    while (m) {
+      const int k = __builtin_ctzll(m);
+      m &= m - 1;
+      const uint32_t hk = __builtin_amdgcn_readlane((int)h, k);
+      const int zk = __builtin_amdgcn_readlane((int)z, k), yk = __builtin_amdgcn_readlane((int)y, k);
+      // the one or two blocks along y and z that hold the row (the lower one first)
+      const int qy = yk / kPullNY, qz = zk / kPullNZ;
+      const int by1 = min(qy, nb.y - 1), by0 = (qy * kPullNY == yk && qy > 0) ? qy - 1 : by1;
+      const int bz1 = min(qz, nb.z - 1), bz0 = (qz * kPullNZ == zk && qz > 0) ? qz - 1 : bz1;
+#pragma unroll
+      for (int i = 0; i < NB; ++i) {
+        const uint32_t x = ((uint32_t)(lane + 64 * i) ^ hk) & (B - 1u);
+        if (x > (uint32_t)N) continue;
+        const int qx = (int)x / NX;
+        const int bx1 = min(qx, nb.x - 1), bx0 = (qx * NX == (int)x && qx > 0) ? qx - 1 : bx1;
+        for (int bz = bz0; bz <= bz1; ++bz)
+          for (int by = by0; by <= by1; ++by)
+            for (int bx = bx0; bx <= bx1; ++bx) {
+              const vec v = *(const vec*)(bl + ((((size_t)(bz * nb.y + by) * nb.x + bx) * 16 + (zk - kPullNZ * bz) * 4 +
+                                                (yk - kPullNY * by)) * VX + ((int)x - NX * bx)) * C);
+#pragma unroll
+              for (int c = 0; c < C; ++c) acc[i][c] += v[c];
+            }
+      }
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < NB; ++i)
+#pragma unroll
+    for (int c = 0; c < C; ++c) sSum[wave][(lane + 64 * i) * C + c] = acc[i][c];
+  __syncthreads();
+  float* dst = dF + gt * table_stride + (size_t)run * C;
+  for (uint32_t i = threadIdx.x; i < B * C; i += 256)
+    dst[i] += ((sSum[0][i] + sSum[1][i]) + sSum[2][i]) + sSum[3][i];
+}
+
+// The transform gradient through the interpolation weights: per feature grid, sums over the
+// points of (dl_d) x^T and dl_d, in float64.  kTgPoints points per thread, so the wave
+// reduction of the 12 sums (a butterfly of float64 shuffles, several times the work of a
+// point) is paid once per block and not once per point.
+constexpr int kTgPoints = 16;
+template <int C, int ENC>
+__global__ void __launch_bounds__(256) k_enc_transform_grad(EncScatterArgs a) {
+  __shared__ double sred[4][12];
+  const Shape s = a.s;
+  const int g = blockIdx.y, bx = blockIdx.x, gt = g / s.L;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const float hR = 0.5f * (float)(s.R - 1);
+  const float sc = ENC == kEncHash ? 0.5f * (float)enc_level_res(a.enc, g - gt * s.L) : hR;
+  double acc[12];
+#pragma unroll
+  for (int k = 0; k < 12; ++k) acc[k] = 0.0;
+  const int64_t p0 = (int64_t)bx * (256 * kTgPoints);
+  for (int64_t p = p0 + threadIdx.x; p < min(a.n, p0 + 256 * kTgPoints); p += 256) {
+    const float x = a.pts[p], y = a.pts[a.ld + p], z = a.pts[2 * a.ld + p];
+    const float tq = ENC == kEncTime ? a.tau[p] : 0.f;
+    float dy[C];
+#pragma unroll
+    for (int c = 0; c < C; ++c) dy[c] = a.dY[((size_t)g * a.n + p) * C + c];
+    GridTap<C, ENC> t;
+    enc_tap<C, false, ENC>(s, a.G, a.F, a.enc, g, x, y, z, tq, true, hR, t);
+    if (!t.in) continue;
+    float dl[3];
+    if constexpr (ENC == kEncHash) {
+      trilerp_dw<C>(t.val, t.w, dy, dl);
     } else {
       float d0[3], d1[3];
       trilerp_dw<C>(t.va, t.w, dy, d0);
       trilerp_dw<C>(t.vb, t.w, dy, d1);
 #pragma unroll
-      for (int d = 0; d < 3; ++d) dl[d] = ((1.f - t.wt) * d0[d] + t.wt * d1[d]) * hR;
+      for (int d = 0; d < 3; ++d) dl[d] = (1.f - t.wt) * d0[d] + t.wt * d1[d];
+    }
+#pragma unroll
+    for (int r = 0; r < 3; ++r) {
+      const double d = (double)(dl[r] * sc);
+      acc[4 * r] += d * (double)x;
+      acc[4 * r + 1] += d * (double)y;
+      acc[4 * r + 2] += d * (double)z;
+      acc[4 * r + 3] += d;
     }
   }
-  if (a.dGpart) {
-    const float xs[4] = {t.in ? x : 0.f, t.in ? y : 0.f, t.in ? z : 0.f, t.in ? 1.f : 0.f};
-    const int wave = threadIdx.x >> 6;
 #pragma unroll
-    for (int r = 0; r < 3; ++r)
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const double v = wave_sum((double)dl[r] * (double)xs[k]);
-        if (lane == 0) sred[wave][4 * r + k] = v;
-      }
-    __syncthreads();
-    if (threadIdx.x < 12) {
-      const double v = sred[0][threadIdx.x] + sred[1][threadIdx.x] + sred[2][threadIdx.x] + sred[3][threadIdx.x];
-      a.dGpart[((size_t)g * a.nbx + bx) * 12 + threadIdx.x] = v;
-    }
+  for (int k = 0; k < 12; ++k) {
+    const double v = wave_sum(acc[k]);
+    if (lane == 0) sred[wave][k] = v;
+  }
+  __syncthreads();
+  if (threadIdx.x < 12) {
+    const double v = sred[0][threadIdx.x] + sred[1][threadIdx.x] + sred[2][threadIdx.x] + sred[3][threadIdx.x];
+    a.dGpart[((size_t)g * a.nbx + bx) * 12 + threadIdx.x] = v;
   }
 }
 
@@ -270,11 +364,58 @@ __global__ void k_cl_to_paper(int64_t nm, int64_t V, const float* __restrict__ s
   }
 }
 
-hipError_t launch_enc_scatter(const EncScatterArgs& a, int enc, hipStream_t st) {
-  const dim3 grid((unsigned)a.nbx, (unsigned)a.s.M);
+// rows: feature grids g0, g0 + gs, ...
+hipError_t launch_enc_scatter(const EncScatterArgs& a, int enc, int rows, hipStream_t st) {
+  const dim3 grid((unsigned)((a.n + 255) / 256), (unsigned)rows);
   if (a.s.C != 2) return hipErrorInvalidValue;
   if (enc == kEncHash) hipLaunchKernelGGL((k_enc_scatter<2, kEncHash>), grid, dim3(256), 0, st, a);
   else if (enc == kEncTime) hipLaunchKernelGGL((k_enc_scatter<2, kEncTime>), grid, dim3(256), 0, st, a);
+  else return hipErrorInvalidValue;
+  return hipGetLastError();
+}
+hipError_t launch_enc_transform_grad(const EncScatterArgs& a, int enc, hipStream_t st) {
+  const dim3 grid((unsigned)a.nbx, (unsigned)a.s.M);
+  if (a.s.C != 2) return hipErrorInvalidValue;
+  if (enc == kEncHash) hipLaunchKernelGGL((k_enc_transform_grad<2, kEncHash>), grid, dim3(256), 0, st, a);
+  else if (enc == kEncTime) hipLaunchKernelGGL((k_enc_transform_grad<2, kEncTime>), grid, dim3(256), 0, st, a);
+  else return hipErrorInvalidValue;
+  return hipGetLastError();
+}
+
+// A hash level takes the block gather (k_block_pull + k_lattice_to_table / k_lattice_to_hash)
+// while its vertices are at most four per point: the lattices then stay within 64 bytes per
+// point and grid, and a block of 63 cells has points enough to pay for finding its candidates.
+// A hashed level's rows also have to fit one aligned run of entries of the table, and a
+// workgroup's registers (at most 1024 entries a run).  Measured at 2^20 points, 8 grids: the
+// gather and fold of N = 16 / 32 / 64 / 128 take 0.13 / 0.10 / 0.17 / 0.54 ms, the atomics 2.5 ms per level.
+inline int hash_run_log2(int N) {   // log2 of B, the power of two >= N + 1 and >= 64
+  int b = 6;
+  while ((1 << b) < N + 1) ++b;
+  return b;
+}
+inline bool hash_level_dense(const EncArgs& e, int N) {
+  return (uint64_t)(N + 1) * (N + 1) * (N + 1) <= (uint64_t)e.tmask + 1u;
+}
+inline bool hash_level_pull(const EncArgs& e, int N, int64_t n) {
+  if ((double)(N + 1) * (N + 1) * (N + 1) > 4.0 * (double)n) return false;
+  const int b = hash_run_log2(N);
+  return hash_level_dense(e, N) || (b <= 10 && (1u << b) <= e.tmask + 1u);
+}
+hipError_t launch_lattice_to_entries(const EncArgs& e, int N, int mt, const float* lat, float* dF, size_t table_stride,
+                                     hipStream_t st) {
+  if (hash_level_dense(e, N)) {
+    const int64_t nv = (int64_t)(N + 1) * (N + 1) * (N + 1);
+    hipLaunchKernelGGL(k_lattice_to_table<2>, dim3((unsigned)std::min<int64_t>((nv + 255) / 256, 1024), mt), dim3(256), 0,
+                       st, N, lat, dF, table_stride);
+    return hipGetLastError();
+  }
+  const int b = hash_run_log2(N);
+  const dim3 grid((e.tmask + 1u) >> b, mt);
+  if (b == 6) hipLaunchKernelGGL((k_lattice_to_hash<2, 1>), grid, dim3(256), 0, st, N, e.tmask, lat, dF, table_stride);
+  else if (b == 7) hipLaunchKernelGGL((k_lattice_to_hash<2, 2>), grid, dim3(256), 0, st, N, e.tmask, lat, dF, table_stride);
+  else if (b == 8) hipLaunchKernelGGL((k_lattice_to_hash<2, 4>), grid, dim3(256), 0, st, N, e.tmask, lat, dF, table_stride);
+  else if (b == 9) hipLaunchKernelGGL((k_lattice_to_hash<2, 8>), grid, dim3(256), 0, st, N, e.tmask, lat, dF, table_stride);
+  else if (b == 10) hipLaunchKernelGGL((k_lattice_to_hash<2, 16>), grid, dim3(256), 0, st, N, e.tmask, lat, dF, table_stride);
   else return hipErrorInvalidValue;
   return hipGetLastError();
 }

@@ -14,6 +14,7 @@ from oracle import apmg_variants as V
 from test_gpu_parity import A, DEV, assert_close, f64, host_model, kink_free, make_points, soa
 from test_gpu_variants import f64 as vf64
 from test_gpu_variants import kink_free as v_kink_free
+from test_gpu_variants import hash_host, hash_model
 from test_gpu_variants import points as v_points
 from test_gpu_variants import time_host, time_model
 
@@ -79,3 +80,31 @@ def test_time_block_gather_edges(R, n, Rt):
         dFn = dF.cpu().numpy()
         assert_close(f"dF4 (channel-last {cl})", dFn.transpose(0, 5, 1, 2, 3, 4) if cl else dFn, go["dF4"])
         assert_close("dG", dG.cpu().numpy(), go["dG"])
+
+
+# levels of one entry per vertex, hashed levels whose rows of N + 1 vertices fill runs of 64, 128 and
+# 256 entries (exactly, and one past), and levels left to the atomics: more than four vertices a
+# point, or a table smaller than a run
+@pytest.mark.parametrize("res,T,M,n,fixed_order", [
+    ((1, 7, 20, 31), 1 << 12, 3, 40000, True),
+    ((63, 64), 1 << 12, 2, 80000, True),
+    ((127, 128), 1 << 14, 1, 545000, True),
+    ((3, 100), 1 << 6, 4, 3000, False),
+    ((15, 40), 1 << 6, 2, 20000, False),
+])
+def test_hash_table_gradient_levels(res, T, M, n, fixed_order):
+    h = hash_host(M=M, L=len(res), T=T, res=res, seed=n)
+    x = v_points(n, seed=n + 1)
+    _, cache = V.hash_forward(vf64(h), x.astype(np.float64))
+    # points at a ReLU kink stay in the batch (its size picks the path) with dL/df = 0
+    df = np.where(v_kink_free(cache), np.random.default_rng(8).normal(size=n), 0.0).astype(np.float32)
+    dfd, xd = torch.from_numpy(df).to(DEV), soa(x)
+    model = hash_model(h)
+    dF, dG, _ = A().apmg_variant_backward(model, xd, dfd)
+    again, _, _ = A().apmg_variant_backward(model, xd, dfd, want_dG=False, want_dW=False)
+    if fixed_order:
+        assert torch.equal(dF, again)
+    go = V.hash_backward(vf64(h), x.astype(np.float64), df.astype(np.float64))
+    for k in range(len(res)):
+        assert_close(f"dTheta level {k}", dF[:, k].cpu().numpy(), go["dTheta"][:, k])
+    assert_close("dG", dG.cpu().numpy(), go["dG"])

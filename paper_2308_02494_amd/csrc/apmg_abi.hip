@@ -67,8 +67,25 @@ apmg_status check_points(const float* pts, int64_t ld, int64_t n) {
 
 apmg_status hip_status(hipError_t e) { return e == hipSuccess ? APMG_OK : APMG_EHIP; }
 
+// dW1 [H][cols1], dW2 [rows2][H] and dW3 [H] (with3) from contiguous per-block partials; one model
+void reduce_dw(const Shape& s, int cols1, int rows2, bool with3, const double* part, int nblk, int len, float* d1,
+               float* d2, float* d3, int accumulate, hipStream_t st);
+void clear_dw(const Shape& s, float* const* dW, hipStream_t st) {
+  if (!dW) return;
+  hipLaunchKernelGGL(k_fill_f32, dim3(32), dim3(256), 0, st, dW[0], (size_t)s.H * s.MC, 0.f);
+  hipLaunchKernelGGL(k_fill_f32, dim3(32), dim3(256), 0, st, dW[1], (size_t)s.H * s.H, 0.f);
+  hipLaunchKernelGGL(k_fill_f32, dim3(1), dim3(256), 0, st, dW[2], (size_t)s.H, 0.f);
+}
+
 inline unsigned red_blocks(int64_t count) {
   return (unsigned)std::max<int64_t>(1, std::min<int64_t>((count + 31) / 32, 2048));
+}
+
+void reduce_dw(const Shape& s, int cols1, int rows2, bool with3, const double* part, int nblk, int len, float* d1,
+               float* d2, float* d3, int accumulate, hipStream_t st) {
+  const int n1 = s.H * cols1, n2 = s.H * rows2, n3 = with3 ? s.H : 0;
+  hipLaunchKernelGGL(k_reduce_dw, dim3(red_blocks(n1 + n2 + n3), 1), dim3(256), 0, st, part, nblk, len, n1, n2, n3, d1,
+                     d2, d3, (size_t)0, accumulate, (const int32_t*)nullptr);
 }
 
 inline unsigned grid1(int64_t n, int64_t cap = 4096) {
@@ -453,20 +470,18 @@ size_t bwd_ws(const Shape& s, const apmg_model* m, int64_t n, void* ws, BwdWs* o
 }
 
 int dens_blocks(int64_t n) { return (int)std::max<int64_t>(1, std::min<int64_t>((n + 255) / 256, kDensBlocks)); }
-int dens_chunks(int64_t n) { return (int)std::max<int64_t>(1, (n + kDensChunk - 1) / kDensChunk); }
+int dens_chunks(int64_t n) { return (int)std::max<int64_t>(1, (n + dens_chunk(n) - 1) / dens_chunk(n)); }
 
-struct DenWs { float *rho, *coef; double *pa, *sums, *pb1, *lq, *pb2, *U, *a; };
+struct DenWs { float* rho; double *pa, *sums, *pb1, *lq, *pb2, *a; };
 size_t den_ws(const Shape& s, int64_t n, int nb, void* ws, DenWs* o) {
   Carver cv(ws);
   DenWs d;
   d.rho = cv.take<float>((size_t)nb * std::max<int64_t>(n, 1));
-  d.coef = cv.take<float>((size_t)nb * std::max<int64_t>(n, 1));
   d.pa = cv.take<double>((size_t)nb * kDensBlocks * 2);
   d.sums = cv.take<double>((size_t)nb * 2);
   d.pb1 = cv.take<double>((size_t)nb * kDensBlocks * 3);
   d.lq = cv.take<double>((size_t)nb * 3);
   d.pb2 = cv.take<double>((size_t)nb * dens_chunks(n) * 13 * s.M);
-  d.U = cv.take<double>((size_t)nb * 13 * s.M);
   d.a = cv.take<double>((size_t)nb * std::max<int64_t>(n, 1));
   if (o) *o = d;
   return cv.off;
@@ -506,7 +521,7 @@ void launch_density_a_gen(const Shape& s, const float* G, size_t G_stride, uint6
 }
 
 // rho_perm (the training step): pass A already ran over the drawn batch (launch_density_a_gen,
-// rho in draw order); only its error sums are formed here and B1 reads rho through rho_perm.
+// rho in draw order) and k_step_sums formed the sums; B1 reads rho through rho_perm.
 hipError_t launch_density(const Shape& s, const float* G, size_t G_stride, const float* pts, int64_t ld,
                           size_t pts_stride, int64_t n, const float* err, size_t err_stride, double eps,
                           int p, uint32_t flags, double* loss, int lstride, double* dG, size_t dG_stride, int dG_rows,
@@ -517,35 +532,30 @@ hipError_t launch_density(const Shape& s, const float* G, size_t G_stride, const
   const size_t rho_stride = rho_user ? (size_t)n : (size_t)std::max<int64_t>(n, 1);
   const int ba = dens_blocks(n), nch = dens_chunks(n);
   const size_t shA = 64 + (size_t)13 * s.M * 4;
-  if (rho_perm)
-    hipLaunchKernelGGL(k_density_errsum, dim3(ba, nb), dim3(256), 0, st, err, err_stride, n, w.pa, active);
-  else if (p == 10)
-    hipLaunchKernelGGL(k_density_a<10>, dim3(ba, nb), dim3(256), shA, st, s, G, G_stride, pts, ld, pts_stride, n,
-                       err, err_stride, p, abs_det, rho, rho_stride, w.pa, active, 0, nullptr, 0);
-  else
-    hipLaunchKernelGGL(k_density_a<0>, dim3(ba, nb), dim3(256), shA, st, s, G, G_stride, pts, ld, pts_stride, n,
-                       err, err_stride, p, abs_det, rho, rho_stride, w.pa, active, 0, nullptr, 0);
-  hipLaunchKernelGGL(k_density_sums, dim3(nb), dim3(256), 0, st, w.pa, ba, w.sums, nb);
+  if (!rho_perm) {
+    if (p == 10)
+      hipLaunchKernelGGL(k_density_a<10>, dim3(ba, nb), dim3(256), shA, st, s, G, G_stride, pts, ld, pts_stride, n,
+                         err, err_stride, p, abs_det, rho, rho_stride, w.pa, active, 0, nullptr, 0);
+    else
+      hipLaunchKernelGGL(k_density_a<0>, dim3(ba, nb), dim3(256), shA, st, s, G, G_stride, pts, ld, pts_stride, n,
+                         err, err_stride, p, abs_det, rho, rho_stride, w.pa, active, 0, nullptr, 0);
+    hipLaunchKernelGGL(k_density_sums, dim3(nb), dim3(256), 0, st, w.pa, ba, w.sums, nb);
+  }
   const size_t astride = (size_t)std::max<int64_t>(n, 1);
   hipLaunchKernelGGL(k_density_b1, dim3(ba, nb), dim3(256), 0, st, rho, rho_stride, err, err_stride, n,
                      w.sums, eps, w.pb1, w.a, astride, active, rho_perm);
-  hipLaunchKernelGGL(k_density_lq, dim3(nb), dim3(256), 0, st, w.pb1, ba, n, w.lq, nb, norm);
+  hipLaunchKernelGGL(k_density_lq, dim3(nb), dim3(256), 0, st, w.pb1, ba, n, w.lq, norm, loss, lstride);
   if (dG) {
-    const size_t cstride = (size_t)std::max<int64_t>(n, 1);
-    hipLaunchKernelGGL(k_density_coef, dim3(grid1(n, 2048), nb), dim3(256), 0, st, w.a, astride, n, w.sums, w.lq,
-                       w.coef, cstride, active);
+    const dim3 grid(nch, (s.M + 3) / 4, nb);
     if (p == 10)
-      hipLaunchKernelGGL(k_density_b2<10>, dim3(nch, (s.M + 3) / 4, nb), dim3(256), 0, st, s, G, G_stride, pts,
-                         ld, pts_stride, n, w.coef, cstride, p, w.pb2, active);
+      hipLaunchKernelGGL(k_density_b2<10>, grid, dim3(256), 0, st, s, G, G_stride, pts, ld, pts_stride, n, w.a,
+                         astride, w.sums, w.lq, p, w.pb2, active);
     else
-      hipLaunchKernelGGL(k_density_b2<0>, dim3(nch, (s.M + 3) / 4, nb), dim3(256), 0, st, s, G, G_stride, pts,
-                         ld, pts_stride, n, w.coef, cstride, p, w.pb2, active);
-    hipLaunchKernelGGL(k_density_b2_reduce, dim3(s.M, nb), dim3(256), 0, st, w.pb2, s.M, nch, w.U,
-                       active);
-    hipLaunchKernelGGL(k_density_grad, dim3(1, nb), dim3(64), 0, st, s, G, G_stride, w.U, p, abs_det, dG, dG_stride,
-                       dG_rows, accumulate, w.sums, active);
+      hipLaunchKernelGGL(k_density_b2<0>, grid, dim3(256), 0, st, s, G, G_stride, pts, ld, pts_stride, n, w.a,
+                         astride, w.sums, w.lq, p, w.pb2, active);
+    hipLaunchKernelGGL(k_density_grad, dim3(s.M, nb), dim3(256), 0, st, s, G, G_stride, w.pb2, nch, p, abs_det, dG,
+                       dG_stride, dG_rows, accumulate, w.sums, active);
   }
-  if (loss) hipLaunchKernelGGL(k_copy_f64, dim3((nb + 63) / 64), dim3(64), 0, st, w.lq, 3, loss, lstride, nb, 1.0);
   return hipGetLastError();
 }
 
@@ -559,7 +569,8 @@ struct StepWs {
   float* dF;      // [nb][F]
   float* dW;      // [nb][W]
   double* dG;     // [nb][12 M]  transform gradient used by Adam
-  double* lrec;   // [nb] sum (f - v)^2
+  float *adam, *adam_g;   // [nb][2] Adam rates of this step: grids and MLP, transforms
+  uint64_t* step; // [1] the step counter the batch is drawn with
   double* part;   // adjoint partials
   int32_t* live;  // [nb] models that train this step (not frozen)
   int32_t* dlive; // [nb] models whose transforms train this step
@@ -589,7 +600,9 @@ size_t step_ws(const apmg_batch* b, const Shape& s, void* ws, StepWs* o) {
   w.dF = cv.take<float>((size_t)nb * f_elems(s));
   w.dW = cv.take<float>((size_t)nb * w_elems(s));
   w.dG = cv.take<double>((size_t)nb * 12 * s.M);
-  w.lrec = cv.take<double>((size_t)nb);
+  w.adam = cv.take<float>((size_t)nb * 2);
+  w.adam_g = cv.take<float>((size_t)nb * 2);
+  w.step = cv.take<uint64_t>(1);
   w.part = cv.take<double>((size_t)nb * step_max_blocks(b->n, nb) * max_part_len(s, bf));
   w.live = cv.take<int32_t>((size_t)nb);
   w.dlive = cv.take<int32_t>((size_t)nb);
@@ -792,16 +805,10 @@ apmg_status apmg_backward(const apmg_model* m, const float* pts, int64_t ld, int
   if (passes.empty()) return APMG_EUNSUPPORTED;
   const bool acc = flags & APMG_ACCUMULATE;
   const size_t nF = (size_t)s.M * s.R * s.R * s.R * s.C;
-  if (!acc) {
-    if (dW) {
-      hipLaunchKernelGGL(k_fill_f32, dim3(grid1((int64_t)s.H * s.MC)), dim3(256), 0, st, dW[0], (size_t)s.H * s.MC, 0.f);
-      hipLaunchKernelGGL(k_fill_f32, dim3(grid1((int64_t)s.H * s.H)), dim3(256), 0, st, dW[1], (size_t)s.H * s.H, 0.f);
-      hipLaunchKernelGGL(k_fill_f32, dim3(1), dim3(256), 0, st, dW[2], (size_t)s.H, 0.f);
-    }
-    if (n == 0) {
-      if (dF) hipLaunchKernelGGL(k_fill_f32, dim3(grid1(nF)), dim3(256), 0, st, dF, nF, 0.f);
-      if (dG) hipLaunchKernelGGL(k_fill_f64, dim3(1), dim3(256), 0, st, dG, (size_t)4 * grows * s.M, 0.0);
-    }
+  if (!acc && n == 0) {
+    clear_dw(s, dW, st);
+    if (dF) hipLaunchKernelGGL(k_fill_f32, dim3(grid1(nF)), dim3(256), 0, st, dF, nF, 0.f);
+    if (dG) hipLaunchKernelGGL(k_fill_f64, dim3(1), dim3(256), 0, st, dG, (size_t)4 * grows * s.M, 0.0);
   }
   if (n == 0) return hip_status(hipGetLastError());
   BwdWs w;
@@ -841,17 +848,9 @@ apmg_status apmg_backward(const apmg_model* m, const float* pts, int64_t ld, int
                : launch_tile(true, kb, a, gf16, bf, dim3(nblk, 1), backward_lds_bytes(s, ncols, nrows, bf, kb), st);
     if (e != hipSuccess) return APMG_EHIP;
     if (&ps == &passes.back()) prof_end(st, 0);
-    if (ncols > 0)
-      hipLaunchKernelGGL(k_reduce_parts, dim3(red_blocks((int64_t)s.H * ncols), 1), dim3(256), 0, st, w.part,
-                         nblk, pl.len, pl.o_w1, s.H * ncols, ncols, s.MC, ps.c1_lo, dW[0], (double*)nullptr,
-                         (size_t)0, 1, (const int32_t*)nullptr);
-    if (nrows > 0)
-      hipLaunchKernelGGL(k_reduce_parts, dim3(red_blocks((int64_t)s.H * nrows), 1), dim3(256), 0, st, w.part, nblk,
-                         pl.len, pl.o_w2, s.H * nrows, s.H * nrows, 0, ps.w2_lo * s.H, dW[1], (double*)nullptr,
-                         (size_t)0, 1, (const int32_t*)nullptr);
-    if (a.do_w3)
-      hipLaunchKernelGGL(k_reduce_parts, dim3(1, 1), dim3(256), 0, st, w.part, nblk, pl.len, pl.o_w3, s.H, s.H, 0,
-                         0, dW[2], (double*)nullptr, (size_t)0, 1, (const int32_t*)nullptr);
+    // (without the activation path the one pass holds every column and row)
+    if (dW && !use_act) reduce_dw(s, s.MC, s.H, true, w.part, nblk, pl.len, dW[0], dW[1], dW[2], acc ? 1 : 0, st);
+    if (dW && use_act) reduce_dw(s, 0, 0, true, w.part, nblk, pl.len, nullptr, nullptr, dW[2], acc ? 1 : 0, st);
   }
   // the weight-gradient products (activation path) and the grid-gradient gather both read
   // what the adjoint kernel wrote and write disjoint outputs: the products run on the
@@ -883,12 +882,7 @@ apmg_status apmg_backward(const apmg_model* m, const float* pts, int64_t ld, int
       hipLaunchKernelGGL(k_dw_gemm<false>, g2, dim3(256), 0, pst, w.act, rows_tot, s.MC + 2 * s.H, s.MC, np, s.H,
                          s.H, w.gpart, plen, s.H * s.MC);
     }
-    hipLaunchKernelGGL(k_reduce_parts, dim3(red_blocks((int64_t)s.H * s.MC), 1), dim3(256), 0, pst, w.gpart, nch,
-                       plen, 0, s.H * s.MC, s.MC, s.MC, 0, dW[0], (double*)nullptr, (size_t)0, 1,
-                       (const int32_t*)nullptr);
-    hipLaunchKernelGGL(k_reduce_parts, dim3(red_blocks((int64_t)s.H * s.H), 1), dim3(256), 0, pst, w.gpart, nch,
-                       plen, s.H * s.MC, s.H * s.H, s.H, s.H, 0, dW[1], (double*)nullptr, (size_t)0, 1,
-                       (const int32_t*)nullptr);
+    reduce_dw(s, s.MC, s.H, false, w.gpart, nch, plen, dW[0], dW[1], nullptr, acc ? 1 : 0, pst);
   }
   hipError_t ec = hipSuccess;
   if (want_cells)
@@ -1050,15 +1044,15 @@ apmg_status run_step(const apmg_batch* b, const Shape& s, void* ws, const Tune& 
   step_ws(b, s, ws, &w);
   const size_t nF = f_elems(s), nW = w_elems(s), nG = (size_t)12 * s.M;
   const size_t swz_stride = swz_sizes(s).total();
-  hipLaunchKernelGGL(k_live_masks, dim3((nb + 63) / 64), dim3(64), 0, st, b->frozen, b->density_active, w.live,
-                     w.dlive, nb);
+  hipLaunchKernelGGL(k_step_begin, dim3((nb + 63) / 64), dim3(64), 0, st, b->frozen, b->density_active, b->bricks, b->t,
+                     b->tG, b->step, b->lr, b->lr_G, b->beta1, b->beta2, b->lr_scale, update ? 1 : 0, w.live, w.dlive,
+                     w.scale, w.adam, w.adam_g, w.step, nb);
   const bool paper = paper_grids(&b->shape);
   const void* Fg = nullptr;
   hipError_t e = hipSuccess;
   {
-    // The gather copy of the grids, the weights' operands, the output scaling and the zeroed
-    // gradients do not depend on the batch points: they run on the device's side stream while
-    // the points are generated, sorted and sampled.
+    // The gather copy of the grids and the weights' operands do not depend on the batch points:
+    // they run on the device's side stream while the points are generated, sorted and sampled.
     std::lock_guard<std::mutex> lk(g_side_mu);     // one fork..join at a time per process
     SideStream* side = n > 0 ? side_stream(st) : nullptr;
     hipStream_t pst = st;
@@ -1069,25 +1063,23 @@ apmg_status run_step(const apmg_batch* b, const Shape& s, void* ws, const Tune& 
     const float* Gc;
     if (launch_ops(s, nb, b->G, 3, b->F, false, paper, w.ops, gf16, pst, &Gc, &Fg) != hipSuccess) return APMG_EHIP;
     (void)Gc;
-    // 2. operands of this step's weights, output scaling, zeroed gradients
+    // 2. operands of this step's weights
     e = launch_swizzle(s, bf, b->W, b->W + (size_t)s.H * s.MC, b->W + (size_t)s.H * s.MC + (size_t)s.H * s.H, nW,
                        w.swz, swz_stride, w.w3s, nb, pst);
     if (e != hipSuccess) return APMG_EHIP;
-    hipLaunchKernelGGL(k_brick_scale, dim3((nb + 63) / 64), dim3(64), 0, pst, b->bricks, w.scale, nb);
-    hipLaunchKernelGGL(k_fill_f32, dim3(grid1((int64_t)(nb * nW))), dim3(256), 0, pst, w.dW, nb * nW, 0.f);
-    hipLaunchKernelGGL(k_fill_f64, dim3(1), dim3(256), 0, pst, w.lrec, (size_t)nb, 0.0);
     // an empty batch: every gradient of the (empty) losses is zero, the transforms' included
     // (the density chain that writes dG runs only for a non-empty batch)
     if (n == 0) {
       hipLaunchKernelGGL(k_fill_f32, dim3(grid1((int64_t)(nb * nF))), dim3(256), 0, pst, w.dF, nb * nF, 0.f);
+      hipLaunchKernelGGL(k_fill_f32, dim3(grid1((int64_t)(nb * nW))), dim3(256), 0, pst, w.dW, nb * nW, 0.f);
       hipLaunchKernelGGL(k_fill_f64, dim3(grid1((int64_t)(nb * nG))), dim3(256), 0, pst, w.dG, nb * nG, 0.0);
     }
     // pass A of the density loss needs the drawn points and the transforms only: beside the sort
     if (n > 0)
-      launch_density_a_gen(s, b->G, nG, b->seed, b->step, b->stream0, n, b->p, b->flags, w.den, nb, w.dlive, pst);
+      launch_density_a_gen(s, b->G, nG, b->seed, w.step, b->stream0, n, b->p, b->flags, w.den, nb, w.dlive, pst);
     // 1. batch points, sorted by spatial bin, and the ground truth at the sorted points
     if (n > 0) {
-      hipError_t e0 = launch_step_sort(b->seed, b->step, b->stream0, n, nb, w.srt, b->volume, b->vol[0], b->vol[1],
+      hipError_t e0 = launch_step_sort(b->seed, w.step, b->stream0, n, nb, w.srt, b->volume, b->vol[0], b->vol[1],
                                        b->bricks, w.v, st);
       if (e0 != hipSuccess) return APMG_EHIP;
     }
@@ -1100,9 +1092,11 @@ apmg_status run_step(const apmg_batch* b, const Shape& s, void* ws, const Tune& 
   // 3. forward + adjoint of L_rec (part 1 of the step)
   const int nblk = tu.tile_blocks;
   const bool use_act = act_path(s, bf);
-  const std::vector<Pass> passes = use_act ? std::vector<Pass>{{0, 0, 0, 0, true}} : plan_passes(s, bf, true);
-  if (passes.empty()) return APMG_EUNSUPPORTED;
-  const int kb = (!use_act && passes.size() == 1) ? register_kb(s) : 0;
+  // (one pass: the register-resident shapes accumulate every column and row, the others store
+  // their activations)
+  const int kb = use_act ? 0 : register_kb(s);
+  const int ncols = use_act ? 0 : s.MC, nrows = use_act ? 0 : s.H;
+  const PartLayout pl = part_layout(s, ncols, nrows);
   const bool rec_dG = b->flags & APMG_ADD_REC_DG;
   const size_t act_stride = (size_t)(s.MC + 3 * s.H) * act_ld(n);
   // activation path: dW1 and dW2 of every model from its stored activations
@@ -1126,33 +1120,17 @@ apmg_status run_step(const apmg_batch* b, const Shape& s, void* ws, const Tune& 
                            gp, plen, s.H * s.MC);
       }
     }
-    hipLaunchKernelGGL(k_reduce_parts, dim3(red_blocks((int64_t)s.H * s.MC), nb), dim3(256), 0, rs, w.gpart, nch,
-                       plen, 0, s.H * s.MC, s.MC, s.MC, 0, w.dW, (double*)nullptr, nW, 0, (const int32_t*)w.live);
-    hipLaunchKernelGGL(k_reduce_parts, dim3(red_blocks((int64_t)s.H * s.H), nb), dim3(256), 0, rs, w.gpart, nch,
-                       plen, s.H * s.MC, s.H * s.H, s.H, s.H, s.H * s.MC, w.dW, (double*)nullptr, nW, 0,
-                       (const int32_t*)w.live);
+    const int n1 = s.H * s.MC, n2 = s.H * s.H;
+    hipLaunchKernelGGL(k_reduce_dw, dim3(red_blocks(n1 + n2), nb), dim3(256), 0, rs, w.gpart, nch, plen, n1, n2, 0, w.dW,
+                       w.dW + n1, (float*)nullptr, nW, 0, (const int32_t*)w.live);
   };
-  // block partials of one pass -> dW (and, for the first pass, dW3 and the L_rec sum)
-  auto reduce_pass = [&](const Pass& ps, hipStream_t rs) {
-    const int ncols = ps.c1_hi - ps.c1_lo, nrows = ps.w2_hi - ps.w2_lo;
-    const PartLayout pl = part_layout(s, ncols, nrows);
-    if (ncols > 0)
-      hipLaunchKernelGGL(k_reduce_parts, dim3(red_blocks((int64_t)s.H * ncols), nb), dim3(256), 0, rs, w.part, nblk,
-                         pl.len, pl.o_w1, s.H * ncols, ncols, s.MC, ps.c1_lo, w.dW, (double*)nullptr, nW, 0,
-                         (const int32_t*)w.live);
-    if (nrows > 0)
-      hipLaunchKernelGGL(k_reduce_parts, dim3(red_blocks((int64_t)s.H * nrows), nb), dim3(256), 0, rs, w.part, nblk,
-                         pl.len, pl.o_w2, s.H * nrows, s.H * nrows, 0, s.H * s.MC + ps.w2_lo * s.H, w.dW,
-                         (double*)nullptr, nW, 0, (const int32_t*)w.live);
-    if (ps.first) {
-      hipLaunchKernelGGL(k_reduce_parts, dim3(1, nb), dim3(256), 0, rs, w.part, nblk, pl.len, pl.o_w3, s.H, s.H, 0,
-                         s.H * s.MC + s.H * s.H, w.dW, (double*)nullptr, nW, 0, (const int32_t*)w.live);
-      hipLaunchKernelGGL(k_reduce_parts, dim3(1, nb), dim3(256), 0, rs, w.part, nblk, pl.len, pl.o_loss, 1, 1, 0, 0,
-                         (float*)nullptr, w.lrec, (size_t)1, 0, (const int32_t*)w.live);
-    }
+  // the adjoint's block partials -> dW (of the activation path the output layer alone)
+  auto reduce_part = [&](hipStream_t rs) {
+    const int n1 = use_act ? 0 : s.H * s.MC, n2 = use_act ? 0 : s.H * s.H;
+    hipLaunchKernelGGL(k_reduce_dw, dim3(red_blocks(n1 + n2 + s.H), nb), dim3(256), 0, rs, w.part, nblk, pl.len, n1, n2,
+                       s.H, w.dW, w.dW + n1, w.dW + (size_t)s.H * s.MC + (size_t)s.H * s.H, nW, 0, (const int32_t*)w.live);
   };
-  for (size_t pi = 0; pi < passes.size() && n > 0; ++pi) {
-    const Pass& ps = passes[pi];
+  if (n > 0) {
     TileArgs a;
     memset(&a, 0, sizeof(a));
     a.s = s;
@@ -1163,27 +1141,23 @@ apmg_status run_step(const apmg_batch* b, const Shape& s, void* ws, const Tune& 
     a.pts = w.srt.spts; a.ld = n; a.pts_stride = (size_t)3 * n; a.n = n;
     a.df = nullptr; a.v = w.v; a.v_stride = n; a.err = w.err; a.err_stride = n;
     a.err_abs = (b->flags & APMG_ERR_ABS) ? 1 : 0;
-    a.dY = ps.first ? w.cell.dY : nullptr;
-    a.c1_lo = ps.c1_lo; a.c1_hi = ps.c1_hi;
-    a.w2_lo = ps.w2_lo; a.w2_hi = ps.w2_hi;
-    a.do_w3 = ps.first;
-    a.want_loss = ps.first;
+    a.dY = w.cell.dY;
+    a.c1_lo = 0; a.c1_hi = ncols;
+    a.w2_lo = 0; a.w2_hi = nrows;
+    a.do_w3 = 1;
+    a.want_loss = 1;
     a.part = w.part;
     a.active = w.live;
     a.act = use_act ? w.act : nullptr;
     a.act_rows = s.MC + 3 * s.H;
     a.act_stride = act_stride;
-    const int ncols = ps.c1_hi - ps.c1_lo, nrows = ps.w2_hi - ps.w2_lo;
-    const PartLayout pl = part_layout(s, ncols, nrows);
     a.part_len = pl.len;
-    if (pi == 0) prof_begin(st, 0);
+    prof_begin(st, 0);
     e = (kb > 0 && tu.adjoint < 3)
             ? launch_adjoint(a, gf16, bf, tu.adjoint, dim3(nblk, nb), st)
             : launch_tile(true, kb, a, gf16, bf, dim3(nblk, nb), backward_lds_bytes(s, ncols, nrows, bf, kb), st);
     if (e != hipSuccess) return APMG_EHIP;
-    if (pi + 1 == passes.size()) prof_end(st, 0);
-    // the last pass's reductions wait for the fork below (they overlap the gather)
-    if (pi + 1 < passes.size()) reduce_pass(ps, st);
+    prof_end(st, 0);
   }
   if (n == 0) hipLaunchKernelGGL(k_fill_f64, dim3(1), dim3(256), 0, st, b->losses, (size_t)2 * nb, 0.0);
 
@@ -1199,15 +1173,15 @@ apmg_status run_step(const apmg_batch* b, const Shape& s, void* ws, const Tune& 
     hipStream_t dst = st;
     if (side && hipEventRecord(side->fork, st) == hipSuccess && hipStreamWaitEvent(side->s, side->fork, 0) == hipSuccess)
       dst = side->s;
-    // the density chain first: it is the longer of the two streams' work, and the
+    // L_rec and the sums the density loss starts from, then the density chain; the
     // weight-gradient reductions are needed only by Adam
+    hipLaunchKernelGGL(k_step_sums, dim3(nb), dim3(256), 0, dst, w.part, nblk, pl.len, pl.o_loss, w.den.pa,
+                       dens_blocks(n), n, b->losses, w.den.sums, w.live, w.dlive);
     const hipError_t ed = launch_density(s, b->G, nG, w.srt.spts, n, (size_t)3 * n, n, w.err, n, b->eps_density,
                                          b->p, b->flags, b->losses + 1, 2, w.dG, nG, 3, 0, nullptr, w.den, nb,
                                          w.dlive, dst, w.srt.v0);
-    reduce_pass(passes.back(), dst);
+    reduce_part(dst);
     if (use_act) act_products(dst);
-    hipLaunchKernelGGL(k_copy_f64, dim3((nb + 63) / 64), dim3(64), 0, dst, w.lrec, 1, b->losses, 2, nb,
-                       1.0 / (double)n);
     const hipError_t ec = launch_cells(s, gf16, b->G, nG, Fg, nF, w.srt, n, w.cell, w.dF, nF, paper ? 1 : 0, 0,
                                        rec_dG, nullptr, 0, 3, 0, nb, w.live, st, tu.cell_unroll, nullptr,
                                        tu.cell_kernel);
@@ -1224,17 +1198,12 @@ apmg_status run_step(const apmg_batch* b, const Shape& s, void* ws, const Tune& 
   if (!update) return hip_status(hipGetLastError());
 
   // 6. Adam: grids and MLP every step, transforms while the density phase is active
-  hipLaunchKernelGGL(k_adam, dim3(grid1(((int64_t)nF + 3) / 4), nb), dim3(256), 0, st, b->F, b->mF, b->vF, (const float*)w.dF,
-                     (const double*)nullptr, nF, (const int32_t*)b->t, (const int32_t*)w.live, b->lr, b->beta1,
-                     b->beta2, b->adam_eps, b->lr_scale);
-  hipLaunchKernelGGL(k_adam, dim3(grid1(((int64_t)nW + 3) / 4), nb), dim3(256), 0, st, b->W, b->mW, b->vW, (const float*)w.dW,
-                     (const double*)nullptr, nW, (const int32_t*)b->t, (const int32_t*)w.live, b->lr, b->beta1,
-                     b->beta2, b->adam_eps, b->lr_scale);
-  hipLaunchKernelGGL(k_adam, dim3(1, nb), dim3(256), 0, st, b->G, b->mG, b->vG, (const float*)nullptr,
-                     (const double*)w.dG, nG, (const int32_t*)b->tG, (const int32_t*)w.dlive, b->lr_G, b->beta1,
-                     b->beta2, b->adam_eps, b->lr_scale);
-  hipLaunchKernelGGL(k_step_counters, dim3((nb + 63) / 64), dim3(64), 0, st, b->t, b->tG, (const int32_t*)w.live,
-                     (const int32_t*)w.dlive, b->step, nb);
+  const int bF = (int)grid1(((int64_t)nF + 3) / 4), bW = (int)grid1(((int64_t)nW + 3) / 4);
+  const AdamSet aF = {b->F, b->mF, b->vF, w.dF, nullptr, nF}, aW = {b->W, b->mW, b->vW, w.dW, nullptr, nW},
+                aG = {b->G, b->mG, b->vG, nullptr, w.dG, nG};
+  const AdamArgs h = {b->beta1, b->beta2, b->adam_eps};
+  hipLaunchKernelGGL(k_adam, dim3(bF + bW + 1, nb), dim3(256), 0, st, aF, aW, aG, bF, bW, h, (const float*)w.adam,
+                     (const float*)w.adam_g, (const int32_t*)w.live, (const int32_t*)w.dlive);
   return hip_status(hipGetLastError());
 }
 
@@ -1635,11 +1604,7 @@ apmg_status apmg_variant_backward(const apmg_model* m, const apmg_encoder* e, co
   VarWs w;
   var_ws(s, ea, m, e, n, true, ws, &w);
   if (!acc) {
-    if (dW) {
-      hipLaunchKernelGGL(k_fill_f32, dim3(grid1((int64_t)s.H * s.MC)), dim3(256), 0, st, dW[0], (size_t)s.H * s.MC, 0.f);
-      hipLaunchKernelGGL(k_fill_f32, dim3(grid1((int64_t)s.H * s.H)), dim3(256), 0, st, dW[1], (size_t)s.H * s.H, 0.f);
-      hipLaunchKernelGGL(k_fill_f32, dim3(1), dim3(256), 0, st, dW[2], (size_t)s.H, 0.f);
-    }
+    if (n == 0) clear_dw(s, dW, st);
     // (the per-cell gather of the 4-D grids overwrites dF)
     if (dF && (n == 0 || e->kind == APMG_ENC_HASH || !w.tcc)) hipLaunchKernelGGL(k_fill_f32, dim3(grid1(nF)), dim3(256), 0, st, dF, nF, 0.f);
     if (dG) hipLaunchKernelGGL(k_fill_f64, dim3(1), dim3(256), 0, st, dG, (size_t)4 * grows * mt, 0.0);
@@ -1690,16 +1655,7 @@ apmg_status apmg_variant_backward(const apmg_model* m, const apmg_encoder* e, co
   a.part = w.part;
   a.part_len = pl.len;
   if (launch_enc_adjoint(a, e->kind, bf, dim3(nblk, 1), st) != hipSuccess) return APMG_EHIP;
-  if (dW) {
-    hipLaunchKernelGGL(k_reduce_parts, dim3(red_blocks((int64_t)s.H * s.MC), 1), dim3(256), 0, st, w.part, nblk,
-                       pl.len, pl.o_w1, s.H * s.MC, s.MC, s.MC, 0, dW[0], (double*)nullptr, (size_t)0, 1,
-                       (const int32_t*)nullptr);
-    hipLaunchKernelGGL(k_reduce_parts, dim3(red_blocks((int64_t)s.H * s.H), 1), dim3(256), 0, st, w.part, nblk,
-                       pl.len, pl.o_w2, s.H * s.H, s.H * s.H, 0, 0, dW[1], (double*)nullptr, (size_t)0, 1,
-                       (const int32_t*)nullptr);
-    hipLaunchKernelGGL(k_reduce_parts, dim3(1, 1), dim3(256), 0, st, w.part, nblk, pl.len, pl.o_w3, s.H, s.H, 0, 0,
-                       dW[2], (double*)nullptr, (size_t)0, 1, (const int32_t*)nullptr);
-  }
+  if (dW) reduce_dw(s, s.MC, s.H, true, w.part, nblk, pl.len, dW[0], dW[1], dW[2], acc ? 1 : 0, st);
   if (!want_enc) return hip_status(hipGetLastError());
   EncScatterArgs sa;
   memset(&sa, 0, sizeof(sa));

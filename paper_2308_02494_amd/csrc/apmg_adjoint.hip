@@ -201,7 +201,7 @@ __global__ void __launch_bounds__(NW * kWave, 8 / NW) k_adjoint(TileArgs a) {
   double* part = a.part + ((size_t)model * gridDim.x + lb) * pl.len;
   const bool act = !a.active || a.active[model];
 
-  // LDS: sG [12M] | sW3w [wave][H] | sLoss [wave] | swizzled weights | TD, TY [64][P]
+  // LDS: sG [12M] | sW3w [wave][H] | sLoss [wave][point][2] | swizzled weights | TD, TY [64][P]
   // (the cross-wave weight-gradient sums alias TD/TY at the end)
   const size_t esz = BF ? 2 : 4;
   const size_t wbytes = swz_sizes(s).total() * esz;
@@ -209,9 +209,9 @@ __global__ void __launch_bounds__(NW * kWave, 8 / NW) k_adjoint(TileArgs a) {
   float* sG = smem;
   float* sW3w = sG + 12 * s.M;
   size_t off = (size_t)(12 * s.M + kAdjWaves * H) * 4;
-  off = (off + 7) & ~(size_t)7;
+  off = (off + 15) & ~(size_t)15;
   double* sLoss = (double*)(lbase + off);
-  off = (off + 8 * kAdjWaves + 15) & ~(size_t)15;
+  off = (off + 16 * 32 * kAdjWaves + 15) & ~(size_t)15;
   char* lw = lbase + off;
   TT_* TD = (TT_*)(lbase + off + wbytes);
   TT_* TY = TD + (size_t)64 * P;
@@ -249,7 +249,10 @@ __global__ void __launch_bounds__(NW * kWave, 8 / NW) k_adjoint(TileArgs a) {
   f32x16 acc1, acc2;
 #pragma unroll
   for (int r = 0; r < 16; ++r) { acc1[r] = 0.f; acc2[r] = 0.f; }
-  double loss = 0.0;
+  // this lane's sums of (f - v)^2 and of the errors, in LDS: as registers held across the tile
+  // they put the kernel into scratch
+  double2* lsum = (double2*)sLoss + threadIdx.x / 64 * 32 + (threadIdx.x & 31);
+  if ((threadIdx.x & 63) < 32) *lsum = make_double2(0.0, 0.0);
   const int nblk = s.KHP / 16;
 
   const int64_t ntiles = act ? (a.n + 31) / 32 : 0;
@@ -282,8 +285,12 @@ __global__ void __launch_bounds__(NW * kWave, 8 / NW) k_adjoint(TileArgs a) {
         const float e = fv - a.v[model * a.v_stride + p];
         df = 2.0f * e / (float)a.n;
         if (lane < 32) {
-          a.err[model * a.err_stride + p] = a.err_abs ? fabsf(e) : e * e;
-          loss += (double)e * (double)e;
+          const float h = a.err_abs ? fabsf(e) : e * e;
+          a.err[model * a.err_stride + p] = h;
+          double2 ls = *lsum;
+          ls.x += (double)e * (double)e;
+          ls.y += (double)h;
+          *lsum = ls;
         }
       }
     }
@@ -496,8 +503,9 @@ __global__ void __launch_bounds__(NW * kWave, 8 / NW) k_adjoint(TileArgs a) {
     }
   }
   if (a.want_loss) {
-    const double t = wave_sum(loss);
-    if (lane == 0) sLoss[wave] = t;
+    const double2 ls = lane < 32 ? *lsum : make_double2(0.0, 0.0);
+    const double t = wave_sum(ls.x), u = wave_sum(ls.y);
+    if (lane == 0) *lsum = make_double2(t, u);
   }
   __syncthreads();
   for (int i = threadIdx.x; i < H * s.MC; i += blockDim.x) part[pl.o_w1 + i] = sW1[i];
@@ -508,18 +516,18 @@ __global__ void __launch_bounds__(NW * kWave, 8 / NW) k_adjoint(TileArgs a) {
       for (int w = 0; w < kAdjWaves; ++w) t += (double)sW3w[w * H + i];
       part[pl.o_w3 + i] = t;
     }
-  if (threadIdx.x == 0) {
+  if (threadIdx.x < 2) {
     double t = 0.0;
-    for (int w = 0; w < kAdjWaves; ++w) t += a.want_loss ? sLoss[w] : 0.0;
-    part[pl.o_loss] = t;
+    for (int w = 0; w < kAdjWaves; ++w) t += a.want_loss ? sLoss[64 * w + threadIdx.x] : 0.0;
+    part[pl.o_loss + threadIdx.x] = t;
   }
 }
 
 // LDS bytes of k_adjoint with nw waves per block.
 size_t adjoint_lds_bytes(const Shape& s, bool bf, int nw) {
   size_t b = (size_t)(12 * s.M + nw * s.H) * 4;
-  b = (b + 7) & ~(size_t)7;
-  b += 8 * nw;
+  b = (b + 15) & ~(size_t)15;
+  b += 16 * 32 * nw;
   b = (b + 15) & ~(size_t)15;
   const size_t esz = bf ? 2 : 4;
   b += swz_sizes(s).total() * esz;

@@ -77,7 +77,7 @@ struct TileArgs {
   int c1_lo, c1_hi;                       // first-layer gradient columns accumulated by this launch
   int w2_lo, w2_hi;                       // second-layer gradient rows (multiples of 32)
   int do_w3;                              // accumulate the output layer gradient
-  int want_loss;                          // accumulate sum (f - v)^2
+  int want_loss;                          // accumulate sum (f - v)^2 and the sum of the errors
   double* part; int part_len;             // per-block partials [model][block][part_len]
   const int32_t* active;                  // per model: skip the model when 0 (or NULL)
   // activation path: when non-NULL, the per-point activations of the weight-gradient
@@ -89,18 +89,17 @@ struct TileArgs {
 };
 
 // Per-block partial sums of the adjoint, float64: [dW1 slice H x ncols]
-// [dW2 rows nrows2 x H] [dW3 H] [dG M x 12] [loss 1].
+// [dW2 rows nrows2 x H] [dW3 H] [sum (f - v)^2, sum of the errors h].
 struct PartLayout {
-  int o_w1, o_w2, o_w3, o_g, o_loss, len;
+  int o_w1, o_w2, o_w3, o_loss, len;
 };
 __host__ __device__ inline PartLayout part_layout(const Shape& s, int ncols, int nrows2) {
   PartLayout p;
   p.o_w1 = 0;
   p.o_w2 = s.H * ncols;
   p.o_w3 = p.o_w2 + nrows2 * s.H;
-  p.o_g = p.o_w3 + s.H;
-  p.o_loss = p.o_g + 12 * s.M;
-  p.len = p.o_loss + 1;
+  p.o_loss = p.o_w3 + s.H;
+  p.len = p.o_loss + 2;
   return p;
 }
 

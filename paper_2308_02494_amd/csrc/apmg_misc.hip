@@ -12,16 +12,17 @@ __global__ void k_fill_f64(double* p, size_t n, double v) {
   for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) p[i] = v;
 }
 
-// out[model][e] (+)= sum_b part[(model*nblk + b)*len + off + e] for e < count, in float64.
-// Element e lands at (e / cols) * ld_out + col0 + e % cols of the model's output.
-// A block handles 32 elements; its 8 thread groups sum 8 contiguous ranges of b, which are
-// then added in range order (a fixed order: bitwise reproducible).
+// Weight gradients from per-block partials: for e < n1 + n2 + n3, the sum over blocks b of
+// part[(model*nblk + b)*len + e], in float64, (+)= into out1, out2 or out3 (per-model arrays at
+// model * out_stride) by the layer e falls in.  A block handles 32 elements; its 8 thread groups
+// sum 8 contiguous ranges of b, which are then added in range order (a fixed order: bitwise
+// reproducible).
 constexpr int kRedElems = 32, kRedSplit = 8;
-__global__ void __launch_bounds__(256) k_reduce_parts(const double* part, int nblk, int len, int off, int count,
-                                                      int cols, int ld_out, int col0, float* outf, double* outd,
-                                                      size_t out_stride, int accumulate, const int32_t* active) {
+__global__ void __launch_bounds__(256) k_reduce_dw(const double* part, int nblk, int len, int n1, int n2, int n3,
+                                                   float* out1, float* out2, float* out3, size_t out_stride,
+                                                   int accumulate, const int32_t* active) {
   __shared__ double sp[kRedSplit][kRedElems];
-  const int model = blockIdx.y;
+  const int model = blockIdx.y, count = n1 + n2 + n3;
   if (active && !active[model]) return;
   const int el = threadIdx.x % kRedElems, sp_i = threadIdx.x / kRedElems;
   const int per = (nblk + kRedSplit - 1) / kRedSplit;
@@ -30,7 +31,7 @@ __global__ void __launch_bounds__(256) k_reduce_parts(const double* part, int nb
     const int e = base + el;
     double s = 0.0;
     if (e < count) {
-      const double* p = part + (size_t)model * nblk * len + off + e;
+      const double* p = part + (size_t)model * nblk * len + e;
 #pragma unroll 8
       for (int b = b0; b < b1; ++b) s += p[(size_t)b * len];
     }
@@ -39,17 +40,11 @@ __global__ void __launch_bounds__(256) k_reduce_parts(const double* part, int nb
     if (sp_i == 0 && e < count) {
       double t = sp[0][el];
       for (int k = 1; k < kRedSplit; ++k) t += sp[k][el];
-      const size_t oi = model * out_stride + (size_t)(e / cols) * ld_out + col0 + e % cols;
-      if (outf) outf[oi] = accumulate ? outf[oi] + (float)t : (float)t;
-      else outd[oi] = accumulate ? outd[oi] + t : t;
+      float* o = (e < n1 ? out1 + e : e < n1 + n2 ? out2 + (e - n1) : out3 + (e - n1 - n2)) + model * out_stride;
+      *o = accumulate ? *o + (float)t : (float)t;
     }
     __syncthreads();
   }
-}
-
-__global__ void k_copy_f64(const double* src, int sstride, double* dst, int dstride, int n, double scale) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) dst[(size_t)i * dstride] = src[(size_t)i * sstride] * scale;
 }
 
 // ------------------------------------------------------------------ points / ground truth
@@ -224,9 +219,9 @@ __device__ inline void flat_pow2(float l, int p, float& e2p, float& e2pm1) {
 // part: [model][block][2] = {sum rho, sum err}
 // GEN: the training batch as it is drawn -- point i of model b regenerated from its counter
 // (stream stream0 + b, the bits the sort and the ground truth use), rho kept at draw index i
-// (pass B1 reads it through the sort's permutation), only part[..][0]; the error sums
-// (part[..][1]) come from k_density_errsum once the adjoint has run.  This needs neither the
-// sorted points nor the errors, so it runs beside the batch sort.
+// (pass B1 reads it through the sort's permutation), only part[..][0]; the error sum comes from
+// the adjoint's partials (k_step_sums).  This needs neither the sorted points nor the errors,
+// so it runs beside the batch sort.
 template <int PF, bool GEN = false>
 __global__ void __launch_bounds__(256) k_density_a(Shape s, const float* Gall, size_t G_stride,
     const float* pts, int64_t ld, size_t pts_stride, int64_t n, const float* err, size_t err_stride,
@@ -276,28 +271,11 @@ __global__ void __launch_bounds__(256) k_density_a(Shape s, const float* Gall, s
         ((spart[threadIdx.x] + spart[2 + threadIdx.x]) + spart[4 + threadIdx.x]) + spart[6 + threadIdx.x];
 }
 
-// The error half of pass A's partials (part[model][block][1] = block sum of err, the blocks and
-// the order of k_density_a), for the training step's pass A over the drawn batch.
-__global__ void __launch_bounds__(256) k_density_errsum(const float* err, size_t err_stride, int64_t n, double* part,
-                                                        const int32_t* active) {
-  __shared__ double spart[4];
-  const int model = blockIdx.y;
-  double serr = 0.0;
-  if (!active || active[model])
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-      serr += err[model * err_stride + i];
-  serr = wave_sum(serr);
-  if ((threadIdx.x & 63) == 0) spart[threadIdx.x >> 6] = serr;
-  __syncthreads();
-  if (threadIdx.x == 0)
-    part[((size_t)model * gridDim.x + blockIdx.x) * 2 + 1] = ((spart[0] + spart[1]) + spart[2]) + spart[3];
-}
-
 // Fixed-order block sum of the K-tuples part[model][k][K], k < nblk: out[q] = sum_k [q].
 // Thread t sums the contiguous range [t*per, (t+1)*per); the 256 range sums are then added
-// by a fixed tree.  One block per model.
+// by a fixed tree.  One block per model.  Tuples are stride doubles apart.
 template <int K>
-__device__ inline void tuple_sum(const double* part, int nblk, double out[K]) {
+__device__ inline void tuple_sum(const double* part, int nblk, int stride, double out[K]) {
   __shared__ double sh[K][256];
   const int per = (nblk + 255) / 256;
   const int k0 = threadIdx.x * per, k1 = min(nblk, k0 + per);
@@ -306,7 +284,7 @@ __device__ inline void tuple_sum(const double* part, int nblk, double out[K]) {
   for (int q = 0; q < K; ++q) x[q] = 0.0;
   for (int k = k0; k < k1; ++k)
 #pragma unroll
-    for (int q = 0; q < K; ++q) x[q] += part[K * (size_t)k + q];
+    for (int q = 0; q < K; ++q) x[q] += part[(size_t)stride * k + q];
 #pragma unroll
   for (int q = 0; q < K; ++q) sh[q][threadIdx.x] = x[q];
   __syncthreads();
@@ -318,14 +296,33 @@ __device__ inline void tuple_sum(const double* part, int nblk, double out[K]) {
   }
 #pragma unroll
   for (int q = 0; q < K; ++q) out[q] = sh[q][0];
+  __syncthreads();
 }
 
 // Reduce pass-A partials: sums[model] = {S, sum err}.
 __global__ void __launch_bounds__(256) k_density_sums(const double* part, int nblk, double* sums, int nmodels) {
   const int model = blockIdx.x;
   double o[2];
-  tuple_sum<2>(part + (size_t)model * nblk * 2, nblk, o);
+  tuple_sum<2>(part + (size_t)model * nblk * 2, nblk, 2, o);
   if (threadIdx.x == 0) { sums[2 * model] = o[0]; sums[2 * model + 1] = o[1]; }
+}
+
+// The training step's sums of one model, once the adjoint has run: L_rec = (sum of squared
+// errors) / n into losses[2 model], and for the density loss sums[model] = {S of pass A's
+// partials rho_part[model][rho_blk][2], sum of errors}, both error sums from the adjoint's
+// partials adj[model][adj_blk][adj_len] at [loss, err].  Frozen models: L_rec 0.
+__global__ void __launch_bounds__(256) k_step_sums(const double* adj, int adj_blk, int adj_len, int o_loss,
+                                                   const double* rho_part, int rho_blk, int64_t n, double* losses,
+                                                   double* sums, const int32_t* live, const int32_t* dlive) {
+  const int model = blockIdx.x;
+  double e[2] = {0.0, 0.0}, r[1] = {0.0};
+  if (live[model]) tuple_sum<2>(adj + (size_t)model * adj_blk * adj_len + o_loss, adj_blk, adj_len, e);
+  if (dlive[model]) tuple_sum<1>(rho_part + (size_t)model * rho_blk * 2, rho_blk, 2, r);
+  if (threadIdx.x == 0) {
+    losses[2 * model] = e[0] * (1.0 / (double)n);
+    sums[2 * model] = r[0];
+    sums[2 * model + 1] = e[1];
+  }
 }
 
 // Target density and loss summand for one point, float64 (Eqs. (8), (9)): rho_s, the
@@ -379,11 +376,12 @@ __global__ void __launch_bounds__(256) k_density_b1(const float* rho, size_t rho
 // Reduce pass-B1 partials into lq[model] = {loss, Q, Z}: Z = 1 for the literal target, and
 // Z = sum rho* for the renormalised one (target rho*/Z), for which
 // loss = (sum of summands) / (n Z) - log(Z) / n and Q = Q_raw / Z.
-__global__ void __launch_bounds__(256) k_density_lq(const double* part, int nblk, int64_t n, double* lq, int nmodels,
-                                                    int norm_target) {
+// The loss also goes to loss[model * lstride].
+__global__ void __launch_bounds__(256) k_density_lq(const double* part, int nblk, int64_t n, double* lq, int norm_target,
+                                                    double* loss_out, int lstride) {
   const int model = blockIdx.x;
   double o[3];
-  tuple_sum<3>(part + (size_t)model * nblk * 3, nblk, o);
+  tuple_sum<3>(part + (size_t)model * nblk * 3, nblk, 3, o);
   if (threadIdx.x == 0) {
     const double Z = (norm_target && o[2] > 0.0) ? o[2] : 1.0;
     double loss = n > 0 ? o[0] / ((double)n * Z) : 0.0;
@@ -391,36 +389,28 @@ __global__ void __launch_bounds__(256) k_density_lq(const double* part, int nblk
     lq[3 * model] = loss;
     lq[3 * model + 1] = o[1] / Z;
     lq[3 * model + 2] = Z;
+    loss_out[(size_t)model * lstride] = loss;
   }
 }
 
-// Per-point coefficient c(x) = dL/drho(x) = (a(x)/Z - Q)/S (float64 arithmetic, stored float32).
-__global__ void k_density_coef(const double* a_in, size_t a_stride, int64_t n, const double* sums, const double* lq,
-                               float* coef, size_t coef_stride, const int32_t* active) {
-  const int model = blockIdx.y;
-  const bool act = (!active || active[model]) && sums[2 * model] != 0.0;
-  const double S = sums[2 * model];
-  const double Q = lq[3 * model + 1], Z = lq[3 * model + 2];
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-    float c = 0.f;
-    if (act) c = (float)((a_in[model * a_stride + i] / Z - Q) / S);
-    coef[model * coef_stride + i] = c;
-  }
-}
-
-// Pass B2: per grid i, U_i = {sum c phi_i, sum c phi_i q_d x_k (9), sum c phi_i q_d (3)}.
+// Pass B2: per grid i, U_i = {sum c phi_i, sum c phi_i q_d x_k (9), sum c phi_i q_d (3)} with the
+// per-point coefficient c(x) = dL/drho(x) = (a(x)/Z - Q)/S (float64 arithmetic, rounded to
+// float32; each grid's wave forms it again, which costs less than a pass of its own).
 // Wave w of block (chunk, grid group, model) owns grid 4*blockIdx.y + w and streams the
 // chunk's points; one wave reduction per (grid, chunk).  part: [model][M][chunk][13]
-constexpr int kDensChunk = 4096;
+// Points per chunk: 4096, and fewer for smaller batches, whose chunks would not fill the device
+// (65,536 points, 16 grids: 64 blocks of 4096-point chunks take 49 us, 512 blocks of 512 13 us).
+__host__ __device__ constexpr int dens_chunk(int64_t n) { return n >= (1 << 18) ? 4096 : n >= (1 << 17) ? 2048 : 512; }
 template <int PF>
 __global__ void __launch_bounds__(256) k_density_b2(Shape s, const float* Gall, size_t G_stride,
-    const float* pts, int64_t ld, size_t pts_stride, int64_t n, const float* coef, size_t coef_stride, int p,
-    double* part, const int32_t* active) {
+    const float* pts, int64_t ld, size_t pts_stride, int64_t n, const double* a_in, size_t a_stride,
+    const double* sums, const double* lq, int p, double* part, const int32_t* active) {
   const int model = blockIdx.z, wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int g = 4 * blockIdx.y + wave;
   const int nchunk = gridDim.x;
   if (g >= s.M) return;
-  const bool act = !active || active[model];
+  const double S = sums[2 * model];
+  const bool act = (!active || active[model]) && S != 0.0;
   float Gg[12];
   for (int k = 0; k < 12; ++k) Gg[k] = Gall[model * G_stride + 12 * g + k];
   float u[13];
@@ -428,10 +418,11 @@ __global__ void __launch_bounds__(256) k_density_b2(Shape s, const float* Gall, 
   for (int q = 0; q < 13; ++q) u[q] = 0.f;
   if (act) {
     const float* P = pts + model * pts_stride;
-    const float* cf = coef + model * coef_stride;
-    const int64_t i0 = (int64_t)blockIdx.x * kDensChunk, i1 = min(n, i0 + kDensChunk);
+    const double* av = a_in + model * a_stride;
+    const double rS = 1.0 / S, Q = lq[3 * model + 1], rZ = 1.0 / lq[3 * model + 2];
+    const int64_t i0 = (int64_t)blockIdx.x * dens_chunk(n), i1 = min(n, i0 + dens_chunk(n));
     for (int64_t i = i0 + lane; i < i1; i += 64) {
-      const float c = cf[i];
+      const float c = (float)((av[i] * rZ - Q) * rS);
       if (c == 0.f) continue;
       const float xs[3] = {P[i], P[ld + i], P[2 * ld + i]};
       float l[3];
@@ -460,138 +451,138 @@ __global__ void __launch_bounds__(256) k_density_b2(Shape s, const float* Gall, 
   }
 }
 
-// U[model][g][q] = sum over chunks of part[model][g][chunk][q]: thread t sums a contiguous
-// range of chunks, then a fixed tree adds the 256 range sums.  Grid (M, models).
-__global__ void __launch_bounds__(256) k_density_b2_reduce(const double* part, int M, int nchunk, double* U,
-                                                           const int32_t* active) {
-  __shared__ double sh[256];
-  const int model = blockIdx.y, g = blockIdx.x;
+// dG_i = sgn_i cof_i U0 - 2p det_i [U1 | U2] of grid blockIdx.x, U the sums over the chunks of
+// part[model][g][chunk][13] (thread t adds chunks t, t + 256, ..., then a fixed order over the
+// lanes and waves), where det_i and sgn_i are det(A_i) and 1 (signed reading) or |det(A_i)| and
+// sign(det(A_i)) (abs_det).  dG rows per transform: grows (3, or 4 with row 3 written as 0).
+__global__ void __launch_bounds__(256) k_density_grad(Shape s, const float* Gall, size_t G_stride, const double* part,
+                                                      int nchunk, int p, int abs_det, double* dG, size_t dG_stride,
+                                                      int grows, int accumulate, const double* sums,
+                                                      const int32_t* active) {
+  __shared__ double sh[4][13];
+  const int model = blockIdx.y, g = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   if (active && !active[model]) return;
-  const double* pp = part + ((size_t)model * M + g) * nchunk * 13;
-  const int per = (nchunk + 255) / 256;
-  const int k0 = threadIdx.x * per, k1 = min(nchunk, k0 + per);
+  const double* pp = part + ((size_t)model * s.M + g) * nchunk * 13;
+  double x[13];
+#pragma unroll
+  for (int q = 0; q < 13; ++q) x[q] = 0.0;
+  for (int k = threadIdx.x; k < nchunk; k += 256)
+#pragma unroll
+    for (int q = 0; q < 13; ++q) x[q] += pp[(size_t)k * 13 + q];
+#pragma unroll
   for (int q = 0; q < 13; ++q) {
-    double x = 0.0;
-    for (int k = k0; k < k1; ++k) x += pp[(size_t)k * 13 + q];
-    sh[threadIdx.x] = x;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-      if ((int)threadIdx.x < w) sh[threadIdx.x] += sh[threadIdx.x + w];
-      __syncthreads();
-    }
-    if (threadIdx.x == 0) U[((size_t)model * M + g) * 13 + q] = sh[0];
-    __syncthreads();
+    const double t = wave_sum(x[q]);
+    if (lane == 0) sh[wave][q] = t;
   }
-}
-
-// Assemble dG_i = cof_i U0 - 2p det_i [U1 | U2] from the reduced pass-B2 sums.
-// Assemble dG_i = sgn_i cof_i U0 - 2p det_i [U1 | U2] from the reduced pass-B2 sums, where
-// det_i and sgn_i are det(A_i) and 1 (signed reading) or |det(A_i)| and sign(det(A_i))
-// (abs_det).  dG rows per transform: grows (3, or 4 with row 3 written as 0).
-__global__ void k_density_grad(Shape s, const float* Gall, size_t G_stride, const double* U, int p, int abs_det,
-                               double* dG, size_t dG_stride, int grows, int accumulate, const double* sums,
-                               const int32_t* active) {
-  const int model = blockIdx.y;
-  if (active && !active[model]) return;
-  const bool zero = sums[2 * model] == 0.0;
-  for (int g = blockIdx.x * blockDim.x + threadIdx.x; g < s.M; g += gridDim.x * blockDim.x) {
-    double dc[10];
-    det_cof(Gall + model * G_stride + 12 * g, dc);
-    const double sgn = abs_det ? (dc[0] > 0.0 ? 1.0 : (dc[0] < 0.0 ? -1.0 : 0.0)) : 1.0;
-    const double det = abs_det ? fabs(dc[0]) : dc[0];
-    const double* u = U + (size_t)model * 13 * s.M + 13 * g;
-    double* o = dG + model * dG_stride + 4 * grows * g;
-    for (int r = 0; r < 3; ++r) {
-      for (int k = 0; k < 3; ++k) {
-        const double v = zero ? 0.0 : sgn * dc[1 + 3 * r + k] * u[0] - 2.0 * p * det * u[1 + 3 * r + k];
-        o[4 * r + k] = accumulate ? o[4 * r + k] + v : v;
-      }
-      const double v = zero ? 0.0 : -2.0 * p * det * u[10 + r];
-      o[4 * r + 3] = accumulate ? o[4 * r + 3] + v : v;
-    }
-    if (grows == 4 && !accumulate)
-      for (int k = 0; k < 4; ++k) o[12 + k] = 0.0;
+  __syncthreads();
+  const int e = threadIdx.x;
+  if (e >= 4 * grows) return;
+  double* o = dG + model * dG_stride + 4 * grows * g + e;
+  if (e >= 12) {
+    if (!accumulate) *o = 0.0;
+    return;
   }
+  const int r = e >> 2, k = e & 3;
+  double dc[10];
+  det_cof(Gall + model * G_stride + 12 * g, dc);
+  const double sgn = abs_det ? (dc[0] > 0.0 ? 1.0 : (dc[0] < 0.0 ? -1.0 : 0.0)) : 1.0;
+  const double det = abs_det ? fabs(dc[0]) : dc[0];
+  const auto U = [&](int q) { return ((sh[0][q] + sh[1][q]) + sh[2][q]) + sh[3][q]; };
+  double v = -2.0 * p * det * U(k < 3 ? 1 + 3 * r + k : 10 + r);
+  if (k < 3) v = sgn * dc[1 + 3 * r + k] * U(0) + v;
+  if (sums[2 * model] == 0.0) v = 0.0;
+  *o = accumulate ? *o + v : v;
 }
 
 // ------------------------------------------------------------------ Adam
-// theta -= lr * mhat / (sqrt(vhat) + eps), bias-corrected with step t+1 (t read from
-// counters[model]).  gd (double) or gf (float) gradient.
-// active: per model, skip when 0 (NULL = all); lr_scale: per model multiplier of lr (NULL = 1).
-__global__ void k_adam(float* theta, float* m, float* v, const float* gf, const double* gd, size_t per_model,
-                       const int32_t* counters, const int32_t* active, float lr, float b1, float b2,
-                       float eps, const float* lr_scale) {
-  const int model = blockIdx.y;
-  if (active && !active[model]) return;
-  // bias corrections in float64, once per block
-  __shared__ float sc[2];
-  if (threadIdx.x == 0) {
-    const int t = counters[model] + 1;
-    const float bc1 = (float)(1.0 - pow((double)b1, (double)t));
-    const float bc2 = (float)(1.0 - pow((double)b2, (double)t));
-    const float lrm = lr_scale ? lr * lr_scale[model] : lr;
-    sc[0] = lrm / bc1;
-    sc[1] = 1.0f / sqrtf(bc2);
+// theta -= lr * mhat / (sqrt(vhat) + eps), bias-corrected with step t + 1.  The rates of a step
+// are the same for every element of a model: sc[0] = lr lr_scale / (1 - b1^(t+1)), sc[1] =
+// 1 / sqrt(1 - b2^(t+1)), from k_step_begin.
+struct AdamArgs { float b1, b2, eps; };
+__device__ inline void adam_one(const AdamArgs& h, float step, float rb2, float g, float& mk, float& vk, float& th) {
+  mk = __builtin_fmaf(h.b1, mk, (1.f - h.b1) * g);
+  vk = __builtin_fmaf(h.b2, vk, (1.f - h.b2) * g * g);
+  th = th - step * mk / (sqrtf(vk) * rb2 + h.eps);
+}
+
+// The start of a training step, one thread per model: which models train (live = not frozen,
+// dlive = live and density active), the output scaling, and Adam's rates (bias corrections in
+// float64) from the counters t, tG.  With update, the counters then advance; the batch is drawn
+// with *step_now, the step counter's value before.
+__global__ void k_step_begin(const int32_t* frozen, const int32_t* density_active, const apmg_brick* bricks, int32_t* t,
+                             int32_t* tG, uint64_t* step, float lr, float lr_G, float b1, float b2,
+                             const float* lr_scale, int update, int32_t* live, int32_t* dlive, float* scale, float* adam,
+                             float* adam_g, uint64_t* step_now, int nb) {
+  const int b = blockIdx.x * blockDim.x + threadIdx.x;
+  if (b < nb) {
+    const int32_t l = frozen ? (frozen[b] ? 0 : 1) : 1, d = (l && density_active[b]) ? 1 : 0;
+    live[b] = l;
+    dlive[b] = d;
+    scale[b] = bricks[b].vmax - bricks[b].vmin;
+    scale[nb + b] = bricks[b].vmin;
+    const auto rates = [&](int count, float rate, float* out) {
+      const float bc1 = (float)(1.0 - pow((double)b1, (double)(count + 1)));
+      const float bc2 = (float)(1.0 - pow((double)b2, (double)(count + 1)));
+      out[0] = (lr_scale ? rate * lr_scale[b] : rate) / bc1;
+      out[1] = 1.0f / sqrtf(bc2);
+    };
+    rates(t[b], lr, adam + 2 * b);
+    rates(tG[b], lr_G, adam_g + 2 * b);
+    if (update) {
+      t[b] += l;
+      tG[b] += d;
+    }
   }
-  __syncthreads();
-  const float step = sc[0], rb2 = sc[1];
-  const size_t off = (size_t)model * per_model;
-  auto one = [&](float g, float& mk, float& vk, float& th) {
-    mk = __builtin_fmaf(b1, mk, (1.f - b1) * g);
-    vk = __builtin_fmaf(b2, vk, (1.f - b2) * g * g);
-    th = th - step * mk / (sqrtf(vk) * rb2 + eps);
-  };
-  const size_t stride = (size_t)gridDim.x * blockDim.x;
+  if (b == 0) {
+    *step_now = *step;
+    if (update) *step += 1;
+  }
+}
+
+// Adam of up to three arrays of every model in one launch: blocks [0, nbF) update F, [nbF, nbF +
+// nbW) the MLP (both with rates sc, where live), the rest the transforms (float64 gradient,
+// rates sc_g, where dlive).
+struct AdamSet { float *theta, *m, *v; const float* gf; const double* gd; size_t per_model; };
+__global__ void k_adam(AdamSet F, AdamSet W, AdamSet G, int nbF, int nbW, AdamArgs h, const float* sc, const float* sc_g,
+                       const int32_t* live, const int32_t* dlive) {
+  const int model = blockIdx.y;
+  const bool isF = (int)blockIdx.x < nbF, isG = (int)blockIdx.x >= nbF + nbW;
+  const int32_t* active = isG ? dlive : live;
+  if (!active[model]) return;
+  const AdamSet a = isF ? F : isG ? G : W;
+  const unsigned bx = isF ? blockIdx.x : isG ? blockIdx.x - nbF - nbW : blockIdx.x - nbF;
+  const unsigned nbx = isF ? nbF : isG ? gridDim.x - nbF - nbW : nbW;
+  const float* rates = (isG ? sc_g : sc) + 2 * model;
+  const float step = rates[0], rb2 = rates[1];
+  const size_t off = (size_t)model * a.per_model;
+  const size_t stride = (size_t)nbx * blockDim.x;
   size_t i0 = 0;
   // four elements per thread with 16-byte accesses where every array allows it; the same
   // arithmetic per element as the scalar loop that finishes the rest
-  if (gf && ((uintptr_t)(theta + off) | (uintptr_t)(m + off) | (uintptr_t)(v + off) |
-                        (uintptr_t)(gf + off)) % 16 == 0) {
-    const size_t n4 = per_model / 4;
-    for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n4; i += stride) {
+  if (a.gf && ((uintptr_t)(a.theta + off) | (uintptr_t)(a.m + off) | (uintptr_t)(a.v + off) |
+               (uintptr_t)(a.gf + off)) % 16 == 0) {
+    const size_t n4 = a.per_model / 4;
+    for (size_t i = bx * (size_t)blockDim.x + threadIdx.x; i < n4; i += stride) {
       const size_t k = off + 4 * i;
-      const float4 g4 = *(const float4*)(gf + k);
-      float4 m4 = *(float4*)(m + k), v4 = *(float4*)(v + k), t4 = *(float4*)(theta + k);
-      one(g4.x, m4.x, v4.x, t4.x);
-      one(g4.y, m4.y, v4.y, t4.y);
-      one(g4.z, m4.z, v4.z, t4.z);
-      one(g4.w, m4.w, v4.w, t4.w);
-      *(float4*)(m + k) = m4;
-      *(float4*)(v + k) = v4;
-      *(float4*)(theta + k) = t4;
+      const float4 g4 = *(const float4*)(a.gf + k);
+      float4 m4 = *(float4*)(a.m + k), v4 = *(float4*)(a.v + k), t4 = *(float4*)(a.theta + k);
+      adam_one(h, step, rb2, g4.x, m4.x, v4.x, t4.x);
+      adam_one(h, step, rb2, g4.y, m4.y, v4.y, t4.y);
+      adam_one(h, step, rb2, g4.z, m4.z, v4.z, t4.z);
+      adam_one(h, step, rb2, g4.w, m4.w, v4.w, t4.w);
+      *(float4*)(a.m + k) = m4;
+      *(float4*)(a.v + k) = v4;
+      *(float4*)(a.theta + k) = t4;
     }
     i0 = 4 * n4;
   }
-  for (size_t i = i0 + blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < per_model; i += stride) {
+  for (size_t i = i0 + bx * (size_t)blockDim.x + threadIdx.x; i < a.per_model; i += stride) {
     const size_t k = off + i;
-    float mk = m[k], vk = v[k], th = theta[k];
-    one(gf ? gf[k] : (float)gd[k], mk, vk, th);
-    m[k] = mk;
-    v[k] = vk;
-    theta[k] = th;
-  }
-}
-
-// G is stored [M][3][4] float; its gradient is float64 of the same shape.
-// live: models that trained this step; dlive: models whose transforms trained.
-__global__ void k_step_counters(int32_t* t, int32_t* tG, const int32_t* live, const int32_t* dlive, uint64_t* step,
-                                int nb) {
-  const int b = blockIdx.x * blockDim.x + threadIdx.x;
-  if (b < nb) {
-    if (live[b]) t[b] += 1;
-    if (dlive[b]) tG[b] += 1;
-  }
-  if (b == 0) *step += 1;
-}
-
-// live[b] = !frozen[b]; dlive[b] = live[b] && density_active[b].
-__global__ void k_live_masks(const int32_t* frozen, const int32_t* density_active, int32_t* live, int32_t* dlive,
-                             int nb) {
-  const int b = blockIdx.x * blockDim.x + threadIdx.x;
-  if (b < nb) {
-    const int32_t l = frozen ? (frozen[b] ? 0 : 1) : 1;
-    live[b] = l;
-    dlive[b] = (l && density_active[b]) ? 1 : 0;
+    float mk = a.m[k], vk = a.v[k], th = a.theta[k];
+    adam_one(h, step, rb2, a.gf ? a.gf[k] : (float)a.gd[k], mk, vk, th);
+    a.m[k] = mk;
+    a.v[k] = vk;
+    a.theta[k] = th;
   }
 }
 

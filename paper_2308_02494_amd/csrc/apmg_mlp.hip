@@ -493,8 +493,8 @@ __global__ void __launch_bounds__(kBlock) k_backward(TileArgs a) {
   float* sG = smem;
   float* sW3w = sG + 12 * s.M;
   off = (off + 7) & ~(size_t)7;
-  double* sLoss = (double*)(lbase + off);   // [wave]
-  off = (off + 8 * kWavesPerBlock + 15) & ~(size_t)15;
+  double* sLoss = (double*)(lbase + off);   // [wave][2]
+  off = (off + 16 * kWavesPerBlock + 15) & ~(size_t)15;
   char* lw = lbase + off;
   TTy* tiles = (TTy*)(lbase + off + wbytes);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, j = lane & 31, hf = lane >> 5;
@@ -547,7 +547,7 @@ __global__ void __launch_bounds__(kBlock) k_backward(TileArgs a) {
         for (int r = 0; r < 16; ++r) aw1[ib][kb][r] = 0.f;
     }
   }
-  double loss = 0.0;
+  double loss = 0.0, esum = 0.0;
   const int nblk = REG ? KB : s.KHP / 16;
 
   const int64_t ntiles = act ? (a.n + 31) / 32 : 0;
@@ -584,8 +584,10 @@ __global__ void __launch_bounds__(kBlock) k_backward(TileArgs a) {
         const float e = fv - a.v[model * a.v_stride + p];
         df = 2.0f * e / (float)a.n;
         if (lane < 32) {
-          a.err[model * a.err_stride + p] = a.err_abs ? fabsf(e) : e * e;
+          const float h = a.err_abs ? fabsf(e) : e * e;
+          a.err[model * a.err_stride + p] = h;
           loss += (double)e * (double)e;
+          esum += (double)h;
         }
       }
     }
@@ -775,8 +777,8 @@ __global__ void __launch_bounds__(kBlock) k_backward(TileArgs a) {
   }
 
   if (a.want_loss) {
-    const double t = wave_sum(loss);
-    if (lane == 0) sLoss[wave] = t;
+    const double t = wave_sum(loss), u = wave_sum(esum);
+    if (lane == 0) { sLoss[2 * wave] = t; sLoss[2 * wave + 1] = u; }
   }
   __syncthreads();
   for (int i = threadIdx.x; i < H * ncols; i += blockDim.x) part[pl.o_w1 + i] = sW1[i];
@@ -784,7 +786,10 @@ __global__ void __launch_bounds__(kBlock) k_backward(TileArgs a) {
   if (a.do_w3)
     for (int i = threadIdx.x; i < H; i += blockDim.x)
       part[pl.o_w3 + i] = (double)sW3w[i] + (double)sW3w[H + i] + (double)sW3w[2 * H + i] + (double)sW3w[3 * H + i];
-  if (threadIdx.x == 0) part[pl.o_loss] = a.want_loss ? ((sLoss[0] + sLoss[1]) + sLoss[2]) + sLoss[3] : 0.0;
+  if (threadIdx.x < 2) {
+    const double* sl = sLoss + threadIdx.x;
+    part[pl.o_loss + threadIdx.x] = a.want_loss ? ((sl[0] + sl[2]) + sl[4]) + sl[6] : 0.0;
+  }
 }
 
 // Weight-gradient products from stored activations: part[chunk][off + i * cols + j] = sum over
@@ -893,7 +898,7 @@ size_t backward_lds_bytes(const Shape& s, int ncols, int nrows2, bool bf, int kb
   const size_t esz = bf ? 2 : 4;
   size_t b = (size_t)(12 * s.M + kWavesPerBlock * s.H) * 4;
   b = (b + 7) & ~(size_t)7;
-  b += 8 * kWavesPerBlock;
+  b += 16 * kWavesPerBlock;
   b = (b + 15) & ~(size_t)15;
   if (kb) b += swz_sizes(s).total() * esz;
   const size_t tiles = (size_t)kWavesPerBlock * (s.H + 32 + 32 * kb) * ldt * esz;

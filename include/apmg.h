@@ -344,9 +344,10 @@ apmg_status apmg_dd_forward(const apmg_dd_models* models, const apmg_brick_table
  * device runs entirely on `stream`. */
 /* Launch shapes of the training step (fields of 0 take the defaults).
  *   tile_blocks: blocks of the fused forward+adjoint tile kernel per model
- *     (each block = 8 or 4 waves of 32-point tiles); default CUs / nb when nb divides
- *     the device's compute units (one round of blocks), else ceil(2 CUs / nb); at
- *     most 4 times the default and at most the number of 4-tile groups.
+ *     (each block = 8 or 4 waves of 32-point tiles); default the count that fills the
+ *     device's last round of blocks best (one per compute unit for one model); at
+ *     most 4 times CUs / nb (or ceil(2 CUs / nb) when nb does not divide the CUs) and
+ *     at most the number of 4-tile groups.
  *   cell_kernel: grid-gradient gather, 1 = a block of cells per wave or workgroup
  *     (the default; each candidate point is read once and the block's vertex sums
  *     are matrix products), 2 = one thread per cell.  Either also produces L_rec's transform gradient when it is

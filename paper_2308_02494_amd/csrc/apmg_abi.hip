@@ -100,9 +100,9 @@ int tile_blocks(int64_t n) {
   return (int)std::max<int64_t>(1, std::min<int64_t>(b, kMaxTileBlocks));
 }
 
-// Training-step launch shapes (apmg_tuning): tile-kernel blocks per model, default one
-// per CU over all models when nb divides the CUs evenly, else about two per CU, at most 4x the default,
-// 1024, and the number of 4-tile groups; gather batch of 2, 4 or 8 candidates.
+// Training-step launch shapes (apmg_tuning): tile-kernel blocks per model (default
+// step_rule_blocks), at most 4x step_default_blocks, 1024, and the number of 4-tile groups; gather
+// batch of 2, 4 or 8 candidates.
 constexpr int kDefaultCellGroup = 4;   // reported by the autotuner (the block gather takes no such choice)
 // adjoint: 0 = tiled adjoint, waves per block by dtype; 1 = eight waves; 2 = four waves;
 // 3 = the one-wave-per-SIMD register kernel.
@@ -135,18 +135,35 @@ int step_default_blocks(int64_t n, int nb) {
 int step_max_blocks(int64_t n, int nb) {
   return std::max(1, std::min(std::min(4 * step_default_blocks(n, nb), 1024), step_groups(n)));
 }
+// The default: the block count per model for which the adjoint's last round of blocks is fullest.
+// R blocks run at a time (one eight-wave or two four-wave blocks per compute unit); a block takes
+// a round per `waves` tiles and about one more for its weights and partial sums.  One block per CU
+// for one model; 80 models of 2^17 points with four-wave blocks take 19 blocks each (2.97 rounds
+// of blocks: 1.80 ms) where two per CU over all models, 14 each, left a third round almost
+// empty (2.19 rounds: 2.38 ms).
+int step_rule_blocks(int64_t n, int nb, int waves) {
+  const int64_t R = (int64_t)device_cus() * (waves == 4 ? 2 : 1), tiles = (std::max<int64_t>(n, 1) + 31) / 32;
+  const int64_t cap = step_max_blocks(n, nb);
+  int64_t best = cap, best_t = -1;
+  for (int64_t rounds = (nb + R - 1) / R;; ++rounds) {   // the most blocks that fit each number of rounds
+    const int64_t b = std::min(cap, std::max<int64_t>(1, rounds * R / nb));
+    const int64_t t = rounds * (((tiles + b - 1) / b + waves - 1) / waves + 1);
+    if (best_t < 0 || t < best_t) { best_t = t; best = b; }
+    if (b == cap) break;
+  }
+  return (int)best;
+}
 bool resolve_tune(const apmg_tuning* t, int64_t n, int nb, bool bf, Tune* out) {
-  out->tile_blocks = step_default_blocks(n, nb);
   out->cell_unroll = 4;
   out->cell_kernel = 0;
   out->adjoint = 0;
-  // four-wave tiled adjoint blocks run two per compute unit
-  const auto two_per_cu = [&]() {
-    if (out->adjoint < 3 && adjoint_waves(out->adjoint, bf) == 4)
-      out->tile_blocks = std::min(2 * out->tile_blocks, step_max_blocks(n, nb));
+  // (the one-wave-per-SIMD kernel, adjoint 3, also runs one four-wave block per compute unit)
+  const auto rule = [&]() {
+    const int waves = out->adjoint < 3 ? adjoint_waves(out->adjoint, bf) : 8;
+    out->tile_blocks = step_rule_blocks(n, nb, waves);
   };
   if (!t) {
-    two_per_cu();
+    rule();
     return true;
   }
   if (t->tile_blocks < 0 || t->tile_blocks > step_max_blocks(n, nb)) return false;
@@ -159,7 +176,7 @@ bool resolve_tune(const apmg_tuning* t, int64_t n, int nb, bool bf, Tune* out) {
   if (t->cell_kernel > 0) out->cell_kernel = t->cell_kernel - 1;
   if (t->adjoint_kernel < 0 || t->adjoint_kernel > 3) return false;
   out->adjoint = t->adjoint_kernel;
-  if (t->tile_blocks == 0) two_per_cu();
+  if (t->tile_blocks == 0) rule();
   return true;
 }
 
@@ -1230,6 +1247,10 @@ extern "C" apmg_status apmg_autotune_batched_step(const apmg_batch* b, void* ws,
   std::vector<int> blocks;
   for (int c : {d / 2, d, 2 * d, 4 * d}) {
     const int v = std::max(1, std::min(c, mx));
+    if (std::find(blocks.begin(), blocks.end(), v) == blocks.end()) blocks.push_back(v);
+  }
+  for (int waves : {4, 8}) {
+    const int v = step_rule_blocks(b->n, b->nb, waves);
     if (std::find(blocks.begin(), blocks.end(), v) == blocks.end()) blocks.push_back(v);
   }
   hipEvent_t e0, e1;

@@ -1313,7 +1313,7 @@ extern "C" apmg_status apmg_train_control(const apmg_control* c, const double* l
 // ---------------------------------------------------------------- domain-decomposition inference
 struct DdWs {
   uint32_t *k0, *v0, *k1, *v1, *hist, *rowtot, *dbase, *seg;
-  float *lpts, *fs, *w3s, *scale;
+  float *w3s, *scale;
   void* swz;
   OpsWs ops;
 };
@@ -1330,8 +1330,6 @@ size_t dd_ws(const Shape& s, const apmg_model* shape, int nb, int64_t n, void* w
   w.rowtot = cv.take<uint32_t>(kRadixDigits);
   w.dbase = cv.take<uint32_t>(kRadixDigits);
   w.seg = cv.take<uint32_t>((size_t)nb + 1);
-  w.lpts = cv.take<float>((size_t)3 * nn);
-  w.fs = cv.take<float>(nn);
   w.swz = cv.take<char>((size_t)nb * swz_sizes(s).total() * (bf ? 2 : 4));
   w.w3s = cv.take<float>((size_t)nb * s.H);
   w.scale = cv.take<float>((size_t)2 * nb);
@@ -1362,11 +1360,15 @@ extern "C" apmg_status apmg_dd_forward(const apmg_dd_models* d, const apmg_brick
   if (launch_ops(s, nb, d->G, g_rows(&d->shape), d->F, gf16, paper_grids(&d->shape), w.ops, gf16, st, &Gc, &Fc) !=
       hipSuccess)
     return APMG_EHIP;
-  // brick ids, then a stable radix sort of the points by brick
-  hipLaunchKernelGGL(k_dd_keys, dim3(grid1(n)), dim3(256), 0, st, *t, pts, ld, n, w.k0, w.v0);
+  // brick ids (and, from kFwdSortMin points on, bins inside the bricks: as many bits as two radix
+  // passes leave), then a stable radix sort of the points by them
+  const int kb = key_bits(nb), sb = n >= kFwdSortMin ? std::max(0, kBinBits - kb) : 0;
+  const int3 bits = sb >= 3 ? make_int3((sb + 2) / 3, (sb + 1) / 3, sb / 3) : make_int3(0, 0, 0);
+  const int sbits = bits.x + bits.y + bits.z;
+  hipLaunchKernelGGL(k_dd_keys, dim3(grid1(n)), dim3(256), 0, st, *t, d->bricks, bits, pts, ld, n, w.k0, w.v0);
   const int nt = sort_tiles(n);
   uint32_t *ki = w.k0, *vi = w.v0, *ko = w.k1, *vo = w.v1;
-  for (int shift = 0; shift < key_bits(nb); shift += kRadixBits) {
+  for (int shift = 0; shift < kb + sbits; shift += kRadixBits) {
     hipLaunchKernelGGL(k_radix_hist, dim3(nt, 1), dim3(kSortThreads), 0, st, ki, n, shift, w.hist, nt);
     hipLaunchKernelGGL(k_radix_rowscan, dim3(kRadixDigits, 1), dim3(256), 0, st, w.hist, nt, w.rowtot);
     hipLaunchKernelGGL(k_radix_digitscan, dim3(1), dim3(256), 0, st, w.rowtot, w.dbase);
@@ -1374,8 +1376,7 @@ extern "C" apmg_status apmg_dd_forward(const apmg_dd_models* d, const apmg_brick
     std::swap(ki, ko);
     std::swap(vi, vo);
   }
-  hipLaunchKernelGGL(k_seg_starts, dim3(grid1((int64_t)nb + 1)), dim3(256), 0, st, ki, n, nb, w.seg);
-  hipLaunchKernelGGL(k_dd_local, dim3(grid1(n)), dim3(256), 0, st, pts, ld, n, ki, vi, d->bricks, *t, w.lpts);
+  hipLaunchKernelGGL(k_seg_starts, dim3(grid1((int64_t)nb + 1)), dim3(256), 0, st, ki, n, sbits, nb, w.seg);
   // every brick's model over its segment, one launch
   hipError_t e = launch_swizzle(s, bf, d->W, d->W + (size_t)s.H * s.MC, d->W + (size_t)s.H * s.MC + (size_t)s.H * s.H,
                                 nW, w.swz, swz_sizes(s).total(), w.w3s, nb, st);
@@ -1388,15 +1389,17 @@ extern "C" apmg_status apmg_dd_forward(const apmg_dd_models* d, const apmg_brick
   a.F = Fc; a.F_stride = nF;
   a.swz = w.swz; a.swz_stride = swz_sizes(s).total(); a.w3s = w.w3s;
   a.bscale = w.scale; a.boff = w.scale + nb;
-  a.pts = w.lpts; a.ld = n; a.pts_stride = 0; a.n = n;
+  a.pts = pts; a.ld = ld; a.pts_stride = 0; a.n = n;
   a.seg = w.seg;
-  a.f = w.fs;
+  a.perm = vi;
+  a.f = f;
+  a.bricks = d->bricks;
+  for (int k = 0; k < 3; ++k) a.vol_h[k] = 0.5f * (float)(t->vol[k] - 1);
   // blocks per brick: twice the even share of the tiles, at least one
   const int64_t per = (n + nb - 1) / nb;
   const int nblk = std::max(1, std::min(2 * tile_blocks(per), kMaxTileBlocks));
   e = launch_tile(false, 0, a, gf16, bf, dim3(nblk, nb), forward_lds_bytes(s, bf), st);
   if (e != hipSuccess) return APMG_EHIP;
-  hipLaunchKernelGGL(k_dd_scatter, dim3(grid1(n)), dim3(256), 0, st, w.fs, vi, n, f);
   return hip_status(hipGetLastError());
 }
 

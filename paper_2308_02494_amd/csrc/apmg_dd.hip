@@ -1,9 +1,10 @@
 // Global-query inference over a domain decomposition (Sec. 5.3).  Each global
-// point is hashed to its brick, mapped into that brick model's local frame, and
-// the points are grouped by brick (a stable radix sort on the brick id) so that
-// one launch of the forward tile kernel evaluates every brick's points with its
-// own model (block row = brick, the points a contiguous segment); the outputs
-// are scattered back to the input order.
+// point is hashed to its brick, and the points are ordered by brick and, inside a
+// brick, by spatial bin (a stable radix sort), so that one launch of the forward
+// tile kernel evaluates every brick's points with its own model (block row =
+// brick, a contiguous segment of the order): it reads each point and writes its
+// output through the order's permutation and maps the point into its brick's
+// local frame itself.
 
 namespace apmg {
 
@@ -22,50 +23,40 @@ __device__ inline int brick_of(const apmg_brick_table& t, const float p[3]) {
   return idx[0] + t.dims[0] * (idx[1] + t.dims[1] * idx[2]);
 }
 
-// keys[i] = brick of point i, vals[i] = i.
-__global__ void k_dd_keys(apmg_brick_table t, const float* pts, int64_t ld, int64_t n, uint32_t* keys,
-                          uint32_t* vals) {
+// keys[i] = brick of point i, followed by bits of its bin inside the brick (x fastest: bits[0]
+// of x, bits[1] of y, bits[2] of z; none for a small batch), vals[i] = i.  The bin only orders the
+// work -- a tile's points then share grid cells in cache -- so it may round as it likes.
+__global__ void k_dd_keys(apmg_brick_table t, const apmg_brick* bricks, int3 bits, const float* pts, int64_t ld,
+                          int64_t n, uint32_t* keys, uint32_t* vals) {
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
     const float p[3] = {pts[i], pts[ld + i], pts[2 * ld + i]};
-    keys[i] = (uint32_t)brick_of(t, p);
+    uint32_t key = (uint32_t)brick_of(t, p);
+    const int nbits[3] = {bits.x, bits.y, bits.z};
+    if (nbits[0] > 0) {
+      const apmg_brick br = bricks[key];
+#pragma unroll
+      for (int d = 2; d >= 0; --d) {
+        const float h = 0.5f * (float)(t.vol[d] - 1), e0 = (float)br.e0[d], span = (float)(br.e1[d] - br.e0[d]);
+        const float top = (float)((1 << nbits[d]) - 1);
+        const float b = (__builtin_fmaf(p[d], h, h) - e0) * __frcp_rn(span + 1.f) * (top + 1.f);
+        key = (key << nbits[d]) | (uint32_t)fminf(fmaxf(b, 0.f), top);   // (NaN -> 0)
+      }
+    }
+    keys[i] = key;
     vals[i] = (uint32_t)i;
   }
 }
 
-// Sorted point j (input point perm[j], brick keys[j]) in its brick model's local frame,
-// the inverse of the training map u = e0 + (l + 1)/2 (e1 - e0):
-//   l = fma(u - e0, 2 / (e1 - e0), -1), u = fma(p, h, h), each operation rounded once.
-__global__ void k_dd_local(const float* pts, int64_t ld, int64_t n, const uint32_t* keys, const uint32_t* perm,
-                           const apmg_brick* bricks, apmg_brick_table t, float* out) {
-  for (int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; j < n; j += (int64_t)gridDim.x * blockDim.x) {
-    const uint32_t i = perm[j];
-    const apmg_brick br = bricks[keys[j]];
-    for (int d = 0; d < 3; ++d) {
-      const float h = 0.5f * (float)(t.vol[d] - 1);
-      const float u = __builtin_fmaf(pts[d * ld + i], h, h);
-      const int span = br.e1[d] - br.e0[d];
-      const float sc = span > 0 ? __fdiv_rn(2.0f, (float)span) : 0.0f;
-      out[d * n + j] = __builtin_fmaf(u - (float)br.e0[d], sc, -1.0f);
-    }
-  }
-}
-
-// start[b] = first sorted position with key >= b, b in [0, nseg]; binary search.
-__global__ void k_seg_starts(const uint32_t* keys, int64_t n, int nseg, uint32_t* start) {
+// start[b] = first position whose key >> shift is >= b, b in [0, nseg]; binary search.
+__global__ void k_seg_starts(const uint32_t* keys, int64_t n, int shift, int nseg, uint32_t* start) {
   for (int b = blockIdx.x * blockDim.x + threadIdx.x; b <= nseg; b += gridDim.x * blockDim.x) {
     int64_t lo = 0, hi = n;
     while (lo < hi) {
       const int64_t mid = (lo + hi) >> 1;
-      if (keys[mid] < (uint32_t)b) lo = mid + 1; else hi = mid;
+      if ((keys[mid] >> shift) < (uint32_t)b) lo = mid + 1; else hi = mid;
     }
     start[b] = (uint32_t)lo;
   }
-}
-
-// f[perm[j]] = fs[j].
-__global__ void k_dd_scatter(const float* fs, const uint32_t* perm, int64_t n, float* f) {
-  for (int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; j < n; j += (int64_t)gridDim.x * blockDim.x)
-    f[perm[j]] = fs[j];
 }
 
 }  // namespace apmg

@@ -63,9 +63,12 @@ struct TileArgs {
   const float* bscale;                    // per model (vmax - vmin) or NULL
   const float* boff;                      // per model vmin or NULL
   const float* pts; int64_t ld; size_t pts_stride; int64_t n;
-  const uint32_t* seg;                    // forward only: [models + 1] segment starts in one shared array, or NULL
-  const uint32_t* perm;                   // forward only, model 0, no segments: the tile's point p is input and
-                                          // output position perm[p] (a spatial order of the points), or NULL
+  // forward only.  perm: position p of the order is point perm[p], input and output (NULL: the
+  // points as given).  Domain decomposition (bricks set): perm orders global points by model,
+  // segment starts seg[models + 1]; vol_h = (n_d - 1) / 2 of the volume's axes
+  const uint32_t* perm;
+  const uint32_t* seg;
+  const apmg_brick* bricks; float vol_h[3];
   // forward
   float* f;
   // adjoint

@@ -375,7 +375,10 @@ __host__ __device__ inline size_t fwd_weight_bytes(const Shape& s, bool bf) {
 // CU's LDS (then eight waves share them, two per SIMD, instead of one; measured on the 64-grid
 // 256-128-128-1 BF16 model: 8.06 -> 6.14 ms per 16.6 M-point frame; twelve waves, three per
 // SIMD, 6.26 ms).
-template <int C, int H, bool GF16, bool BF, bool WL, int ENC = kEncDense, int NWF = kWavesPerBlock>
+// DD: global points of a domain decomposition, in the order of k_dd_keys (perm), a segment per
+// model, mapped into each model's brick here: one pass less over the points than mapping them
+// into an array of their own first, and none to scatter the outputs back.
+template <int C, int H, bool GF16, bool BF, bool WL, int ENC = kEncDense, int NWF = kWavesPerBlock, bool DD = false>
 __global__ void __launch_bounds__(NWF * kWave) k_forward(TileArgs a) {
   extern __shared__ float smem[];
   // logical block: models in order, each model's blocks over contiguous runs of its
@@ -401,12 +404,24 @@ __global__ void __launch_bounds__(NWF * kWave) k_forward(TileArgs a) {
   const float* w3s = a.w3s + (size_t)model * H;
   const float vs = a.bscale ? a.bscale[model] : a.vscale;
   const float vo = a.boff ? a.boff[model] : a.voff;
-  // points of this model: [model * pts_stride, + n) of its own arrays, or, with segments,
-  // [seg[model], seg[model + 1]) of one shared array (outputs at the same positions)
-  const int64_t base = a.seg ? (int64_t)a.seg[model] : 0;
-  const int64_t cnt = a.seg ? (int64_t)a.seg[model + 1] - base : a.n;
-  const float* P = a.seg ? a.pts + base : a.pts + model * a.pts_stride;
-  float* fo = a.seg ? a.f + base : a.f + (size_t)model * a.n;
+  // points of this model: [model * pts_stride, + n) of its own arrays, or (DD) the positions
+  // [seg[model], seg[model + 1]) of one order of global points
+  const int64_t base = DD ? (int64_t)a.seg[model] : 0;
+  const int64_t cnt = DD ? (int64_t)a.seg[model + 1] - base : a.n;
+  const float* P = DD ? a.pts : a.pts + model * a.pts_stride;
+  float* fo = DD ? a.f : a.f + (size_t)model * a.n;
+  const uint32_t* perm = DD ? a.perm + base : a.perm;
+  // DD: the model's brick frame (l = fma(u - e0, 2 / (e1 - e0), -1))
+  float e0[3], sc[3];
+  if constexpr (DD) {
+    const apmg_brick br = a.bricks[model];
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+      const int span = br.e1[d] - br.e0[d];
+      e0[d] = (float)br.e0[d];
+      sc[d] = span > 0 ? __fdiv_rn(2.0f, (float)span) : 0.0f;
+    }
+  }
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, j = lane & 31;
   const int64_t ntiles = (cnt + 31) / 32;
   const int64_t per = (ntiles + gridDim.x - 1) / gridDim.x;
@@ -415,10 +430,15 @@ __global__ void __launch_bounds__(NWF * kWave) k_forward(TileArgs a) {
     const int64_t p = tile * 32 + j;
     const bool valid = p < cnt;
     // the point at the tile's position p, or, in a spatial order, at position perm[p]
-    const int64_t q = (a.perm && valid) ? (int64_t)a.perm[p] : p;
+    const int64_t q = (perm && valid) ? (int64_t)perm[p] : p;
     float x = 0.f, y = 0.f, z = 0.f, tq = 0.f;
     if (valid) { x = P[q]; y = P[a.ld + q]; z = P[2 * a.ld + q]; }
     if constexpr (ENC == kEncTime) tq = valid ? a.tau[q] : 0.f;
+    if constexpr (DD) {
+      x = __builtin_fmaf(__builtin_fmaf(x, a.vol_h[0], a.vol_h[0]) - e0[0], sc[0], -1.0f);
+      y = __builtin_fmaf(__builtin_fmaf(y, a.vol_h[1], a.vol_h[1]) - e0[1], sc[1], -1.0f);
+      z = __builtin_fmaf(__builtin_fmaf(z, a.vol_h[2], a.vol_h[2]) - e0[2], sc[2], -1.0f);
+    }
     f32x16 z1[H / 32], z2[H / 32];
     float m;
     tile_fwd<C, H, GF16, BF, false, ENC>(s, sG, F, swz, w3s, x, y, z, valid, lane, z1, z2, m, nullptr, nullptr,
@@ -871,7 +891,14 @@ constexpr size_t kFwdWideLds = 80 * 1024;
 template <int C, int H, bool GF16, bool BF>
 hipError_t launch_tile_kernels(bool backward, int kb, const TileArgs& a, dim3 grid, size_t shmem,
                                hipStream_t st) {
-  if (!backward) {
+  if (!backward && a.bricks) {
+    if (fwd_weight_bytes(a.s, BF) > kFwdWeightLdsMax)
+      hipLaunchKernelGGL((k_forward<C, H, GF16, BF, false, kEncDense, 4, true>), grid, dim3(kBlock), shmem, st, a);
+    else if (shmem > kFwdWideLds)
+      hipLaunchKernelGGL((k_forward<C, H, GF16, BF, true, kEncDense, 8, true>), grid, dim3(8 * kWave), shmem, st, a);
+    else
+      hipLaunchKernelGGL((k_forward<C, H, GF16, BF, true, kEncDense, 4, true>), grid, dim3(kBlock), shmem, st, a);
+  } else if (!backward) {
     if (fwd_weight_bytes(a.s, BF) > kFwdWeightLdsMax)
       hipLaunchKernelGGL((k_forward<C, H, GF16, BF, false>), grid, dim3(kBlock), shmem, st, a);
     else if (shmem > kFwdWideLds)

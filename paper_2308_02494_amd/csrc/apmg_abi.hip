@@ -744,6 +744,16 @@ apmg_status forward_impl(const apmg_model* m, const float* pts, int64_t ld, int6
   const bool bf = m->mlp_dtype == APMG_BF16, gf16 = m->grid_dtype == APMG_F16;
   if (ws_bytes < fwd_ws(s, m, n, nullptr, nullptr, sortable) || !ws) return APMG_EWORKSPACE;
   if (n == 0) return APMG_OK;
+  if (forward_small_applies(s, n)) {
+    SmallArgs a;
+    a.s = s;
+    a.G = m->G; a.grows = g_rows(m);
+    a.F = m->F;
+    a.W1 = m->W[0]; a.W2 = m->W[1]; a.W3 = m->W[2];
+    a.vscale = m->vmax - m->vmin; a.voff = m->vmin;
+    a.pts = pts; a.ld = ld; a.n = n; a.f = f;
+    return launch_forward_small(a, gf16, bf, !paper_grids(m), st) == hipSuccess ? APMG_OK : APMG_EHIP;
+  }
   FwdWs w;
   fwd_ws(s, m, n, ws, &w, sortable);
   const float* Gc;

@@ -447,6 +447,198 @@ __global__ void __launch_bounds__(NWF * kWave) k_forward(TileArgs a) {
   }
 }
 
+// ------------------------------------------------------------------ small batches
+// One launch for a small batch (a probe of a few points, a few thousand samples): no gather copy
+// of the grids, no swizzle kernel, no sort.  Corner values are read where the caller keeps them
+// (paper order: one x-adjacent pair per channel; LAST: channel-last, as k_forward), the transforms
+// from their 3 or 4 rows, and each block lays the weights out in LDS in operand order itself,
+// 16 bytes of a row per lane.  The arithmetic is that of k_forward: the same bits.
+// Bound by latency, and by the L1's one cache line a cycle (scattered points: every lane of every
+// load its own line), so the points spread over as many compute units as there are: a block takes
+// one tile of 32 points, its four waves a quarter of the grids each (features through LDS), and
+// its first two waves one 32-row block of every layer each.  A call on 257 points, 16 grids at
+// 16^3 x 2: 8.8 us, the host's share, in place of 16.2 us in three kernels (eight tiles a block:
+// 25 us); 4000 points, 32 grids at 32^3 x 2: 37.6 -> 20.0 us.
+struct SmallArgs {
+  Shape s;
+  const float* G; int grows;
+  const void* F;
+  const float *W1, *W2, *W3;
+  float vscale, voff;
+  const float* pts; int64_t ld; int64_t n;
+  float* f;
+};
+constexpr int kSmallWaves = 4;
+
+// Four consecutive values of a weight row, from k (zeros from kend on); vec: k, kend and the row
+// start are multiples of 4 values in 16-byte aligned memory.
+__device__ inline f32x4 weight_quad(const float* row, int k, int kend, bool vec) {
+  if (vec) return k < kend ? *(const f32x4*)(row + k) : f32x4{0.f, 0.f, 0.f, 0.f};
+  f32x4 v;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) v[e] = k + e < kend ? row[k + e] : 0.f;
+  return v;
+}
+
+// The 8 corner values of grid g's cell i0 from paper-order grids [M][C][R^3].
+template <int C, bool F16>
+__device__ inline void gather_cell_paper(const void* F, int g, int R, const int i0[3], float val[8][C]) {
+  typedef uint32_t u32a2 __attribute__((aligned(2)));
+  const uint32_t R2 = (uint32_t)R * R, R3 = R2 * R;
+  const uint32_t base = (uint32_t)g * C * R3 + ((uint32_t)i0[2] * R + i0[1]) * R + i0[0];
+#pragma unroll
+  for (int q2 = 0; q2 < 4; ++q2)
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+      const uint32_t o = base + c * R3 + (q2 & 1) * R + (q2 >> 1) * R2;
+      if constexpr (F16) {
+        const uint32_t w = *(const u32a2*)((const uint16_t*)F + o);
+        const float2 f = __half22float2(*(const __half2*)&w);
+        val[2 * q2][c] = f.x; val[2 * q2 + 1][c] = f.y;
+      } else {
+        const f32x2a4 f = *(const f32x2a4*)((const float*)F + o);
+        val[2 * q2][c] = f.x; val[2 * q2 + 1][c] = f.y;
+      }
+    }
+}
+
+template <int C, int H, bool GF16, bool BF, bool LAST>
+__global__ void __launch_bounds__(kSmallWaves * kWave) k_forward_small(SmallArgs a) {
+  static_assert(H == 64, "two row blocks, one per wave");
+  extern __shared__ float smem[];
+  constexpr int NB = H / 32;
+  const Shape s = a.s;
+  float* sG = smem;                       // [12 M]
+  float* w3s = sG + 12 * s.M;             // [hf][H/2]
+  float* sF = w3s + H;                    // features [KHP][64 lanes], then relu(z1) and relu(z2) [H/2][64]
+  char* lw = (char*)smem + (((12 * s.M + H + 64 * max(s.KHP, H / 2)) * 4 + 15) & ~15);
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), j = lane & 31,
+            hf = lane >> 5;
+  const int64_t p = (int64_t)blockIdx.x * 32 + j;
+  const bool valid = p < a.n;
+  float x = 0.f, y = 0.f, z = 0.f;
+  if (valid) { x = a.pts[p]; y = a.pts[a.ld + p]; z = a.pts[2 * a.ld + p]; }
+  for (int i = threadIdx.x; i < 12 * s.M; i += blockDim.x) sG[i] = a.G[(i / 12) * 4 * a.grows + i % 12];
+  for (int i = threadIdx.x; i < H; i += blockDim.x)
+    w3s[i] = a.W3[32 * ((i % (H / 2)) >> 4) + acc_row(i & 15, i / (H / 2))];
+  // first layer: lane l of operand (b, .) holds row 32 b + l % 32, features of half l / 32; second
+  // layer: columns in the accumulator's row order
+  const bool vec1 = ((uintptr_t)a.W1 % 16 == 0) && s.MC % 4 == 0 && s.KH % 4 == 0, vec2 = (uintptr_t)a.W2 % 16 == 0;
+  const int kbeg = hf * s.KH, kend = min(s.KH, s.MC - kbeg);     // this half's features [0, kend)
+  constexpr int Q = BF ? 2 : 1;           // quads per operand word
+  const int S1 = s.KHP / (4 * Q), S2 = H / (8 * Q);              // quads (or pairs) per block of each layer
+  for (int o = wave; o < NB * (S1 + S2); o += kSmallWaves) {
+    const bool first = o < NB * S1;
+    const int oo = first ? o : o - NB * S1, S = first ? S1 : S2, b = oo / S, q = oo % S;
+    f32x4 v[Q];
+#pragma unroll
+    for (int h = 0; h < Q; ++h) {
+      const int qq = Q * q + h;
+      if (first) v[h] = weight_quad(a.W1 + (size_t)(32 * b + j) * s.MC + kbeg, 4 * qq, kend, vec1);
+      else v[h] = weight_quad(a.W2 + (size_t)(32 * b + j) * H, 8 * qq + 4 * hf, H, vec2);
+    }
+    if constexpr (BF) {
+      float w8[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) w8[e] = v[e >> 2][e & 3];
+      ((bf16x8*)lw)[(first ? 0 : NB * S1 * 64) + (b * S + q) * 64 + lane] = bf16_pack8(w8);
+    } else {
+      float* dst = (float*)lw + (first ? 0 : NB * S1 * 4 * 64) + (size_t)(b * S + q) * 4 * 64 + lane;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) dst[64 * e] = v[0][e];
+    }
+  }
+  __syncthreads();
+  // grids wave, wave + 4, ... of each half (past the last grid: zero features up to KHP)
+  const float hR = 0.5f * (float)(s.R - 1);
+  auto tap = [&](int gi, GridTap<C>& t) {
+    const int g = hf * s.Mh + gi;
+    const bool gok = valid && gi < s.Mh && g < s.M;
+    const int gg = gok ? g : 0;
+    float l[3];
+    local_coords(sG + 12 * gg, x, y, z, l);
+    int i0[3];
+    t.in = cell_of(l, hR, s.R, i0, t.w) && gok;
+#pragma unroll
+    for (int d = 0; d < 3; ++d) i0[d] = t.in ? i0[d] : 0;
+    if constexpr (LAST) gather_cell<C, GF16>(a.F, gg, s.R, i0, t.val);
+    else gather_cell_paper<C, GF16>(a.F, gg, s.R, i0, t.val);
+  };
+  auto put = [&](int gi, const GridTap<C>& t) {
+    float e[C];
+    grid_tap_value<C>(t, e);
+#pragma unroll
+    for (int c = 0; c < C; ++c) sF[(gi * C + c) * 64 + lane] = e[c];
+  };
+  const int total = s.KHP / C;
+  GridTap<C> t0, t1;
+  tap(wave, t0);
+  for (int gi = wave; gi < total; gi += 2 * kSmallWaves) {
+    tap(gi + kSmallWaves, t1);
+    sched_barrier();
+    put(gi, t0);
+    tap(gi + 2 * kSmallWaves, t0);
+    sched_barrier();
+    if (gi + kSmallWaves < total) put(gi + kSmallWaves, t1);
+  }
+  __syncthreads();
+  f32x16 zb;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) zb[r] = 0.f;
+  if (wave < NB) {
+    const int b = wave;
+    if constexpr (!BF) {
+      const float* W1 = (const float*)lw + (size_t)b * s.KHP * 64 + lane;
+      for (int k = 0; k < s.KH; ++k) zb = mma_f32(W1[k * 64], sF[k * 64 + lane], zb);
+    } else {
+      for (int st = 0; st < S1; ++st) {
+        float Bv[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) Bv[e] = sF[(8 * st + e) * 64 + lane];
+        zb = mma_bf16(((const bf16x8*)lw)[(b * S1 + st) * 64 + lane], bf16_pack8(Bv), zb);
+      }
+    }
+  }
+  __syncthreads();
+  if (wave < NB)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) sF[(16 * wave + r) * 64 + lane] = fmaxf(zb[r], 0.f);
+  __syncthreads();
+  if (wave < NB) {
+    const int b = wave;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) zb[r] = 0.f;
+    if constexpr (!BF) {
+      const float* W2 = (const float*)lw + (size_t)NB * s.KHP * 64 + (size_t)b * (H / 2) * 64 + lane;
+#pragma unroll 8
+      for (int st = 0; st < H / 2; ++st) zb = mma_f32(W2[st * 64], sF[st * 64 + lane], zb);
+    } else {
+      const bf16x8* W2 = (const bf16x8*)lw + NB * S1 * 64;
+#pragma unroll
+      for (int st = 0; st < H / 16; ++st) {
+        float Bv[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) Bv[e] = sF[(8 * st + e) * 64 + lane];
+        zb = mma_bf16(W2[((size_t)b * (H / 16) + st) * 64 + lane], bf16_pack8(Bv), zb);
+      }
+    }
+  }
+  __syncthreads();
+  // the output layer in k_forward's order: row block 0, then 1
+  if (wave == 1)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) sF[r * 64 + lane] = fmaxf(zb[r], 0.f);
+  __syncthreads();
+  if (wave != 0) return;
+  float acc = 0.f;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) acc = __builtin_fmaf(w3s[hf * (H / 2) + r], fmaxf(zb[r], 0.f), acc);
+#pragma unroll
+  for (int r = 0; r < 16; ++r) acc = __builtin_fmaf(w3s[hf * (H / 2) + 16 + r], sF[r * 64 + lane], acc);
+  const float m = acc + __shfl_xor(acc, 32, 64);
+  if (valid && lane < 32) a.f[p] = __builtin_fmaf(m, a.vscale, a.voff);
+}
+
 // ------------------------------------------------------------------ adjoint
 __device__ inline void wave_lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -960,6 +1152,40 @@ hipError_t launch_tile(bool backward, int kb, const TileArgs& a, bool grid_f16, 
   APMG_DISPATCH(2, 128)
   APMG_DISPATCH(4, 128)
 #undef APMG_DISPATCH
+  return hipErrorInvalidValue;
+}
+
+// Batches of up to kFwdSmallMax points whose forward weights are at most kFwdSmallWeights elements
+// (every block lays them out again) take the one-launch kernel.  Its blocks' own cost shows once
+// they queue for compute units: 16,000 points of 32 grids at 32^3 x 2 take 31 us against 36 us
+// through k_forward, 32,000 take 55 against 35.
+constexpr int64_t kFwdSmallMax = (int64_t)1 << 14;
+constexpr size_t kFwdSmallWeights = 16384;
+bool forward_small_applies(const Shape& s, int64_t n) {
+  const SwzSizes z = swz_sizes(s);
+  return n <= kFwdSmallMax && z.w1 + z.w2 <= kFwdSmallWeights;
+}
+hipError_t launch_forward_small(const SmallArgs& a, bool grid_f16, bool bf, bool last, hipStream_t st) {
+  const Shape& s = a.s;
+  const dim3 grid((unsigned)((a.n + 31) / 32)), blk(kSmallWaves * kWave);
+  const size_t shmem = (((size_t)(12 * s.M + s.H + 64 * std::max(s.KHP, s.H / 2)) * 4 + 15) & ~(size_t)15) +
+                       fwd_weight_bytes(s, bf);
+#define APMG_SMALL_L(CC, G16, B16)                                                                             \
+  {                                                                                                            \
+    if (last) hipLaunchKernelGGL((k_forward_small<CC, 64, G16, B16, true>), grid, blk, shmem, st, a);            \
+    else hipLaunchKernelGGL((k_forward_small<CC, 64, G16, B16, false>), grid, blk, shmem, st, a);                \
+  }
+#define APMG_SMALL(CC)                                                                                         \
+  if (s.C == CC && s.H == 64) {                                                                                \
+    if (!grid_f16 && !bf) APMG_SMALL_L(CC, false, false)                                                        \
+    else if (!grid_f16) APMG_SMALL_L(CC, false, true)                                                           \
+    else if (!bf) APMG_SMALL_L(CC, true, false)                                                                 \
+    else APMG_SMALL_L(CC, true, true)                                                                           \
+    return hipGetLastError();                                                                                  \
+  }
+  APMG_SMALL(1) APMG_SMALL(2) APMG_SMALL(4)
+#undef APMG_SMALL
+#undef APMG_SMALL_L
   return hipErrorInvalidValue;
 }
 

@@ -261,8 +261,11 @@ hipError_t launch_ops(const Shape& s, int nb, const float* G, int grows, const v
 // ---------------------------------------------------------------- workspace layouts
 // Spatial sort of nb models' points: keys/values ping-pong, digit histograms, bin starts,
 // sorted points and an optional permuted per-point array.
-struct SortWs { uint32_t *k0, *v0, *k1, *v1, *hist, *rowtot, *dbase, *start; float *spts, *sf; float4* spts4; };
-inline int sort_tiles(int64_t n) { return (int)std::max<int64_t>(1, (n + kSortTile - 1) / kSortTile); }
+struct SortWs { uint32_t *k0, *v0, *k1, *v1, *hist, *rowtot, *start; float *spts, *sf; float4* spts4; };
+inline int sort_tiles(int64_t n, int nb) {
+  const int64_t tile = kSortThreads * (small_sort(n, nb) ? kSmallRounds : kLargeRounds);
+  return (int)std::max<int64_t>(1, (n + tile - 1) / tile);
+}
 void take_sort(Carver& cv, int64_t n, int nb, bool with_f, SortWs* o, bool keys_only = false);
 
 // Forward operands; from kFwdSortMin points on, the points are first sorted into spatial
@@ -293,9 +296,8 @@ void take_sort(Carver& cv, int64_t n, int nb, bool with_f, SortWs* o, bool keys_
   o->v0 = cv.take<uint32_t>((size_t)nb * nn);
   o->k1 = cv.take<uint32_t>((size_t)nb * nn);
   o->v1 = cv.take<uint32_t>((size_t)nb * nn);
-  o->hist = cv.take<uint32_t>((size_t)nb * kRadixDigits * sort_tiles(n));
+  o->hist = cv.take<uint32_t>((size_t)nb * kRadixDigits * sort_tiles(n, nb));
   o->rowtot = cv.take<uint32_t>((size_t)nb * kRadixDigits);
-  o->dbase = cv.take<uint32_t>((size_t)nb * kRadixDigits);
   if (keys_only) {
     o->start = nullptr; o->spts = nullptr; o->sf = nullptr; o->spts4 = nullptr;
     return;
@@ -306,41 +308,48 @@ void take_sort(Carver& cv, int64_t n, int nb, bool with_f, SortWs* o, bool keys_
   o->spts4 = cv.take<float4>((size_t)nb * nn);
 }
 
-// LSD radix passes over the keys/values in k0/v0; after an even number of passes the sorted
-// keys/values are back in k0/v0.
-void radix_passes(int64_t n, int nb, int nt, const SortWs& w, hipStream_t st) {
-  uint32_t *ki = w.k0, *vi = w.v0, *ko = w.k1, *vo = w.v1;
-  static_assert((kBinBits + kRadixBits - 1) / kRadixBits % 2 == 0, "an even number of passes");
-  for (int shift = 0; shift < kBinBits; shift += kRadixBits) {
-    hipLaunchKernelGGL(k_radix_hist, dim3(nt, nb), dim3(kSortThreads), 0, st, ki, n, shift, w.hist, nt);
-    hipLaunchKernelGGL(k_radix_rowscan, dim3(kRadixDigits, nb), dim3(256), 0, st, w.hist, nt, w.rowtot);
-    hipLaunchKernelGGL(k_radix_digitscan, dim3(nb), dim3(256), 0, st, w.rowtot, w.dbase);
-    hipLaunchKernelGGL(k_radix_scatter, dim3(nt, nb), dim3(kSortThreads), 0, st, ki, vi, ko, vo, n, shift, w.hist, w.dbase,
-                       nt);
+// LSD radix passes over bits [0, nbits) of the keys key_of gives (values: the items' indices),
+// ping-ponging between k0/v0 and k1/v1 (after an even number of passes the sorted keys and values
+// are in k0/v0, after an odd one in k1/v1).
+template <int ROUNDS, typename KeyFn>
+void radix_passes(const KeyFn& key_of, int64_t n, int nb, int nbits, const SortWs& w, hipStream_t st) {
+  const int nt = sort_tiles(n, nb);
+  const dim3 grid(nt, nb), blk(kSortThreads);
+  uint32_t *ki = w.k0, *vi = nullptr, *ko = w.k1, *vo = w.v1;
+  for (int shift = 0; shift < nbits; shift += kRadixBits) {
+    if (shift == 0) hipLaunchKernelGGL((k_radix_keys<ROUNDS, KeyFn>), grid, blk, 0, st, key_of, n, ki, w.hist, nt);
+    else hipLaunchKernelGGL(k_radix_hist<ROUNDS>, grid, blk, 0, st, ki, n, shift, w.hist, nt);
+    if (ROUNDS != kSmallRounds)
+      hipLaunchKernelGGL(k_radix_rowscan, dim3(kRadixDigits, nb), dim3(256), 0, st, w.hist, nt, w.rowtot);
+    hipLaunchKernelGGL(k_radix_scatter<ROUNDS>, grid, blk, 0, st, ki, vi, ko, vo, n, shift, w.hist, w.rowtot, nt);
+    vi = vo;
+    vo = vo == w.v1 ? w.v0 : w.v1;
     std::swap(ki, ko);
-    std::swap(vi, vo);
   }
 }
+template <typename KeyFn>
+void radix_sort(const KeyFn& key_of, int64_t n, int nb, int nbits, const SortWs& w, hipStream_t st) {
+  if (small_sort(n, nb)) radix_passes<kSmallRounds>(key_of, n, nb, nbits, w, st);
+  else radix_passes<kLargeRounds>(key_of, n, nb, nbits, w, st);
+}
+static_assert((kBinBits + kRadixBits - 1) / kRadixBits % 2 == 0, "the bin sort ends in k0/v0");
 
 // with_starts: also the points in sorted order, the 16-byte point records and the bin starts
 // (the per-cell gather's candidate lists); a forward pass, which sorts only to order its
 // work, reads its points through the permutation (v0) and needs none of them
 hipError_t launch_sort(const float* pts, int64_t ld, size_t pts_stride, const float4* pts4, int64_t n, int nb,
                        const SortWs& w, const float* src_f, hipStream_t st, bool with_starts = true) {
-  const int nt = sort_tiles(n);
   SortIn in;
   in.pts = pts; in.ld = ld; in.pts_stride = pts_stride; in.pts4 = pts4;
-  hipLaunchKernelGGL(k_bin_keys, dim3(grid1(n), nb), dim3(256), 0, st, in, n, w.k0, w.v0);
-  radix_passes(n, nb, nt, w, st);
+  radix_sort(BinKey{in, n}, n, nb, kBinBits, w, st);
   if (!with_starts) return hipGetLastError();
   hipLaunchKernelGGL(k_permute_points, dim3(grid1(n), nb), dim3(256), 0, st, in, n, w.v0, w.spts, w.spts4, src_f,
                      w.sf);
   // bin starts: one thread per position (gaps between neighbouring keys are short when the
   // points are few per bin), or one per bin (binary search) for large point sets, whose empty
   // regions would leave a few position threads writing long gaps
-  constexpr int64_t kBins = (int64_t)kBinsPerAxis * kBinsPerAxis * kBinsPerAxis;
-  if (n > 8 * kBins)
-    hipLaunchKernelGGL(k_bin_starts_search, dim3(grid1(kBins + 1), nb), dim3(256), 0, st, w.k0, n, w.start);
+  if (n > 8 * (int64_t)kBins)
+    hipLaunchKernelGGL(k_bin_starts_search, dim3(grid1((int64_t)kBins + 1), nb), dim3(256), 0, st, w.k0, n, w.start);
   else
     hipLaunchKernelGGL(k_bin_starts, dim3(grid1(n + 1), nb), dim3(256), 0, st, w.k0, n, w.start);
   return hipGetLastError();
@@ -351,14 +360,9 @@ hipError_t launch_sort(const float* pts, int64_t ld, size_t pts_stride, const fl
 hipError_t launch_step_sort(uint64_t seed, const uint64_t* step_ctr, uint32_t stream0, int64_t n, int nb,
                             const SortWs& w, const float* vol, int vnx, int vny, const apmg_brick* bricks, float* v,
                             hipStream_t st) {
-  const int nt = sort_tiles(n);
-  hipLaunchKernelGGL(k_batch_keys, dim3(grid1(n, 2048), nb), dim3(256), 0, st, seed, step_ctr, stream0, n, w.k0,
-                     w.v0);
-  radix_passes(n, nb, nt, w, st);
-  hipLaunchKernelGGL(k_batch_sorted, dim3(grid1(n, 2048), nb), dim3(256), 0, st, seed, step_ctr, stream0, n, w.v0,
-                     w.spts,
-                     w.spts4, vol, vnx, vny, bricks, v);
-  hipLaunchKernelGGL(k_bin_starts, dim3(grid1(n + 1), nb), dim3(256), 0, st, w.k0, n, w.start);
+  radix_sort(BatchKey{seed, step_ctr, stream0}, n, nb, kBinBits, w, st);
+  hipLaunchKernelGGL(k_batch_sorted, dim3(grid1(n + 1, 2048), nb), dim3(256), 0, st, seed, step_ctr, stream0, n, w.v0,
+                     w.k0, w.start, w.spts, w.spts4, vol, vnx, vny, bricks, v);
   return hipGetLastError();
 }
 
@@ -1322,7 +1326,8 @@ extern "C" apmg_status apmg_train_control(const apmg_control* c, const double* l
 
 // ---------------------------------------------------------------- domain-decomposition inference
 struct DdWs {
-  uint32_t *k0, *v0, *k1, *v1, *hist, *rowtot, *dbase, *seg;
+  SortWs srt;
+  uint32_t* seg;
   float *w3s, *scale;
   void* swz;
   OpsWs ops;
@@ -1331,14 +1336,9 @@ int key_bits(int nseg) { int b = 1; while ((1 << b) < nseg) ++b; return b; }
 size_t dd_ws(const Shape& s, const apmg_model* shape, int nb, int64_t n, void* ws, DdWs* o) {
   Carver cv(ws);
   const bool bf = shape->mlp_dtype == APMG_BF16;
-  const int64_t nn = std::max<int64_t>(n, 1);
   DdWs w;
   take_ops(cv, s, nb, g_rows(shape) == 4, paper_grids(shape), shape->grid_dtype == APMG_F16, &w.ops);
-  w.k0 = cv.take<uint32_t>(nn); w.v0 = cv.take<uint32_t>(nn);
-  w.k1 = cv.take<uint32_t>(nn); w.v1 = cv.take<uint32_t>(nn);
-  w.hist = cv.take<uint32_t>((size_t)kRadixDigits * sort_tiles(n));
-  w.rowtot = cv.take<uint32_t>(kRadixDigits);
-  w.dbase = cv.take<uint32_t>(kRadixDigits);
+  take_sort(cv, n, 1, false, &w.srt, true);
   w.seg = cv.take<uint32_t>((size_t)nb + 1);
   w.swz = cv.take<char>((size_t)nb * swz_sizes(s).total() * (bf ? 2 : 4));
   w.w3s = cv.take<float>((size_t)nb * s.H);
@@ -1375,17 +1375,9 @@ extern "C" apmg_status apmg_dd_forward(const apmg_dd_models* d, const apmg_brick
   const int kb = key_bits(nb), sb = n >= kFwdSortMin ? std::max(0, kBinBits - kb) : 0;
   const int3 bits = sb >= 3 ? make_int3((sb + 2) / 3, (sb + 1) / 3, sb / 3) : make_int3(0, 0, 0);
   const int sbits = bits.x + bits.y + bits.z;
-  hipLaunchKernelGGL(k_dd_keys, dim3(grid1(n)), dim3(256), 0, st, *t, d->bricks, bits, pts, ld, n, w.k0, w.v0);
-  const int nt = sort_tiles(n);
-  uint32_t *ki = w.k0, *vi = w.v0, *ko = w.k1, *vo = w.v1;
-  for (int shift = 0; shift < kb + sbits; shift += kRadixBits) {
-    hipLaunchKernelGGL(k_radix_hist, dim3(nt, 1), dim3(kSortThreads), 0, st, ki, n, shift, w.hist, nt);
-    hipLaunchKernelGGL(k_radix_rowscan, dim3(kRadixDigits, 1), dim3(256), 0, st, w.hist, nt, w.rowtot);
-    hipLaunchKernelGGL(k_radix_digitscan, dim3(1), dim3(256), 0, st, w.rowtot, w.dbase);
-    hipLaunchKernelGGL(k_radix_scatter, dim3(nt, 1), dim3(kSortThreads), 0, st, ki, vi, ko, vo, n, shift, w.hist, w.dbase, nt);
-    std::swap(ki, ko);
-    std::swap(vi, vo);
-  }
+  radix_sort(DdKey{*t, d->bricks, bits, pts, ld}, n, 1, kb + sbits, w.srt, st);
+  const bool odd = ((kb + sbits + kRadixBits - 1) / kRadixBits) % 2 != 0;
+  const uint32_t *ki = odd ? w.srt.k1 : w.srt.k0, *vi = odd ? w.srt.v1 : w.srt.v0;
   hipLaunchKernelGGL(k_seg_starts, dim3(grid1((int64_t)nb + 1)), dim3(256), 0, st, ki, n, sbits, nb, w.seg);
   // every brick's model over its segment, one launch
   hipError_t e = launch_swizzle(s, bf, d->W, d->W + (size_t)s.H * s.MC, d->W + (size_t)s.H * s.MC + (size_t)s.H * s.H,
@@ -1500,7 +1492,7 @@ struct VarWs {
   SortWs srt;      // the points (and dL/df) in spatial-bin order (backward)
   float* tau;      // their times (backward, time grids)
   // time grids: a further stable pass by time cell -> (time cell, spatial bin) order
-  uint32_t *tk0, *tv0, *tk1, *tv1;
+  uint32_t *tk0, *tk1, *tv1;
   float *tpts, *tdf;
   // and the atomic-free per-cell gather of the 4-D grid gradient: (x, y, z, t) records, the
   // starts of every (time cell, bin); the lattices of the block gather (time grids: of every time
@@ -1540,7 +1532,7 @@ size_t var_ws(const Shape& s, const EncArgs& ea, const apmg_model* m, const apmg
       const size_t nn = (size_t)std::max<int64_t>(n, 1);
       w.tau = cv.take<float>(nn);
       if (time_sorted(ea)) {
-        w.tk0 = cv.take<uint32_t>(nn); w.tv0 = cv.take<uint32_t>(nn);
+        w.tk0 = cv.take<uint32_t>(nn);
         w.tk1 = cv.take<uint32_t>(nn); w.tv1 = cv.take<uint32_t>(nn);
         w.tpts = cv.take<float>(3 * nn); w.tdf = cv.take<float>(nn);
         w.trec = cv.take<float4>(nn);
@@ -1654,13 +1646,9 @@ apmg_status apmg_variant_backward(const apmg_model* m, const apmg_encoder* e, co
   const float* bdf = w.srt.sf;
   if (w.tpts) {
     // then a stable pass by time cell: neighbouring points share the time slices too
-    const int nt = sort_tiles(n);
-    hipLaunchKernelGGL(k_time_keys, dim3(grid1(n)), dim3(256), 0, st, pts + 3 * ld, w.srt.v0, n, ea.Rt, w.tk0, w.tv0);
-    hipLaunchKernelGGL(k_radix_hist, dim3(nt, 1), dim3(kSortThreads), 0, st, w.tk0, n, 0, w.srt.hist, nt);
-    hipLaunchKernelGGL(k_radix_rowscan, dim3(kRadixDigits, 1), dim3(256), 0, st, w.srt.hist, nt, w.srt.rowtot);
-    hipLaunchKernelGGL(k_radix_digitscan, dim3(1), dim3(256), 0, st, w.srt.rowtot, w.srt.dbase);
-    hipLaunchKernelGGL(k_radix_scatter, dim3(nt, 1), dim3(kSortThreads), 0, st, w.tk0, w.tv0, w.tk1, w.tv1, n, 0, w.srt.hist,
-                       w.srt.dbase, nt);
+    SortWs ts = w.srt;
+    ts.k0 = w.tk0; ts.v0 = nullptr; ts.k1 = w.tk1; ts.v1 = w.tv1;
+    radix_sort(TimeKey{pts + 3 * ld, w.srt.v0, ea.Rt}, n, 1, 1, ts, st);   // one pass: sorted into tk1, tv1
     hipLaunchKernelGGL(k_time_permute, dim3(grid1(n)), dim3(256), 0, st, w.srt.spts, w.srt.sf, pts + 3 * ld,
                        w.srt.v0, w.tv1, n, w.tpts, w.tdf, w.tau, w.trec);
     hipLaunchKernelGGL(k_time_bin_starts, dim3(grid1(n + 1)), dim3(256), 0, st, w.tk1, w.srt.k0, w.tv1, n, ea.Rt,

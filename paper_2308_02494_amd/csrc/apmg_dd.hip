@@ -23,12 +23,12 @@ __device__ inline int brick_of(const apmg_brick_table& t, const float p[3]) {
   return idx[0] + t.dims[0] * (idx[1] + t.dims[1] * idx[2]);
 }
 
-// keys[i] = brick of point i, followed by bits of its bin inside the brick (x fastest: bits[0]
-// of x, bits[1] of y, bits[2] of z; none for a small batch), vals[i] = i.  The bin only orders the
-// work -- a tile's points then share grid cells in cache -- so it may round as it likes.
-__global__ void k_dd_keys(apmg_brick_table t, const apmg_brick* bricks, int3 bits, const float* pts, int64_t ld,
-                          int64_t n, uint32_t* keys, uint32_t* vals) {
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+// Sort key of a global point: its brick, followed by bits of its bin inside the brick (x fastest:
+// bits[0] of x, bits[1] of y, bits[2] of z; none for a small batch).  The bin only orders the work
+// -- a tile's points then share grid cells in cache -- so it may round as it likes.
+struct DdKey {
+  apmg_brick_table t; const apmg_brick* bricks; int3 bits; const float* pts; int64_t ld;
+  __device__ inline uint32_t operator()(int, int64_t i) const {
     const float p[3] = {pts[i], pts[ld + i], pts[2 * ld + i]};
     uint32_t key = (uint32_t)brick_of(t, p);
     const int nbits[3] = {bits.x, bits.y, bits.z};
@@ -42,10 +42,9 @@ __global__ void k_dd_keys(apmg_brick_table t, const apmg_brick* bricks, int3 bit
         key = (key << nbits[d]) | (uint32_t)fminf(fmaxf(b, 0.f), top);   // (NaN -> 0)
       }
     }
-    keys[i] = key;
-    vals[i] = (uint32_t)i;
+    return key;
   }
-}
+};
 
 // start[b] = first position whose key >> shift is >= b, b in [0, nseg]; binary search.
 __global__ void k_seg_starts(const uint32_t* keys, int64_t n, int shift, int nseg, uint32_t* start) {

@@ -332,22 +332,6 @@ __host__ __device__ inline PullBlocks pull_blocks(int R, int C) {
   return b;
 }
 
-// Inclusive scan over the wave's lanes by DPP: row_shr 1, 2, 4, 8 within rows of 16 lanes,
-// then row_bcast 15 and 31 carry a row's last lane into the next rows (lanes without a source
-// take 0).
-template <int CTRL, int ROWS>
-__device__ inline uint32_t dpp_or0(uint32_t v) {
-  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xf, false);
-}
-__device__ inline uint32_t wave_scan_add(uint32_t v) {
-  v += dpp_or0<0x111, 0xf>(v);
-  v += dpp_or0<0x112, 0xf>(v);
-  v += dpp_or0<0x114, 0xf>(v);
-  v += dpp_or0<0x118, 0xf>(v);
-  v += dpp_or0<0x142, 0xa>(v);
-  v += dpp_or0<0x143, 0xc>(v);
-  return v;
-}
 __device__ inline void wave_lds_order() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();

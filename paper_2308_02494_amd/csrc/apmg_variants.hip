@@ -304,18 +304,16 @@ __global__ void k_gather_f32(const float* __restrict__ src, const uint32_t* __re
     dst[j] = src[perm[j]];
 }
 
-// 4-D grids: the time cell of each spatially sorted point (the float32 decision of the lookup;
-// outside or NaN times -> 0) as a radix key, with the point's sorted position as its value.
-__global__ void k_time_keys(const float* __restrict__ tau, const uint32_t* __restrict__ perm, int64_t n, int Rt,
-                            uint32_t* __restrict__ keys, uint32_t* __restrict__ vals) {
-  const float ht = 0.5f * (float)(Rt - 1);
-  for (int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; j < n; j += (int64_t)gridDim.x * blockDim.x) {
-    const float t = tau[perm[j]];
+// 4-D grids: the time cell of spatially sorted position j (the float32 decision of the lookup;
+// outside or NaN times -> 0), the key of the further sort by time.
+struct TimeKey {
+  const float* tau; const uint32_t* perm; int Rt;
+  __device__ inline uint32_t operator()(int, int64_t j) const {
+    const float ht = 0.5f * (float)(Rt - 1), t = tau[perm[j]];
     const float ft = fminf(fmaxf(floorf(__builtin_fmaf(t, ht, ht)), 0.0f), (float)(Rt - 2));
-    keys[j] = (t >= -1.0f && t <= 1.0f) ? (uint32_t)ft : 0u;
-    vals[j] = (uint32_t)j;
+    return (t >= -1.0f && t <= 1.0f) ? (uint32_t)ft : 0u;
   }
-}
+};
 
 // The points, dL/df and times in (time cell, spatial bin) order: position j takes spatially
 // sorted position q = perm2[j] (original point perm[q]); also as (x, y, z, t) records.

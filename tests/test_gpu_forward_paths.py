@@ -64,3 +64,42 @@ def test_small_batch_weights_at_any_alignment():
     pts = soa(make_points(1000))
     other = A().Model(model.G, model.F, shifted, model.vmin, model.vmax)
     assert torch.equal(A().apmg_forward(model, pts), A().apmg_forward(other, pts))
+
+
+@pytest.mark.parametrize("n", [1023, 1025, 131071, 131072, 131073])
+def test_sort_tiles_and_modes(n):
+    # tiles of 1024 keys up to 2^17 keys, of 4096 above: the sorted forward gives the direct bits, and
+    # the gradients gathered from the sorted points add up to those of two parts sorted apart
+    # (float32 sums in another order: 1e-5 normwise)
+    host = synth.init_model(4, 2, 9, [8, 64, 64, 1], seed=5, grid_range=0.5)
+    model = A().Model.from_host(host, DEV)
+    x = make_points(n)
+    pts = soa(x)
+    assert torch.equal(A().apmg_forward(model, pts), A().apmg_forward_noalloc(model, pts))
+    df = torch.from_numpy(np.random.default_rng(n).normal(size=n).astype(np.float32)).to(DEV)
+    h = n // 3
+    whole = A().apmg_backward(model, pts, df)
+    again = A().apmg_backward(model, pts, df)
+    a = A().apmg_backward(model, pts[:, :h].contiguous(), df[:h])
+    b = A().apmg_backward(model, pts[:, h:].contiguous(), df[h:].contiguous())
+    assert torch.equal(whole[0], again[0]) and torch.equal(whole[1], again[1])
+    for g, ga, gb in zip([whole[0], whole[1], *whole[2]], [a[0], a[1], *a[2]], [b[0], b[1], *b[2]]):
+        want = (ga.double() + gb.double())
+        assert (g.double() - want).norm() <= 1e-5 * want.norm()
+
+
+def test_batched_sort_modes_give_the_same_brick():
+    # a brick sorts alone in small tiles, or with enough others in large ones: the same points in the
+    # same order, so with fixed launch shapes the same step, bit for bit
+    vol = synth.make_volume("blobs_sine", (24, 24, 24 * 12)).to(DEV)
+    _, bricks = A().apmg_make_bricks(24 * 12, 24, 24, 24, 0)
+    hosts = [synth.init_model(4, 2, 6, [8, 64, 64, 1], seed=b, grid_range=0.3) for b in range(12)]
+    out = []
+    for k in (1, 12):
+        tr = A().Trainer(hosts[:k], vol, bricks[:k], 20000, tuning={"tile_blocks": 4})
+        tr.density_active.fill_(1)
+        tr.step()
+        torch.cuda.synchronize()
+        out.append([t[0].clone() for t in (tr.losses, tr.F, tr.G, tr.W, tr.mF, tr.mG, tr.mW)])
+    for a, b in zip(*out):
+        assert torch.equal(a, b)

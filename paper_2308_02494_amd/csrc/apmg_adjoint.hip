@@ -35,7 +35,7 @@ template <bool BF> struct AdjT {
 // unrolled at compile time (at most 32 features per half); gathers run PD - 1 grids ahead
 // of the grid being interpolated.
 template <int C, bool GF16, bool BF, int PD, int ENC = kEncDense>
-__device__ inline void adj_fwd(const Shape& s, const float* sG, const void* F, const void* swz, const float* w3s,
+__device__ inline void adj_fwd(const Shape& s, const float* sG, const GridSrc<ENC>& F, const void* swz, const float* w3s,
                                float x, float y, float z, bool valid, int lane, f32x16 (&z1)[2], f32x16 (&z2)[2],
                                float& m, float (&yv)[32], bf16x8 (&yb)[4], bf16x8 (&hb)[4], const EncArgs& ea,
                                float tq) {
@@ -221,8 +221,7 @@ __global__ void __launch_bounds__(NW * kWave, 8 / NW) k_adjoint(TileArgs a) {
   const float* G = a.G + model * a.G_stride;
   for (int i = threadIdx.x; i < 12 * (s.M / s.L); i += blockDim.x) sG[i] = G[i];
   for (int i = threadIdx.x; i < kAdjWaves * H; i += blockDim.x) sW3w[i] = 0.f;
-  const void* F = GF16 ? (const void*)((const __half*)a.F + model * a.F_stride)
-                       : (const void*)((const float*)a.F + model * a.F_stride);
+  const GridSrc<ENC> F(s, (const char*)a.F + (GF16 ? 2 : 4) * model * a.F_stride, GF16 ? 2 : 4);
   block_copy16(lw, (const char*)a.swz + esz * model * a.swz_stride, wbytes);
   __syncthreads();
   const void* swz = lw;
@@ -551,9 +550,14 @@ hipError_t launch_adjoint(const TileArgs& a, bool grid_f16, bool mlp_bf16, int v
   const int nw = adjoint_waves(variant, mlp_bf16);
   const size_t shmem = adjoint_lds_bytes(a.s, mlp_bf16, nw);
   const int kf = (a.s.L == 1 && a.s.M % 2 == 0) ? (a.s.MC == 64 ? 32 : a.s.MC == 32 ? 16 : 0) : 0;
+  // (binary16 grids always fit a buffer resource: at most 2e9 values)
+  const bool wide = !grid_f16 && !grids_in_buffer(a.s, false);
+#define APMG_ADJ_E(CC, G16, B16, KF_, ENC_)                                                                        \
+  if (nw == 4) hipLaunchKernelGGL((k_adjoint<CC, G16, B16, 4, ENC_, KF_>), grid, dim3(4 * kWave), shmem, st, a);     \
+  else hipLaunchKernelGGL((k_adjoint<CC, G16, B16, 8, ENC_, KF_>), grid, dim3(8 * kWave), shmem, st, a);
 #define APMG_ADJ_K(CC, G16, B16, KF_)                                                                              \
-  if (nw == 4) hipLaunchKernelGGL((k_adjoint<CC, G16, B16, 4, kEncDense, KF_>), grid, dim3(4 * kWave), shmem, st, a); \
-  else hipLaunchKernelGGL((k_adjoint<CC, G16, B16, 8, kEncDense, KF_>), grid, dim3(8 * kWave), shmem, st, a);
+  if (wide) { APMG_ADJ_E(CC, false, B16, KF_, kEncDenseWide) }                                                     \
+  else { APMG_ADJ_E(CC, G16, B16, KF_, kEncDense) }
 #define APMG_ADJ_V(CC, G16, B16)                                                                                   \
   if (kf == 32) { APMG_ADJ_K(CC, G16, B16, 32) }                                                                  \
   else if (kf == 16) { APMG_ADJ_K(CC, G16, B16, 16) }                                                             \
@@ -572,6 +576,7 @@ hipError_t launch_adjoint(const TileArgs& a, bool grid_f16, bool mlp_bf16, int v
 #undef APMG_ADJ
 #undef APMG_ADJ_V
 #undef APMG_ADJ_K
+#undef APMG_ADJ_E
   return hipErrorInvalidValue;
 }
 

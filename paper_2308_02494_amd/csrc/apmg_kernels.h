@@ -23,6 +23,7 @@ struct Shape {
 //    channel-last copy [M][Rt][R^3][C] (time slice t of grid g is grid g * Rt + t there),
 //    the time coordinate in a fourth row of the points.
 constexpr int kEncDense = 0, kEncHash = 1, kEncTime = 2;
+constexpr int kEncDenseWide = 3;   // dense grids of 4 GiB and more (float32): 64-bit addresses
 constexpr int kMaxLevels = 8;
 struct EncArgs {
   uint32_t res2[kMaxLevels / 2];   // hash: cells per axis of level k in bits 16 (k % 2) of word k / 2

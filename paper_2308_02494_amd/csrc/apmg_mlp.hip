@@ -122,9 +122,9 @@ __device__ inline void tt_put(typename TT<BF>::T* t, int row, int j, float v) {
 }
 
 // One grid's contribution split in two so the gathers of the next grid can be in flight
-// while this one is consumed: grid_tap issues the 8 corner loads (always from a valid
+// while this one is consumed: enc_tap issues the 8 corner loads (always from a valid
 // address: cell 0 of grid 0 when the point is outside, invalid or past the last grid),
-// grid_tap_value interpolates and applies the Eq. (2) mask.
+// enc_value interpolates and applies the Eq. (2) mask.
 template <int C, int ENC = kEncDense> struct GridTap {
   float w[3];
   float val[8][C];
@@ -138,25 +138,20 @@ template <int C> struct GridTap<C, kEncTime> {
   bool in;
 };
 
-template <int C, bool GF16>
-__device__ inline void grid_tap(const Shape& s, const float* sG, const void* F, int g, float x, float y, float z,
-                                bool valid, float hR, GridTap<C>& t) {
-  const bool gok = valid && g < s.M;
-  const int gg = gok ? g : 0;
-  float l[3];
-  local_coords(sG + 12 * gg, x, y, z, l);
-  int i0[3];
-  t.in = cell_of(l, hR, s.R, i0, t.w) && gok;
-#pragma unroll
-  for (int d = 0; d < 3; ++d) i0[d] = t.in ? i0[d] : 0;
-  gather_cell<C, GF16>(F, gg, s.R, i0, t.val);
-}
-
-template <int C>
-__device__ inline void grid_tap_value(const GridTap<C>& t, float e[C]) {
-  trilerp<C>(t.val, t.w, e);
-#pragma unroll
-  for (int c = 0; c < C; ++c) e[c] = t.in ? e[c] : 0.f;
+// The grids of one model: a buffer resource, or a pointer (grids past a resource's 4 GiB, and the
+// encoder variants).
+template <int ENC> struct GridSrc {
+  const void* F;
+  __device__ inline GridSrc(const Shape&, const void* f, int) : F(f) {}
+};
+template <> struct GridSrc<kEncDense> {
+  __amdgpu_buffer_rsrc_t r;
+  __device__ inline GridSrc(const Shape& s, const void* f, int esz)
+      : r(__builtin_amdgcn_make_buffer_rsrc((void*)f, (short)0, s.M * s.C * s.R * s.R * s.R * esz, kBufferRsrcWord3)) {}
+};
+// whether the dense grids of one model take the buffer resource
+__host__ inline bool grids_in_buffer(const Shape& s, bool f16) {
+  return (double)s.M * s.C * s.R * s.R * s.R * (f16 ? 2 : 4) < 4294967296.0;
 }
 
 // Entry of vertex (vx, vy, vz) of a hash level with n1 = N + 1 vertices per axis: one entry
@@ -174,10 +169,23 @@ __device__ inline uint32_t hash_entry(uint32_t vx, uint32_t vy, uint32_t vz, uin
 // u_t = fma(t, (Rt-1)/2, (Rt-1)/2) (lower vertex clamped to [0, Rt-2]; a time outside [-1, 1]
 // masks the grid), and the corners of the two time slices.  Every load reads a valid address.
 template <int C, bool GF16, int ENC>
-__device__ inline void enc_tap(const Shape& s, const float* sG, const void* F, const EncArgs& ea, int g, float x,
-                               float y, float z, float tq, bool valid, float hR, GridTap<C, ENC>& t) {
-  if constexpr (ENC == kEncDense) {
-    grid_tap<C, GF16>(s, sG, F, g, x, y, z, valid, hR, t);
+__device__ inline void enc_tap(const Shape& s, const float* sG, const GridSrc<ENC>& F, const EncArgs& ea, int g,
+                               float x, float y, float z, float tq, bool valid, float hR, GridTap<C, ENC>& t) {
+  if constexpr (ENC == kEncDense || ENC == kEncDenseWide) {
+    const bool gok = valid && g < s.M;
+    const int gg = gok ? g : 0;
+    float l[3];
+    local_coords(sG + 12 * gg, x, y, z, l);
+    int i0[3];
+    t.in = cell_of(l, hR, s.R, i0, t.w) && gok;
+    if constexpr (ENC == kEncDense) {
+      const uint32_t off = cell_offset<C, GF16>(gg, s.R, i0);
+      gather_cell_buf<C, GF16>(F.r, t.in ? off : 0u, s.R, t.val);
+    } else {
+#pragma unroll
+      for (int d = 0; d < 3; ++d) i0[d] = t.in ? i0[d] : 0;
+      gather_cell<C, GF16>(F.F, gg, s.R, i0, t.val);
+    }
   } else if constexpr (ENC == kEncHash) {
     const bool gok = valid && g < s.M;
     const int gg = gok ? g : 0;
@@ -191,7 +199,7 @@ __device__ inline void enc_tap(const Shape& s, const float* sG, const void* F, c
     for (int d = 0; d < 3; ++d) i0[d] = t.in ? i0[d] : 0;
     const uint32_t n1 = (uint32_t)N + 1u;
     const bool dense = (uint64_t)n1 * n1 * n1 <= (uint64_t)ea.tmask + 1u;
-    const float* base = (const float*)F + (size_t)gg * ((size_t)ea.tmask + 1u) * C;
+    const float* base = (const float*)F.F + (size_t)gg * ((size_t)ea.tmask + 1u) * C;
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
       const uint32_t ent = hash_entry((uint32_t)i0[0] + (q & 1), (uint32_t)i0[1] + ((q >> 1) & 1),
@@ -222,8 +230,8 @@ __device__ inline void enc_tap(const Shape& s, const float* sG, const void* F, c
     const int t0 = t.in ? (int)ft : 0;
 #pragma unroll
     for (int d = 0; d < 3; ++d) i0[d] = t.in ? i0[d] : 0;
-    gather_cell<C, false>(F, gg * ea.Rt + t0, s.R, i0, t.va);
-    gather_cell<C, false>(F, gg * ea.Rt + t0 + 1, s.R, i0, t.vb);
+    gather_cell<C, false>(F.F, gg * ea.Rt + t0, s.R, i0, t.va);
+    gather_cell<C, false>(F.F, gg * ea.Rt + t0 + 1, s.R, i0, t.vb);
   }
 }
 
@@ -245,7 +253,7 @@ __device__ inline void enc_value(const GridTap<C, ENC>& t, float e[C]) {
 // Forward pass of one 32-point tile.  With STY, the features are also written to the
 // LDS tile Ty in dy-block order: feature t of half hf goes to row 32 (t/16) + 16 hf + t%16.
 template <int C, int H, bool GF16, bool BF, bool STY = false, int ENC = kEncDense>
-__device__ inline void tile_fwd(const Shape& s, const float* sG, const void* F, const void* swz,
+__device__ inline void tile_fwd(const Shape& s, const float* sG, const GridSrc<ENC>& F, const void* swz,
                                 const float* w3s, float x, float y, float z, bool valid, int lane,
                                 f32x16 (&z1)[H / 32], f32x16 (&z2)[H / 32], float& m,
                                 typename TT<BF>::T* Ty = nullptr, const ActTile<BF>* yact = nullptr,
@@ -390,8 +398,7 @@ __global__ void __launch_bounds__(NWF * kWave) k_forward(TileArgs a) {
   float* sG = smem;
   const float* G = a.G + model * a.G_stride;
   for (int i = threadIdx.x; i < 12 * (s.M / s.L); i += blockDim.x) sG[i] = G[i];
-  const void* F = GF16 ? (const void*)((const __half*)a.F + model * a.F_stride)
-                       : (const void*)((const float*)a.F + model * a.F_stride);
+  const GridSrc<ENC> F(s, (const char*)a.F + (GF16 ? 2 : 4) * model * a.F_stride, GF16 ? 2 : 4);
   const size_t esz = BF ? 2 : 4;
   const void* swz = (const char*)a.swz + esz * model * a.swz_stride;
   if constexpr (WL) {
@@ -566,7 +573,7 @@ __global__ void __launch_bounds__(kSmallWaves * kWave) k_forward_small(SmallArgs
   };
   auto put = [&](int gi, const GridTap<C>& t) {
     float e[C];
-    grid_tap_value<C>(t, e);
+    enc_value<C, kEncDense>(t, e);
 #pragma unroll
     for (int c = 0; c < C; ++c) sF[(gi * C + c) * 64 + lane] = e[c];
   };
@@ -674,7 +681,7 @@ __device__ inline f32x16 tt_mma(const typename TT<BF>::T* Ta, int ia, const type
 // gradient rows/columns split across launches.
 // ACT (KB == 0 only): the activation path, the per-point activations are stored (a.act) and
 // no weight gradient is accumulated in the kernel.
-template <int C, int H, bool GF16, bool BF, int KB, bool ACT>
+template <int C, int H, bool GF16, bool BF, int KB, bool ACT, int ENC = kEncDense>
 __global__ void __launch_bounds__(kBlock) k_backward(TileArgs a) {
   static_assert(!ACT || KB == 0, "the activation path has no register accumulators");
   extern __shared__ float smem[];
@@ -723,8 +730,7 @@ __global__ void __launch_bounds__(kBlock) k_backward(TileArgs a) {
   if (!REG)
     for (int i = threadIdx.x; i < H * ncols + nrows2 * H; i += blockDim.x) sW1[i] = 0.f;
 
-  const void* F = GF16 ? (const void*)((const __half*)a.F + model * a.F_stride)
-                       : (const void*)((const float*)a.F + model * a.F_stride);
+  const GridSrc<ENC> F(s, (const char*)a.F + (GF16 ? 2 : 4) * model * a.F_stride, GF16 ? 2 : 4);
   const void* swz = (const char*)a.swz + esz * model * a.swz_stride;
   if constexpr (REG) {
     block_copy16(lw, swz, wbytes);
@@ -776,7 +782,7 @@ __global__ void __launch_bounds__(kBlock) k_backward(TileArgs a) {
     // features y through ya (rows from 0), h1, delta1 and delta2 through ha (rows from MC)
     void* ablk = (char*)a.act + ((size_t)model * a.act_stride + (size_t)tile * a.act_rows * 32) * (BF ? 2 : 4);
     const ActTile<BF> ya(ablk, 0, s.MC, j), ha(ablk, s.MC, a.act_rows, j);
-    tile_fwd<C, H, GF16, BF, REG>(s, sG, F, swz, w3s, x, y, z, valid, lane, z1, z2, m, Ty,
+    tile_fwd<C, H, GF16, BF, REG, ENC>(s, sG, F, swz, w3s, x, y, z, valid, lane, z1, z2, m, Ty,
                                   ACT ? &ya : nullptr);
     if constexpr (ACT) {
 #pragma unroll
@@ -1080,33 +1086,41 @@ constexpr size_t kFwdWeightLdsMax = 120 * 1024;
 // above this much LDS per block only one forward block fits a compute unit: eight-wave blocks
 constexpr size_t kFwdWideLds = 80 * 1024;
 
-template <int C, int H, bool GF16, bool BF>
-hipError_t launch_tile_kernels(bool backward, int kb, const TileArgs& a, dim3 grid, size_t shmem,
-                               hipStream_t st) {
+template <int C, int H, bool GF16, bool BF, int ENC>
+hipError_t launch_tile_enc(bool backward, int kb, const TileArgs& a, dim3 grid, size_t shmem, hipStream_t st) {
   if (!backward && a.bricks) {
     if (fwd_weight_bytes(a.s, BF) > kFwdWeightLdsMax)
-      hipLaunchKernelGGL((k_forward<C, H, GF16, BF, false, kEncDense, 4, true>), grid, dim3(kBlock), shmem, st, a);
+      hipLaunchKernelGGL((k_forward<C, H, GF16, BF, false, ENC, 4, true>), grid, dim3(kBlock), shmem, st, a);
     else if (shmem > kFwdWideLds)
-      hipLaunchKernelGGL((k_forward<C, H, GF16, BF, true, kEncDense, 8, true>), grid, dim3(8 * kWave), shmem, st, a);
+      hipLaunchKernelGGL((k_forward<C, H, GF16, BF, true, ENC, 8, true>), grid, dim3(8 * kWave), shmem, st, a);
     else
-      hipLaunchKernelGGL((k_forward<C, H, GF16, BF, true, kEncDense, 4, true>), grid, dim3(kBlock), shmem, st, a);
+      hipLaunchKernelGGL((k_forward<C, H, GF16, BF, true, ENC, 4, true>), grid, dim3(kBlock), shmem, st, a);
   } else if (!backward) {
     if (fwd_weight_bytes(a.s, BF) > kFwdWeightLdsMax)
-      hipLaunchKernelGGL((k_forward<C, H, GF16, BF, false>), grid, dim3(kBlock), shmem, st, a);
+      hipLaunchKernelGGL((k_forward<C, H, GF16, BF, false, ENC>), grid, dim3(kBlock), shmem, st, a);
     else if (shmem > kFwdWideLds)
-      hipLaunchKernelGGL((k_forward<C, H, GF16, BF, true, kEncDense, 8>), grid, dim3(8 * kWave), shmem, st, a);
+      hipLaunchKernelGGL((k_forward<C, H, GF16, BF, true, ENC, 8>), grid, dim3(8 * kWave), shmem, st, a);
     else
-      hipLaunchKernelGGL((k_forward<C, H, GF16, BF, true>), grid, dim3(kBlock), shmem, st, a);
+      hipLaunchKernelGGL((k_forward<C, H, GF16, BF, true, ENC>), grid, dim3(kBlock), shmem, st, a);
   } else if (a.act) {
-    hipLaunchKernelGGL((k_backward<C, H, GF16, BF, 0, true>), grid, dim3(kBlock), shmem, st, a);
+    hipLaunchKernelGGL((k_backward<C, H, GF16, BF, 0, true, ENC>), grid, dim3(kBlock), shmem, st, a);
   } else if constexpr (H == 64) {
-    if (kb == 1) hipLaunchKernelGGL((k_backward<C, H, GF16, BF, 1, false>), grid, dim3(kBlock), shmem, st, a);
-    else if (kb == 2) hipLaunchKernelGGL((k_backward<C, H, GF16, BF, 2, false>), grid, dim3(kBlock), shmem, st, a);
-    else hipLaunchKernelGGL((k_backward<C, H, GF16, BF, 0, false>), grid, dim3(kBlock), shmem, st, a);
+    if (kb == 1) hipLaunchKernelGGL((k_backward<C, H, GF16, BF, 1, false, ENC>), grid, dim3(kBlock), shmem, st, a);
+    else if (kb == 2) hipLaunchKernelGGL((k_backward<C, H, GF16, BF, 2, false, ENC>), grid, dim3(kBlock), shmem, st, a);
+    else hipLaunchKernelGGL((k_backward<C, H, GF16, BF, 0, false, ENC>), grid, dim3(kBlock), shmem, st, a);
   } else {
-    hipLaunchKernelGGL((k_backward<C, H, GF16, BF, 0, false>), grid, dim3(kBlock), shmem, st, a);
+    hipLaunchKernelGGL((k_backward<C, H, GF16, BF, 0, false, ENC>), grid, dim3(kBlock), shmem, st, a);
   }
   return hipGetLastError();
+}
+
+// (binary16 grids always fit a buffer resource: at most 2e9 values)
+template <int C, int H, bool GF16, bool BF>
+hipError_t launch_tile_kernels(bool backward, int kb, const TileArgs& a, dim3 grid, size_t shmem, hipStream_t st) {
+  if constexpr (!GF16)
+    if (!grids_in_buffer(a.s, false))
+      return launch_tile_enc<C, H, GF16, BF, kEncDenseWide>(backward, kb, a, grid, shmem, st);
+  return launch_tile_enc<C, H, GF16, BF, kEncDense>(backward, kb, a, grid, shmem, st);
 }
 
 // Register-accumulated adjoint applies when H = 64 and at most 2 dy blocks per half.

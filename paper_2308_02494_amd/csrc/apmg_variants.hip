@@ -264,7 +264,7 @@ __global__ void __launch_bounds__(256) k_enc_transform_grad(EncScatterArgs a) {
 #pragma unroll
     for (int c = 0; c < C; ++c) dy[c] = a.dY[((size_t)g * a.n + p) * C + c];
     GridTap<C, ENC> t;
-    enc_tap<C, false, ENC>(s, a.G, a.F, a.enc, g, x, y, z, tq, true, hR, t);
+    enc_tap<C, false, ENC>(s, a.G, GridSrc<ENC>(s, a.F, 4), a.enc, g, x, y, z, tq, true, hR, t);
     if (!t.in) continue;
     float dl[3];
     if constexpr (ENC == kEncHash) {

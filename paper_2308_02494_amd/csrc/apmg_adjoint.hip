@@ -236,6 +236,7 @@ __global__ void __launch_bounds__(NW * kWave, 8 / NW) k_adjoint(TileArgs a) {
   const bool dy_buf = dY && dy_bytes < ((size_t)1 << 31);
   const __amdgpu_buffer_rsrc_t dy_rsrc =
       __builtin_amdgcn_make_buffer_rsrc(dY, (short)0, dy_buf ? (int)dy_bytes : 0, kBufferRsrcWord3);
+  constexpr int kDyNone = (int)0x80000000;   // past every such resource: the store is dropped
   const int dy_grid = dy_buf ? (int)(a.n * C * 4) : 0;   // bytes per grid
 
   // this wave's weight-gradient blocks: dW2 block (ib2, kb2) over published points
@@ -265,7 +266,7 @@ __global__ void __launch_bounds__(NW * kWave, 8 / NW) k_adjoint(TileArgs a) {
     const int64_t tile = rbase + wave;
     const int64_t p = tile * 32 + j;
     const bool valid = tile < t_end && p < a.n;
-    const int dy_lane = dy_buf ? (int)(((int64_t)hf * s.Mh * a.n + p) * C * 4) : 0;
+    const int dy_lane = dy_buf && valid ? (int)(((int64_t)hf * s.Mh * a.n + p) * C * 4) : kDyNone;
     float x = 0.f, y = 0.f, z = 0.f, tq = 0.f;
     if (valid) { x = Pp[p]; y = Pp[a.ld + p]; z = Pp[2 * a.ld + p]; }
     if constexpr (ENC == kEncTime) tq = valid ? a.tau[p] : 0.f;
@@ -326,7 +327,14 @@ __global__ void __launch_bounds__(NW * kWave, 8 / NW) k_adjoint(TileArgs a) {
 #pragma unroll
     for (int b = 0; b < NB; ++b)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) d2[b][r] = z2[b][r] > 0.f ? w3s[hf * (H / 2) + 16 * b + r] * dm : 0.f;
+      for (int q = 0; q < 4; ++q) {
+        // (four weights per load, outside the selects: a load per select becomes a branch each;
+        // with the stores of dL/dy below, 32 to 64 branches a tile: 80 brick models a step 6.49 ->
+        // 6.15 ms, a float32 step of 2^20 points 1090 -> 1059 us)
+        const f32x4 w = *(const f32x4*)(w3s + hf * (H / 2) + 16 * b + 4 * q);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) d2[b][4 * q + r] = z2[b][4 * q + r] > 0.f ? w[r] * dm : 0.f;
+      }
     // bf16: the packed operands stand in for delta2, h1, delta1 and y from here on (the
     // published values are bf16 as well); the ReLU pattern of z1 is kept as a bit mask
     bf16x8 d2b[4], d1b[4];
@@ -402,22 +410,35 @@ __global__ void __launch_bounds__(NW * kWave, 8 / NW) k_adjoint(TileArgs a) {
 #pragma unroll
             for (int st = 0; st < H / 16; ++st) dy = mma_bf16(W1Tb[((size_t)blk * (H / 16) + st) * 64 + lane], d1b[st], dy);
           }
+          if (dy_buf) {
+            // byte offset = lane part (this half's first grid, this point; past the resource for
+            // lanes that store nothing, so no branch per grid) + a uniform per-grid part: no
+            // 64-bit address per grid is held across the tile.  (The builtins take the values'
+            // bits as unsigned integers.)
+            typedef uint32_t u32x2n __attribute__((ext_vector_type(2)));
+            typedef uint32_t u32x4n __attribute__((ext_vector_type(4)));
 #pragma unroll
-          for (int u = 0; u < 16 / C; ++u) {
-            const int gi = 16 * blk / C + u;
-            const int g = hf * s.Mh + gi;
-            if (valid && gi < s.Mh && g < s.M) {
-              if (dy_buf) {
-                // byte offset = lane part (this half's first grid, this point) + a uniform
-                // per-grid part: no 64-bit address per grid is held across the tile (the
-                // builtin takes the value's bits as an unsigned integer)
+            for (int u = 0; u < 16 / C; ++u) {
+              const int gi = 16 * blk / C + u;
+              if (gi >= s.Mh) break;
+              const int o = (KF > 0 || hf * s.Mh + gi < s.M) ? dy_lane : kDyNone;
+              uint32_t w[C];
 #pragma unroll
-                for (int c = 0; c < C; ++c)
-                  __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(dy[u * C + c]), dy_rsrc, dy_lane + 4 * c, gi * dy_grid, 0);
-              } else {
+              for (int c = 0; c < C; ++c) w[c] = __float_as_uint(dy[u * C + c]);
+              if constexpr (C == 1) __builtin_amdgcn_raw_buffer_store_b32(w[0], dy_rsrc, o, gi * dy_grid, 0);
+              else if constexpr (C == 2)
+                __builtin_amdgcn_raw_buffer_store_b64(u32x2n{w[0], w[1]}, dy_rsrc, o, gi * dy_grid, 0);
+              else
+                __builtin_amdgcn_raw_buffer_store_b128(u32x4n{w[0], w[1], w[2], w[3]}, dy_rsrc, o, gi * dy_grid, 0);
+            }
+          } else {
+#pragma unroll
+            for (int u = 0; u < 16 / C; ++u) {
+              const int gi = 16 * blk / C + u;
+              if (valid && gi < s.Mh && hf * s.Mh + gi < s.M) {
                 // (the grid index is opaque here, so its 64-bit offset is formed at the store
                 // instead of being hoisted out of the tile loop and held, or spilled)
-                int gl = g;
+                int gl = hf * s.Mh + gi;
                 asm volatile("" : "+v"(gl));
                 float* dst = dY + ((size_t)gl * a.n + p) * C;
 #pragma unroll

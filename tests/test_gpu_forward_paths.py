@@ -103,3 +103,50 @@ def test_batched_sort_modes_give_the_same_brick():
         out.append([t[0].clone() for t in (tr.losses, tr.F, tr.G, tr.W, tr.mF, tr.mG, tr.mW)])
     for a, b in zip(*out):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("M,C,R,dtype", [(2, 4, 511, torch.float32), (2, 4, 512, torch.float32),
+                                         (3, 4, 512, torch.float16)])
+def test_grids_of_four_gib(M, C, R, dtype):
+    # grids below 4 GiB are read through 32-bit offsets of a buffer resource (above 2 GiB here, so the
+    # upper half of the offsets is used), grids from 4 GiB on with 64-bit addresses; small batches
+    # read the caller's grids another way.  The forward pass gives the same bits, and the adjoint's
+    # weight gradients are those of a float64 interpolation and MLP, 1e-3 normwise
+    g = torch.Generator(device=DEV).manual_seed(R + M)
+    F = torch.empty((M, R, R, R, C), dtype=dtype, device=DEV).normal_(generator=g)
+    G = torch.zeros((M, 3, 4), device=DEV)
+    for m in range(M):
+        G[m, :, :3] = torch.eye(3, device=DEV) * (0.97 - 0.1 * m)
+        G[m, :, 3] = 0.01
+    W = [torch.randn(s, generator=g, device=DEV) / s[1] ** 0.5 for s in ((64, M * C), (64, 64), (1, 64))]
+    model = A().Model(G, F, W, -1.0, 2.0, A().F32, A().GRIDS_MRRRC)
+    n = 20000
+    x = torch.rand((3, n), generator=g, device=DEV) * 2 - 1
+    large = A().apmg_forward(model, x)
+    assert torch.equal(large, torch.cat([A().apmg_forward(model, x[:, :9000].contiguous()),
+                                         A().apmg_forward(model, x[:, 9000:].contiguous())]))
+    df = torch.randn(n, generator=g, device=DEV)
+    dW = A().apmg_backward(model, x, df, want_dF=False, want_dG=False)[2]
+    feats = []
+    for m in range(M):
+        # Eqs. (1) and (2) in the float32 steps that define the cell decision (fused multiply-adds, z
+        # first): a float64 cell would turn ReLUs by itself
+        fma = lambda a, b, c: (a.double() * b.double() + c.double()).float()
+        g4 = G[m]
+        loc = torch.stack([fma(g4[d, 2], x[2], fma(g4[d, 1], x[1], fma(g4[d, 0], x[0], g4[d, 3]))) for d in range(3)])
+        inside = ((loc >= -1) & (loc <= 1)).all(0)
+        hr = torch.tensor(0.5 * (R - 1), device=DEV)
+        u = fma(loc, hr, hr)
+        i0 = u.floor().clamp(0, R - 2)
+        w, i0 = (u - i0).double(), i0.long()
+        e = torch.zeros((C, n), dtype=torch.float64, device=DEV)
+        for q in range(8):
+            b = [(q >> d) & 1 for d in range(3)]
+            wq = torch.stack([w[d] if b[d] else 1 - w[d] for d in range(3)]).prod(0)
+            e += wq * F[m, i0[2] + b[2], i0[1] + b[1], i0[0] + b[0]].double().T
+        feats.append(e * inside)
+    Wd = [w.double().requires_grad_() for w in W]
+    h = torch.relu(Wd[1] @ torch.relu(Wd[0] @ torch.cat(feats)))
+    ((Wd[2] @ h)[0] * 3.0 * df.double()).sum().backward()     # the output's scale: vmax - vmin
+    for got, want in zip(dW, Wd):
+        assert (got.double() - want.grad).norm() <= 1e-3 * want.grad.norm()

@@ -378,6 +378,15 @@ __host__ __device__ inline size_t fwd_weight_bytes(const Shape& s, bool bf) {
   return (z.w1 + z.w2) * (bf ? 2 : 4);
 }
 
+// Waves per SIMD the registers are kept to: four where the accumulators of both layers and two
+// grids' corners fit 128 registers, so that the loads of one wave's corners, the interpolation and
+// the matrix products overlap over four waves in place of three (2^20 points, 32 grids at
+// 32^3 x 2, float32: 272 -> 253 us).  Four-channel, 4-D and domain-decomposition forms and weights
+// read from memory would spill, so those are left to the compiler (1: no bound).
+constexpr int fwd_waves_per_simd(int C, int H, bool wl, int enc, bool dd) {
+  return H == 64 && C <= 2 && wl && enc != kEncTime && !dd ? 4 : 1;
+}
+
 // WL: the swizzled weights are staged in LDS (after the transforms).
 // NWF waves per block: 4, or 8 where the staged weights are so large that one block fills a
 // CU's LDS (then eight waves share them, two per SIMD, instead of one; measured on the 64-grid
@@ -387,7 +396,7 @@ __host__ __device__ inline size_t fwd_weight_bytes(const Shape& s, bool bf) {
 // model, mapped into each model's brick here: one pass less over the points than mapping them
 // into an array of their own first, and none to scatter the outputs back.
 template <int C, int H, bool GF16, bool BF, bool WL, int ENC = kEncDense, int NWF = kWavesPerBlock, bool DD = false>
-__global__ void __launch_bounds__(NWF * kWave) k_forward(TileArgs a) {
+__global__ void __launch_bounds__(NWF * kWave, fwd_waves_per_simd(C, H, WL, ENC, DD)) k_forward(TileArgs a) {
   extern __shared__ float smem[];
   // logical block: models in order, each model's blocks over contiguous runs of its
   // (spatially sorted) tiles, dealt to the XCDs in slabs
@@ -446,6 +455,10 @@ __global__ void __launch_bounds__(NWF * kWave) k_forward(TileArgs a) {
       y = __builtin_fmaf(__builtin_fmaf(y, a.vol_h[1], a.vol_h[1]) - e0[1], sc[1], -1.0f);
       z = __builtin_fmaf(__builtin_fmaf(z, a.vol_h[2], a.vol_h[2]) - e0[2], sc[2], -1.0f);
     }
+    // (weights in memory: loads of the same addresses for every tile are kept in the loop; moved
+    // out of it they take all registers and go to scratch: 64 grids at 32^3 x 4, float32
+    // 256-128-128-1, 2^18 points 1.91 -> 0.44 ms)
+    if constexpr (!WL) asm volatile("" : "+s"(swz));
     f32x16 z1[H / 32], z2[H / 32];
     float m;
     tile_fwd<C, H, GF16, BF, false, ENC>(s, sG, F, swz, w3s, x, y, z, valid, lane, z1, z2, m, nullptr, nullptr,
@@ -680,9 +693,11 @@ __device__ inline f32x16 tt_mma(const typename TT<BF>::T* Ta, int ia, const type
 // every column and row in one launch).  KB == 0: per-tile LDS accumulation, any shape,
 // gradient rows/columns split across launches.
 // ACT (KB == 0 only): the activation path, the per-point activations are stored (a.act) and
-// no weight gradient is accumulated in the kernel.
+// no weight gradient is accumulated in the kernel.  Bound by latency: two waves per SIMD although
+// some 40 values then go to scratch (64 grids at 64^3 x 4, 256-128-128-1 BF16 MLP, 2^19 points, the
+// whole adjoint: 3.18 ms with a loop per activation store, 3.00 ms without, 2.68 ms at two waves).
 template <int C, int H, bool GF16, bool BF, int KB, bool ACT, int ENC = kEncDense>
-__global__ void __launch_bounds__(kBlock) k_backward(TileArgs a) {
+__global__ void __launch_bounds__(kBlock, ACT ? 2 : 1) k_backward(TileArgs a) {
   static_assert(!ACT || KB == 0, "the activation path has no register accumulators");
   extern __shared__ float smem[];
   typedef typename TT<BF>::T TTy;
@@ -716,7 +731,10 @@ __global__ void __launch_bounds__(kBlock) k_backward(TileArgs a) {
   off = (off + 16 * kWavesPerBlock + 15) & ~(size_t)15;
   char* lw = lbase + off;
   TTy* tiles = (TTy*)(lbase + off + wbytes);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, j = lane & 31, hf = lane >> 5;
+  // (a uniform wave index: the tile's buffer resource stays in scalar registers, where a resource
+  // per lane makes every store of an activation a loop over its distinct values)
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), j = lane & 31,
+            hf = lane >> 5;
   const int wrows = H + 32 + (REG ? 32 * KB : 0);
   TTy* Ta = tiles + (size_t)wave * wrows * LDT;
   TTy* Tb = Ta + (size_t)H * LDT;
@@ -743,13 +761,6 @@ __global__ void __launch_bounds__(kBlock) k_backward(TileArgs a) {
   const float* P = a.pts + model * a.pts_stride;
   float* dY = a.dY ? a.dY + (size_t)model * s.M * a.n * C : nullptr;
   const float hR = 0.5f * (float)(s.R - 1);
-  const float* W2T = nullptr; const bf16x8* W2Tb = nullptr;
-  const float* W1T = nullptr; const bf16x8* W1Tb = nullptr;
-  {
-    const size_t o2t = (size_t)2 * H * s.KHP + (size_t)H * H, o1t = o2t + (size_t)H * H;
-    if (BF) { W2Tb = (const bf16x8*)((const uint16_t*)swz + o2t); W1Tb = (const bf16x8*)((const uint16_t*)swz + o1t); }
-    else { W2T = (const float*)swz + o2t; W1T = (const float*)swz + o1t; }
-  }
   f32x16 aw2[REG ? NB : 1][REG ? NB : 1];
   f32x16 aw1[REG ? NB : 1][REG ? KB : 1];
   if constexpr (REG) {
@@ -774,6 +785,14 @@ __global__ void __launch_bounds__(kBlock) k_backward(TileArgs a) {
   for (int64_t tile = lb * per + wave; tile < t_end; tile += kWavesPerBlock) {
     const int64_t p = tile * 32 + j;
     const bool valid = p < a.n;
+    // as in k_forward: loads of the weights stay in the loop (40 grids at 32^3 x 4, float32
+    // 160-128-128-1, 2^18 points: 4.04 -> 2.95 ms for the whole adjoint)
+    if constexpr (!REG) asm volatile("" : "+s"(swz), "+s"(w3s));
+    const size_t o2t = (size_t)2 * H * s.KHP + (size_t)H * H, o1t = o2t + (size_t)H * H;
+    const float* W2T = BF ? nullptr : (const float*)swz + o2t;
+    const float* W1T = BF ? nullptr : (const float*)swz + o1t;
+    const bf16x8* W2Tb = BF ? (const bf16x8*)((const uint16_t*)swz + o2t) : nullptr;
+    const bf16x8* W1Tb = BF ? (const bf16x8*)((const uint16_t*)swz + o1t) : nullptr;
     float x = 0.f, y = 0.f, z = 0.f;
     if (valid) { x = P[p]; y = P[a.ld + p]; z = P[2 * a.ld + p]; }
     f32x16 z1[NB], z2[NB];
@@ -843,11 +862,17 @@ __global__ void __launch_bounds__(kBlock) k_backward(TileArgs a) {
         if (j < 16) sW3w[wave * H + 32 * b + acc_row(j, hf)] += tot;   // one row per lane: no conflicts
       }
     }
+    if constexpr (!REG) asm volatile("" : "+s"(w3s));
     f32x16 d2[NB];
 #pragma unroll
     for (int b = 0; b < NB; ++b)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) d2[b][r] = z2[b][r] > 0.f ? w3s[hf * (H / 2) + 16 * b + r] * dm : 0.f;
+      for (int q = 0; q < 4; ++q) {
+        // (four weights per load, outside the selects: a load per select becomes a branch each)
+        const f32x4 w = *(const f32x4*)(w3s + hf * (H / 2) + 16 * b + 4 * q);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) d2[b][4 * q + r] = z2[b][4 * q + r] > 0.f ? w[r] * dm : 0.f;
+      }
 
     if constexpr (ACT) {
 #pragma unroll
@@ -892,14 +917,21 @@ __global__ void __launch_bounds__(kBlock) k_backward(TileArgs a) {
         if ((st & 7) == 7) sched_fence();
       }
     } else {
+      // (delta2 packed first: half its registers while delta1 accumulates)
+      bf16x8 db[H / 16];
 #pragma unroll
       for (int st = 0; st < H / 16; ++st) {
         float Bv[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) Bv[e] = d2[st >> 1][8 * (st & 1) + e];
-        const bf16x8 B = bf16_pack8(Bv);
+        db[st] = bf16_pack8(Bv);
+      }
+      if constexpr (ACT) sched_barrier();
 #pragma unroll
-        for (int b = 0; b < NB; ++b) d1[b] = mma_bf16(W2Tb[((size_t)b * (H / 16) + st) * 64 + lane], B, d1[b]);
+      for (int st = 0; st < H / 16; ++st) {
+#pragma unroll
+        for (int b = 0; b < NB; ++b) d1[b] = mma_bf16(W2Tb[((size_t)b * (H / 16) + st) * 64 + lane], db[st], d1[b]);
+        if constexpr (ACT) if ((st & 1) == 1) sched_fence();
       }
     }
 #pragma unroll
@@ -920,6 +952,17 @@ __global__ void __launch_bounds__(kBlock) k_backward(TileArgs a) {
       for (int b = 0; b < NB; ++b)
 #pragma unroll
         for (int r = 0; r < 16; ++r) tt_put<BF>(Ta, 32 * b + acc_row(r, hf), j, d1[b][r]);
+    }
+
+    bf16x8 d1b[BF ? H / 16 : 1];
+    if constexpr (BF) {
+#pragma unroll
+      for (int st = 0; st < H / 16; ++st) {
+        float Bv[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) Bv[e] = d1[st >> 1][8 * (st & 1) + e];
+        d1b[st] = bf16_pack8(Bv);
+      }
     }
 
     // dL/dy per block of 16 features of each half: stored per grid for the cell pass,
@@ -1086,6 +1129,13 @@ constexpr size_t kFwdWeightLdsMax = 120 * 1024;
 // above this much LDS per block only one forward block fits a compute unit: eight-wave blocks
 constexpr size_t kFwdWideLds = 80 * 1024;
 
+// LDS bytes of the activation path: no transpose tiles and no gradient sums in LDS (with the tiles,
+// a float32 block would fill a compute unit by itself).
+inline size_t act_lds_bytes(const Shape& s) {
+  const size_t b = ((size_t)(12 * s.M + kWavesPerBlock * s.H) * 4 + 7) & ~(size_t)7;
+  return (b + 16 * kWavesPerBlock + 15) & ~(size_t)15;
+}
+
 template <int C, int H, bool GF16, bool BF, int ENC>
 hipError_t launch_tile_enc(bool backward, int kb, const TileArgs& a, dim3 grid, size_t shmem, hipStream_t st) {
   if (!backward && a.bricks) {
@@ -1103,7 +1153,7 @@ hipError_t launch_tile_enc(bool backward, int kb, const TileArgs& a, dim3 grid, 
     else
       hipLaunchKernelGGL((k_forward<C, H, GF16, BF, true, ENC>), grid, dim3(kBlock), shmem, st, a);
   } else if (a.act) {
-    hipLaunchKernelGGL((k_backward<C, H, GF16, BF, 0, true, ENC>), grid, dim3(kBlock), shmem, st, a);
+    hipLaunchKernelGGL((k_backward<C, H, GF16, BF, 0, true, ENC>), grid, dim3(kBlock), act_lds_bytes(a.s), st, a);
   } else if constexpr (H == 64) {
     if (kb == 1) hipLaunchKernelGGL((k_backward<C, H, GF16, BF, 1, false, ENC>), grid, dim3(kBlock), shmem, st, a);
     else if (kb == 2) hipLaunchKernelGGL((k_backward<C, H, GF16, BF, 2, false, ENC>), grid, dim3(kBlock), shmem, st, a);

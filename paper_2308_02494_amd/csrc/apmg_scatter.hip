@@ -342,11 +342,11 @@ __device__ inline void wave_lds_order() {
 // (neighbouring elements, one quad of slots) into distinct banks.  32 slots at a time (a step's
 // matches beyond them go in a second round): the wave's LDS is what limits the waves per SIMD.
 constexpr int kSlots = 32, kSlotPitch = kSlots + 4;
-// The value of a wave-uniform double in scalar registers.
-__device__ inline double uniform_f64(double v) {
+// Lane k's value of a double, in scalar registers.
+__device__ inline double lane_f64(double v, int k) {
   const uint64_t b = __builtin_bit_cast(uint64_t, v);
-  const uint64_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)b);
-  const uint64_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(b >> 32));
+  const uint64_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, k);
+  const uint64_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), k);
   return __builtin_bit_cast(double, lo | hi << 32);
 }
 
@@ -399,36 +399,44 @@ __global__ void __launch_bounds__(256, DG || C * TS > 2 ? 4 : 6) k_block_pull(Ce
     // the block's box in global space (inverse of Eq. (1) applied to its local box)
     const uint32_t cyz = cb / (uint32_t)nb.x, cz = cyz / (uint32_t)nb.y;
     const int b0[3] = {(int)(cb - cyz * nb.x) * nbk[0], (int)(cyz - cz * nb.y) * nbk[1], (int)cz * nbk[2]};
-    double A[3][3];
-    for (int r = 0; r < 3; ++r) for (int c = 0; c < 3; ++c) A[r][c] = Gg[4 * r + c];
-    const double c00 = A[1][1] * A[2][2] - A[1][2] * A[2][1], c01 = A[1][2] * A[2][0] - A[1][0] * A[2][2];
-    const double c02 = A[1][0] * A[2][1] - A[1][1] * A[2][0];
-    const double det = A[0][0] * c00 + A[0][1] * c01 + A[0][2] * c02;
-    const double inv[9] = {c00, A[0][2] * A[2][1] - A[0][1] * A[2][2], A[0][1] * A[1][2] - A[0][2] * A[1][1],
-                           c01, A[0][0] * A[2][2] - A[0][2] * A[2][0], A[0][2] * A[1][0] - A[0][0] * A[1][2],
-                           c02, A[0][1] * A[2][0] - A[0][0] * A[2][1], A[0][0] * A[1][1] - A[0][1] * A[1][0]};
-    bool bad = !(fabs(det) > 1e-30);
-    float Ai[9];
-    const double rdet = recip_f64(det);
-    for (int k = 0; k < 9; ++k) { Ai[k] = (float)(inv[k] * rdet); bad = bad || !isfinite(Ai[k]); }
+    // The set-up costs a wave of few points more vector instructions than its points, so what is
+    // the same work for several values is done by as many lanes: lane k < 9 takes entry k of the
+    // inverse and bound k of the box (a step of 80 models of 65,536 points, 16 grids at 32^3 x 2:
+    // 6.22 -> 6.15 ms; hash grids of 8 x 4 levels, 2^20 points: 2.28 -> 2.23 ms; several blocks in turn
+    // for one set-up keep more values alive than fit: 6.16 ms at best, 6.8 with one block).
+    const float* Gr = a.G + model * a.G_stride + 12 * g;
+    const int k9 = min(lane, 8), kr = k9 / 3, kc = k9 - 3 * kr;
+    const int c1 = kc == 2 ? 0 : kc + 1, c2 = kc == 0 ? 2 : kc - 1, r1 = kr == 2 ? 0 : kr + 1, r2 = kr == 0 ? 2 : kr - 1;
+    const double cof = (double)Gr[4 * c1 + r1] * (double)Gr[4 * c2 + r2] - (double)Gr[4 * c1 + r2] * (double)Gr[4 * c2 + r1];
+    const float g0 = Gr[4 * kc];
+    const double det = (double)Gg[0] * lane_f64(cof, 0) + (double)Gg[1] * lane_f64(cof, 3) + (double)Gg[2] * lane_f64(cof, 6);
+    const float Ak = (float)(cof * recip_f64(det));             // entry k9 of the inverse
+    const bool bad = __ballot(!isfinite(Ak)) != 0 || !(fabs(det) > 1e-30);
     int lo[3], hi[3];
-    if (bad) {
-      for (int d = 0; d < 3; ++d) { lo[d] = 0; hi[d] = kBinsPerAxis - 1; }
-    } else {
+    {
       float lm[3], hl[3];
+#pragma unroll
       for (int d = 0; d < 3; ++d) {
         const int e = min(b0[d] + nbk[d], R1);
         const float hc = 0.5f * (float)a.cell;
         lm[d] = -1.f + (float)(b0[d] + e) * hc - Gg[4 * d + 3];   // box centre minus the translation
         hl[d] = (float)(e - b0[d]) * hc;                           // box half-width (local units)
       }
+      float wc = 0.f, hw = 0.f;
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        const float Ai = __shfl(Ak, 3 * kc + k, 64);
+        wc = __builtin_fmaf(Ai, lm[k], wc);
+        hw = __builtin_fmaf(fabsf(Ai), hl[k], hw);
+      }
+      const float f0 = floorf((wc - hw - 1e-4f + 1.f) * (0.5f * kBinsPerAxis));
+      const float f1 = floorf((wc + hw + 1e-4f + 1.f) * (0.5f * kBinsPerAxis));
+      const int l0 = bad ? 0 : (int)fminf(fmaxf(f0, 0.f), (float)(kBinsPerAxis - 1));
+      const int l1 = bad ? kBinsPerAxis - 1 : (int)fminf(fmaxf(f1, 0.f), (float)(kBinsPerAxis - 1));
+#pragma unroll
       for (int d = 0; d < 3; ++d) {
-        const float wc = Ai[3 * d] * lm[0] + Ai[3 * d + 1] * lm[1] + Ai[3 * d + 2] * lm[2];
-        const float hw = fabsf(Ai[3 * d]) * hl[0] + fabsf(Ai[3 * d + 1]) * hl[1] + fabsf(Ai[3 * d + 2]) * hl[2];
-        const float f0 = floorf((wc - hw - 1e-4f + 1.f) * (0.5f * kBinsPerAxis));
-        const float f1 = floorf((wc + hw + 1e-4f + 1.f) * (0.5f * kBinsPerAxis));
-        lo[d] = (int)fminf(fmaxf(f0, 0.f), (float)(kBinsPerAxis - 1));
-        hi[d] = (int)fminf(fmaxf(f1, 0.f), (float)(kBinsPerAxis - 1));
+        lo[d] = __builtin_amdgcn_readlane(l0, d);
+        hi[d] = __builtin_amdgcn_readlane(l1, d);
       }
     }
     constexpr size_t kNB3 = (size_t)kBinsPerAxis * kBinsPerAxis * kBinsPerAxis;
@@ -437,17 +445,13 @@ __global__ void __launch_bounds__(256, DG || C * TS > 2 ? 4 : 6) k_block_pull(Ce
     const uint32_t* start = a.start + (size_t)model * (TS == 1 ? kNB3 + 1 : kNB3);
     const float ht = 0.5f * (float)(a.Rt - 1);
     const float hR = 0.5f * (float)R1;
-    double blo[3], bhi[3], ra[3];
-    local_box(Gg, b0, nbk, R1, a.cell, blo, bhi);
-    span_recips(Gg, ra);
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-      blo[d] = uniform_f64(blo[d]);
-      bhi[d] = uniform_f64(bhi[d]);
-      ra[d] = uniform_f64(ra[d]);
-      lo[d] = __builtin_amdgcn_readfirstlane(lo[d]);
-      hi[d] = __builtin_amdgcn_readfirstlane(hi[d]);
-    }
+    // local_box and span_recips: axis kc's lower bound in lanes 0-2, upper bound in 3-5, reciprocal
+    // in 6-8 (to scalar registers where the rows are cut: held from here they would be spilled)
+    static_assert(kPullNY == kPullNZ, "one width for y and z");
+    const int bd = kc == 0 ? b0[0] : kc == 1 ? b0[1] : b0[2], ed = min(bd + (kc == 0 ? nbk[0] : kPullNY), R1);
+    const double td = (double)Gr[4 * kc + 3], rec = g0 != 0.f ? recip_f64((double)g0) : 0.0;
+    const double box = -1.0 + a.cell * (kr == 0 ? bd : ed) + (kr == 0 ? -1e-4 : 1e-4) - td;
+    const double span = kr == 2 ? rec : box;
     const int ny_r = hi[1] - lo[1] + 1, nz_r = hi[2] - lo[2] + 1;
     const int nrows = ny_r * nz_r;
     // the block's cells on an axis: u - ulo in [0, width), cells 0 .. cmax (the grid's last cell
@@ -600,6 +604,13 @@ __global__ void __launch_bounds__(256, DG || C * TS > 2 ? 4 : 6) k_block_pull(Ce
     for (int rb = 0; rb < nrows; rb += kRowBatch) {
       uint32_t s0 = 0, len = 0;
       const int rr = rb + lane;
+      double blo[3], bhi[3], ra[3];
+#pragma unroll
+      for (int d = 0; d < 3; ++d) {
+        blo[d] = lane_f64(span, d);
+        bhi[d] = lane_f64(span, 3 + d);
+        ra[d] = lane_f64(span, 6 + d);
+      }
       if (rr < nrows) {
         int x0 = lo[0], x1 = hi[0];
         const int yb = lo[1] + rr % ny_r, zb = lo[2] + rr / ny_r;

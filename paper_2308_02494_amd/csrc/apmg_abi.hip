@@ -1327,6 +1327,7 @@ extern "C" apmg_status apmg_train_control(const apmg_control* c, const double* l
 // ---------------------------------------------------------------- domain-decomposition inference
 struct DdWs {
   SortWs srt;
+  float4* rec;
   uint32_t* seg;
   float *w3s, *scale;
   void* swz;
@@ -1339,6 +1340,7 @@ size_t dd_ws(const Shape& s, const apmg_model* shape, int nb, int64_t n, void* w
   DdWs w;
   take_ops(cv, s, nb, g_rows(shape) == 4, paper_grids(shape), shape->grid_dtype == APMG_F16, &w.ops);
   take_sort(cv, n, 1, false, &w.srt, true);
+  w.rec = cv.take<float4>((size_t)std::max<int64_t>(n, 1));
   w.seg = cv.take<uint32_t>((size_t)nb + 1);
   w.swz = cv.take<char>((size_t)nb * swz_sizes(s).total() * (bf ? 2 : 4));
   w.w3s = cv.take<float>((size_t)nb * s.H);
@@ -1375,7 +1377,7 @@ extern "C" apmg_status apmg_dd_forward(const apmg_dd_models* d, const apmg_brick
   const int kb = key_bits(nb), sb = n >= kFwdSortMin ? std::max(0, kBinBits - kb) : 0;
   const int3 bits = sb >= 3 ? make_int3((sb + 2) / 3, (sb + 1) / 3, sb / 3) : make_int3(0, 0, 0);
   const int sbits = bits.x + bits.y + bits.z;
-  radix_sort(DdKey{*t, d->bricks, bits, pts, ld}, n, 1, kb + sbits, w.srt, st);
+  radix_sort(DdKey{*t, d->bricks, bits, pts, ld, w.rec}, n, 1, kb + sbits, w.srt, st);
   const bool odd = ((kb + sbits + kRadixBits - 1) / kRadixBits) % 2 != 0;
   const uint32_t *ki = odd ? w.srt.k1 : w.srt.k0, *vi = odd ? w.srt.v1 : w.srt.v0;
   hipLaunchKernelGGL(k_seg_starts, dim3(grid1((int64_t)nb + 1)), dim3(256), 0, st, ki, n, sbits, nb, w.seg);
@@ -1396,6 +1398,7 @@ extern "C" apmg_status apmg_dd_forward(const apmg_dd_models* d, const apmg_brick
   a.perm = vi;
   a.f = f;
   a.bricks = d->bricks;
+  a.rec = w.rec;
   for (int k = 0; k < 3; ++k) a.vol_h[k] = 0.5f * (float)(t->vol[k] - 1);
   // blocks per brick: twice the even share of the tiles, at least one
   const int64_t per = (n + nb - 1) / nb;

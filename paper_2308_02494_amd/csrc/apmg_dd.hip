@@ -25,11 +25,14 @@ __device__ inline int brick_of(const apmg_brick_table& t, const float p[3]) {
 
 // Sort key of a global point: its brick, followed by bits of its bin inside the brick (x fastest:
 // bits[0] of x, bits[1] of y, bits[2] of z; none for a small batch).  The bin only orders the work
-// -- a tile's points then share grid cells in cache -- so it may round as it likes.
+// -- a tile's points then share grid cells in cache -- so it may round as it likes.  The point
+// is also written as one 16-byte record: read through the permutation, a record is one cache line
+// where the three coordinate rows are three (4.0 M points, 80 models: 0.92 -> 0.87 ms for the whole query).
 struct DdKey {
-  apmg_brick_table t; const apmg_brick* bricks; int3 bits; const float* pts; int64_t ld;
+  apmg_brick_table t; const apmg_brick* bricks; int3 bits; const float* pts; int64_t ld; float4* rec;
   __device__ inline uint32_t operator()(int, int64_t i) const {
     const float p[3] = {pts[i], pts[ld + i], pts[2 * ld + i]};
+    rec[i] = make_float4(p[0], p[1], p[2], 0.f);
     uint32_t key = (uint32_t)brick_of(t, p);
     const int nbits[3] = {bits.x, bits.y, bits.z};
     if (nbits[0] > 0) {

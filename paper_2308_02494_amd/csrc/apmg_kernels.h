@@ -70,6 +70,7 @@ struct TileArgs {
   const uint32_t* perm;
   const uint32_t* seg;
   const apmg_brick* bricks; float vol_h[3];
+  const float4* rec;                      // domain decomposition: the global points as records
   // forward
   float* f;
   // adjoint

@@ -424,7 +424,7 @@ __global__ void __launch_bounds__(NWF * kWave, fwd_waves_per_simd(C, H, WL, ENC,
   // [seg[model], seg[model + 1]) of one order of global points
   const int64_t base = DD ? (int64_t)a.seg[model] : 0;
   const int64_t cnt = DD ? (int64_t)a.seg[model + 1] - base : a.n;
-  const float* P = DD ? a.pts : a.pts + model * a.pts_stride;
+  const float* P = DD ? nullptr : a.pts + model * a.pts_stride;
   float* fo = DD ? a.f : a.f + (size_t)model * a.n;
   const uint32_t* perm = DD ? a.perm + base : a.perm;
   // DD: the model's brick frame (l = fma(u - e0, 2 / (e1 - e0), -1))
@@ -448,7 +448,11 @@ __global__ void __launch_bounds__(NWF * kWave, fwd_waves_per_simd(C, H, WL, ENC,
     // the point at the tile's position p, or, in a spatial order, at position perm[p]
     const int64_t q = (perm && valid) ? (int64_t)perm[p] : p;
     float x = 0.f, y = 0.f, z = 0.f, tq = 0.f;
-    if (valid) { x = P[q]; y = P[a.ld + q]; z = P[2 * a.ld + q]; }
+    if constexpr (DD) {
+      if (valid) { const float4 r = a.rec[q]; x = r.x; y = r.y; z = r.z; }
+    } else {
+      if (valid) { x = P[q]; y = P[a.ld + q]; z = P[2 * a.ld + q]; }
+    }
     if constexpr (ENC == kEncTime) tq = valid ? a.tau[q] : 0.f;
     if constexpr (DD) {
       x = __builtin_fmaf(__builtin_fmaf(x, a.vol_h[0], a.vol_h[0]) - e0[0], sc[0], -1.0f);

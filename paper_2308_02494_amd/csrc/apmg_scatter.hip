@@ -399,9 +399,9 @@ __global__ void __launch_bounds__(256, DG || C * TS > 2 ? 4 : 6) k_block_pull(Ce
     // the block's box in global space (inverse of Eq. (1) applied to its local box)
     const uint32_t cyz = cb / (uint32_t)nb.x, cz = cyz / (uint32_t)nb.y;
     const int b0[3] = {(int)(cb - cyz * nb.x) * nbk[0], (int)(cyz - cz * nb.y) * nbk[1], (int)cz * nbk[2]};
-    // The set-up costs a wave of few points more vector instructions than its points, so what is
+    // The set-up costs as many vector instructions as a hundred points or so do, so what is
     // the same work for several values is done by as many lanes: lane k < 9 takes entry k of the
-    // inverse and bound k of the box (a step of 80 models of 65,536 points, 16 grids at 32^3 x 2:
+    // inverse and bound k of the box (a step of 80 models of 131,072 points, 16 grids at 32^3 x 2:
     // 6.22 -> 6.15 ms; hash grids of 8 x 4 levels, 2^20 points: 2.28 -> 2.23 ms; several blocks in turn
     // for one set-up keep more values alive than fit: 6.16 ms at best, 6.8 with one block).
     const float* Gr = a.G + model * a.G_stride + 12 * g;

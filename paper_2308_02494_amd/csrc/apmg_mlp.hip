@@ -381,10 +381,12 @@ __host__ __device__ inline size_t fwd_weight_bytes(const Shape& s, bool bf) {
 // Waves per SIMD the registers are kept to: four where the accumulators of both layers and two
 // grids' corners fit 128 registers, so that the loads of one wave's corners, the interpolation and
 // the matrix products overlap over four waves in place of three (2^20 points, 32 grids at
-// 32^3 x 2, float32: 272 -> 253 us).  Four-channel, 4-D and domain-decomposition forms and weights
-// read from memory would spill, so those are left to the compiler (1: no bound).
-constexpr int fwd_waves_per_simd(int C, int H, bool wl, int enc, bool dd) {
-  return H == 64 && C <= 2 && wl && enc != kEncTime && !dd ? 4 : 1;
+// 32^3 x 2, float32: 272 -> 253 us).  The four-channel and 4-D forms, the hash grids with a BF16
+// MLP (8 x 4 levels, 2^20 points: 486 us bounded, with 46 values in scratch; 278 us without), the
+// domain-decomposed form and weights read from memory would spill, so those are left to the
+// compiler (1: no bound).
+constexpr int fwd_waves_per_simd(int C, int H, bool bf, bool wl, int enc, bool dd) {
+  return H == 64 && C <= 2 && wl && enc != kEncTime && !(enc == kEncHash && bf) && !dd ? 4 : 1;
 }
 
 // WL: the swizzled weights are staged in LDS (after the transforms).
@@ -396,7 +398,7 @@ constexpr int fwd_waves_per_simd(int C, int H, bool wl, int enc, bool dd) {
 // model, mapped into each model's brick here: one pass less over the points than mapping them
 // into an array of their own first, and none to scatter the outputs back.
 template <int C, int H, bool GF16, bool BF, bool WL, int ENC = kEncDense, int NWF = kWavesPerBlock, bool DD = false>
-__global__ void __launch_bounds__(NWF * kWave, fwd_waves_per_simd(C, H, WL, ENC, DD)) k_forward(TileArgs a) {
+__global__ void __launch_bounds__(NWF * kWave, fwd_waves_per_simd(C, H, BF, WL, ENC, DD)) k_forward(TileArgs a) {
   extern __shared__ float smem[];
   // logical block: models in order, each model's blocks over contiguous runs of its
   // (spatially sorted) tiles, dealt to the XCDs in slabs

@@ -240,6 +240,7 @@ __device__ inline uint32_t cell_offset(int g, int R, const int i0[3]) {
 }
 template <int C, bool F16>
 __device__ inline void gather_cell_buf(__amdgpu_buffer_rsrc_t r, uint32_t off, int R, float val[8][C]) {
+  static_assert(!(F16 && C == 1), "pairs of 4-byte alignment");
   constexpr uint32_t VB = C * (F16 ? 2 : 4);
   typedef uint32_t u32x2n __attribute__((ext_vector_type(2)));
   typedef uint32_t u32x4n __attribute__((ext_vector_type(4)));
@@ -248,10 +249,7 @@ __device__ inline void gather_cell_buf(__amdgpu_buffer_rsrc_t r, uint32_t off, i
   for (int q2 = 0; q2 < 4; ++q2) {  // q2 = b + 2c'
     const int so = (int)((q2 & 1) * rowB + (q2 >> 1) * sliceB);
     float pr[2 * C];
-    if constexpr (F16 && C == 1) {
-      pr[0] = __half2float(__ushort_as_half(__builtin_amdgcn_raw_buffer_load_b16(r, (int)off, so, 0)));
-      pr[1] = __half2float(__ushort_as_half(__builtin_amdgcn_raw_buffer_load_b16(r, (int)off + 2, so, 0)));
-    } else if constexpr (F16) {
+    if constexpr (F16) {
       uint32_t w[C];
       if constexpr (C == 2) {
         const u32x2n v = __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, so, 0);

@@ -138,16 +138,18 @@ template <int C> struct GridTap<C, kEncTime> {
   bool in;
 };
 
-// The grids of one model: a buffer resource, or a pointer (grids past a resource's 4 GiB, and the
-// encoder variants).
+// The grids of one model: a buffer resource, or a pointer (grids past a resource's 4 GiB, the
+// encoder variants, and one-channel binary16 grids, see enc_tap).
 template <int ENC> struct GridSrc {
   const void* F;
   __device__ inline GridSrc(const Shape&, const void* f, int) : F(f) {}
 };
 template <> struct GridSrc<kEncDense> {
   __amdgpu_buffer_rsrc_t r;
+  const void* F;
   __device__ inline GridSrc(const Shape& s, const void* f, int esz)
-      : r(__builtin_amdgcn_make_buffer_rsrc((void*)f, (short)0, s.M * s.C * s.R * s.R * s.R * esz, kBufferRsrcWord3)) {}
+      : r(__builtin_amdgcn_make_buffer_rsrc((void*)f, (short)0, s.M * s.C * s.R * s.R * s.R * esz, kBufferRsrcWord3)),
+        F(f) {}
 };
 // whether the dense grids of one model take the buffer resource
 __host__ inline bool grids_in_buffer(const Shape& s, bool f16) {
@@ -178,7 +180,9 @@ __device__ inline void enc_tap(const Shape& s, const float* sG, const GridSrc<EN
     local_coords(sG + 12 * gg, x, y, z, l);
     int i0[3];
     t.in = cell_of(l, hR, s.R, i0, t.w) && gok;
-    if constexpr (ENC == kEncDense) {
+    // (a one-channel binary16 pair is 4 bytes at any 2: one unaligned global load, where a buffer
+    // resource takes two 2-byte loads: 2^20 points, 40 grids at 24^3, BF16 MLP 235 against 270 us)
+    if constexpr (ENC == kEncDense && !(GF16 && C == 1)) {
       const uint32_t off = cell_offset<C, GF16>(gg, s.R, i0);
       gather_cell_buf<C, GF16>(F.r, t.in ? off : 0u, s.R, t.val);
     } else {

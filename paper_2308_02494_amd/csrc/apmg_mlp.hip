@@ -386,11 +386,15 @@ __host__ __device__ inline size_t fwd_weight_bytes(const Shape& s, bool bf) {
 // grids' corners fit 128 registers, so that the loads of one wave's corners, the interpolation and
 // the matrix products overlap over four waves in place of three (2^20 points, 32 grids at
 // 32^3 x 2, float32: 272 -> 253 us).  The four-channel and 4-D forms, the hash grids with a BF16
-// MLP (8 x 4 levels, 2^20 points: 486 us bounded, with 46 values in scratch; 278 us without), the
-// domain-decomposed form and weights read from memory would spill, so those are left to the
-// compiler (1: no bound).
+// MLP (8 x 4 levels, 2^20 points: 486 us bounded, with 46 values in scratch; 278 us without) and
+// weights read from memory would spill, so those are left to the compiler (1: no bound).  The
+// domain-decomposed form holds the brick's frame as well: bound to three, which keeps its
+// accumulators in the registers that four waves leave (left to the compiler it takes 12 more than
+// four waves have: 125 models of 8 grids at 16^3 x 2, binary16 grids, 2^19 points: 185 us against
+// 167); only with a BF16 MLP over float32 grids of two channels it does run three.
 constexpr int fwd_waves_per_simd(int C, int H, bool bf, bool wl, int enc, bool dd) {
-  return H == 64 && C <= 2 && wl && enc != kEncTime && !(enc == kEncHash && bf) && !dd ? 4 : 1;
+  if (H != 64 || C > 2 || !wl || enc == kEncTime || (enc == kEncHash && bf)) return 1;
+  return dd ? 3 : 4;
 }
 
 // WL: the swizzled weights are staged in LDS (after the transforms).
@@ -398,7 +402,7 @@ constexpr int fwd_waves_per_simd(int C, int H, bool bf, bool wl, int enc, bool d
 // CU's LDS (then eight waves share them, two per SIMD, instead of one; measured on the 64-grid
 // 256-128-128-1 BF16 model: 8.06 -> 6.14 ms per 16.6 M-point frame; twelve waves, three per
 // SIMD, 6.26 ms).
-// DD: global points of a domain decomposition, in the order of k_dd_keys (perm), a segment per
+// DD: global points of a domain decomposition, in the order of their DdKey (perm), a segment per
 // model, mapped into each model's brick here: one pass less over the points than mapping them
 // into an array of their own first, and none to scatter the outputs back.
 template <int C, int H, bool GF16, bool BF, bool WL, int ENC = kEncDense, int NWF = kWavesPerBlock, bool DD = false>

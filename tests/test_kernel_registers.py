@@ -48,6 +48,19 @@ def test_forward_kernels_use_no_scratch(kernels):
     assert not {n: s for n, s in fwd.items() if s}
 
 
+def test_brick_forward_keeps_four_waves_per_simd(kernels):
+    # 512 vector registers per SIMD lane, handed out in eights; the weights staged in LDS, four-wave blocks
+    few = {}
+    for C in (1, 2):
+        for f16 in ("true", "false"):
+            for bf16 in ("true", "false"):
+                name = f"apmg::k_forward<{C}, 64, {f16}, {bf16}, true, 0, 4, true>"
+                waves = 512 // (-(-kernels[name][0] // 8) * 8)
+                if waves < (3 if (C, f16, bf16) == (2, "false", "true") else 4):
+                    few[name] = waves
+    assert not few
+
+
 def test_one_channel_half_grids_load_pairs_at_once(code_object):
     # the two binary16 values of an x-adjacent vertex pair come in one 4-byte load
     syms = [ln.split()[-1] for ln in run(LLVM + "llvm-readelf", "-sW", code_object).splitlines() if " FUNC " in ln]

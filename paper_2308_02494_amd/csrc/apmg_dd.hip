@@ -24,7 +24,7 @@ __device__ inline int brick_of(const apmg_brick_table& t, const float p[3]) {
 }
 
 // Sort key of a global point: its brick, followed by bits of its bin inside the brick (x fastest:
-// bits[0] of x, bits[1] of y, bits[2] of z; none for a small batch).  The bin only orders the work
+// bits[0] of x, bits[1] of y, bits[2] of z; none where the order does not pay).  The bin only orders the work
 // -- a tile's points then share grid cells in cache -- so it may round as it likes.  The point
 // is also written as one 16-byte record: read through the permutation, a record is one cache line
 // where the three coordinate rows are three (4.0 M points, 80 models: 0.92 -> 0.87 ms for the whole query).

@@ -1,0 +1,61 @@
+"""Launches per call: the kernel nodes of a graph captured around one call.
+
+Small calls are bound by their launches (about 5 us each), so rules that choose a path by size are
+checked by what they launch.
+"""
+import ctypes
+
+import pytest
+import torch
+
+import synth
+from test_gpu_parity import A, DEV
+
+pytestmark = [pytest.mark.gpu,
+              pytest.mark.skipif(not torch.cuda.is_available(), reason="needs a GPU")]
+
+
+def launches(fn):
+    """Kernel nodes that one call of fn records (fn returns what it allocated, if anything)."""
+    fn()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph):
+        out = fn()
+    lib = next(ln.split()[-1] for ln in open("/proc/self/maps") if "libamdhip64" in ln)
+    n = ctypes.c_size_t()
+    assert ctypes.CDLL(lib).hipGraphGetNodes(ctypes.c_void_p(graph.raw_cuda_graph()), None, ctypes.byref(n)) == 0
+    del out
+    return n.value
+
+
+def brick_models(R, M, bf16, half=True):
+    table, bricks = A().apmg_make_bricks(60, 60, 60, 20, 1)
+    nb = len(bricks)
+    g = torch.Generator(device=DEV).manual_seed(R)
+    F = torch.rand((nb, M, 2, R, R, R), generator=g, device=DEV) - 0.5
+    hosts = [synth.init_model(M, 2, 4, [2 * M, 64, 64, 1], seed=b) for b in range(nb)]
+    G = torch.stack([torch.from_numpy(h["G"]) for h in hosts]).to(DEV)
+    W = torch.stack([torch.cat([torch.from_numpy(w).reshape(-1) for w in h["W"]]) for h in hosts]).to(DEV)
+    return A().DDModels(G, F.half() if half else F, W, [2 * M, 64, 64, 1], table, bricks,
+                        A().BF16 if bf16 else A().F32)
+
+
+# bins inside the bricks are ordered (a second radix pass: three launches more) where the lookups'
+# cache misses cost more than that: by points, grids and bytes of grids, and the MLP that hides them
+@pytest.mark.parametrize("R,M,bf16,half,n,order", [
+    (16, 8, True, True, 1 << 18, False), (16, 8, False, False, 1 << 18, False), (16, 16, False, True, 1 << 18, False),
+    (32, 16, True, False, 1 << 18, True), (32, 16, False, False, 1 << 18, True), (32, 16, False, True, 1 << 14, False),
+])
+def test_brick_queries_order_bins_where_it_pays(R, M, bf16, half, n, order):
+    dd = brick_models(R, M, bf16, half)
+    pts = torch.rand((3, n), device=DEV) * 2 - 1
+    out = torch.empty(n, device=DEV)
+    start = pts[:, :1000].contiguous()
+    few = launches(lambda: A().apmg_dd_forward(dd, start, out=out[:1000]))
+    got = launches(lambda: A().apmg_dd_forward(dd, pts, out=out))
+    scan = 1 if n > 1 << 17 else 0          # (of more than 2^17 points, a pass has a row scan of its own)
+    assert got == few + scan + (2 + scan if order else 0)
+    # ordered or not, the same bits as queries of fewer points, which are not ordered
+    parts = [A().apmg_dd_forward(dd, p.contiguous()) for p in pts.split(30000, dim=1)]
+    assert torch.equal(A().apmg_dd_forward(dd, pts), torch.cat(parts))

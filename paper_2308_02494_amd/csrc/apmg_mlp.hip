@@ -1233,15 +1233,23 @@ hipError_t launch_tile(bool backward, int kb, const TileArgs& a, bool grid_f16, 
   return hipErrorInvalidValue;
 }
 
-// Batches of up to kFwdSmallMax points whose forward weights are at most kFwdSmallWeights elements
-// (every block lays them out again) take the one-launch kernel.  Its blocks' own cost shows once
-// they queue for compute units: 16,000 points of 32 grids at 32^3 x 2 take 31 us against 36 us
-// through k_forward, 32,000 take 55 against 35.
-constexpr int64_t kFwdSmallMax = (int64_t)1 << 14;
+// Batches of up to fwd_small_max points whose forward weights are at most kFwdSmallWeights elements
+// (every block lays them out again) take the one-launch kernel.  Up to 2^13 points its blocks are
+// one per compute unit and it is always faster (24 grids at 16^3 x 4, float32, 8192 points: 21 us
+// against 29 through k_forward, channel-last 14 against 18).  Beyond, the blocks queue, and their
+// cost grows with the features and, by lookups, with the channels: at 2^14 points 32 grids at
+// 16^3 x 2 take 18 us against 21 (channel-last 16 and 16) and 128 grids at 12^3 x 1 25 against 33,
+// but 16 grids at 16^3 x 4 22 against 21 (20 both at 12288 points), 64 grids at 16^3 x 2 channel-last
+// 26 against 24 (24 both at 12288), 24 grids at 16^3 x 4 31 against 27 and 40 grids at 16^3 x 4 47
+// against 37.
 constexpr size_t kFwdSmallWeights = 16384;
+inline int64_t fwd_small_max(const Shape& s) {
+  if (s.C == 1 || s.MC * s.C <= 128) return 16384;
+  return s.MC * s.C <= 256 ? 12288 : 8192;
+}
 bool forward_small_applies(const Shape& s, int64_t n) {
   const SwzSizes z = swz_sizes(s);
-  return n <= kFwdSmallMax && z.w1 + z.w2 <= kFwdSmallWeights;
+  return n <= fwd_small_max(s) && z.w1 + z.w2 <= kFwdSmallWeights;
 }
 hipError_t launch_forward_small(const SmallArgs& a, bool grid_f16, bool bf, bool last, hipStream_t st) {
   const Shape& s = a.s;

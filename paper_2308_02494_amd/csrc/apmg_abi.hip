@@ -1507,7 +1507,8 @@ struct VarWs {
   float* dFcl;     // channel-last time-grid gradient (backward, paper-order grids)
   SortWs srt;      // the points (and dL/df) in spatial-bin order (backward)
   float* tau;      // their times (backward, time grids)
-  // time grids: a further stable pass by time cell -> (time cell, spatial bin) order
+  // time grids: a further stable pass by time cell -> (time cell, spatial bin) order (with one
+  // time cell the spatial order is that order)
   uint32_t *tk0, *tk1, *tv1;
   float *tpts, *tdf;
   // and the atomic-free per-cell gather of the 4-D grid gradient: (x, y, z, t) records, the
@@ -1548,11 +1549,13 @@ size_t var_ws(const Shape& s, const EncArgs& ea, const apmg_model* m, const apmg
       const size_t nn = (size_t)std::max<int64_t>(n, 1);
       w.tau = cv.take<float>(nn);
       if (time_sorted(ea)) {
-        w.tk0 = cv.take<uint32_t>(nn);
-        w.tk1 = cv.take<uint32_t>(nn); w.tv1 = cv.take<uint32_t>(nn);
-        w.tpts = cv.take<float>(3 * nn); w.tdf = cv.take<float>(nn);
         w.trec = cv.take<float4>(nn);
-        w.tstart = cv.take<uint32_t>((size_t)(ea.Rt - 1) * kBinsPerAxis * kBinsPerAxis * kBinsPerAxis + 1);
+        if (ea.Rt > 2) {
+          w.tk0 = cv.take<uint32_t>(nn);
+          w.tk1 = cv.take<uint32_t>(nn); w.tv1 = cv.take<uint32_t>(nn);
+          w.tpts = cv.take<float>(3 * nn); w.tdf = cv.take<float>(nn);
+          w.tstart = cv.take<uint32_t>((size_t)(ea.Rt - 1) * kBinsPerAxis * kBinsPerAxis * kBinsPerAxis + 1);
+        }
         w.tcc = cv.take<float>((size_t)(ea.Rt - 1) * s.M * pull_blocks(s.R, s.C).total() * pull_lat(s.C) * 2 * s.C);
       }
     }
@@ -1671,6 +1674,9 @@ apmg_status apmg_variant_backward(const apmg_model* m, const apmg_encoder* e, co
                        w.tstart);
     bpts = w.tpts;
     bdf = w.tdf;
+  } else if (w.trec) {
+    hipLaunchKernelGGL(k_time_permute, dim3(grid1(n)), dim3(256), 0, st, w.srt.spts, (const float*)nullptr, pts + 3 * ld,
+                       w.srt.v0, (const uint32_t*)nullptr, n, (float*)nullptr, (float*)nullptr, w.tau, w.trec);
   } else if (w.tau) {
     hipLaunchKernelGGL(k_gather_f32, dim3(grid1(n)), dim3(256), 0, st, pts + 3 * ld, w.srt.v0, n, w.tau);
   }
@@ -1735,7 +1741,7 @@ apmg_status apmg_variant_backward(const apmg_model* m, const apmg_encoder* e, co
     CellArgs c;
     memset(&c, 0, sizeof(c));
     c.s = s; c.G = Gc; c.F = Fc;
-    c.pts4 = w.trec; c.n = n; c.start = w.tstart; c.dY = w.dY; c.CC = w.tcc; c.Rt = ea.Rt;
+    c.pts4 = w.trec; c.n = n; c.start = w.tstart ? w.tstart : w.srt.start; c.dY = w.dY; c.CC = w.tcc; c.Rt = ea.Rt;
     c.dY_grid = (size_t)n * s.C; c.cell = 2.0 / (s.R - 1);
     // the points of one time cell decide between one wave and four per block
     const int64_t nt = n / (ea.Rt - 1), wgroups = (int64_t)pull_groups(s, nt) * s.M * (ea.Rt - 1);

@@ -316,20 +316,22 @@ struct TimeKey {
 };
 
 // The points, dL/df and times in (time cell, spatial bin) order: position j takes spatially
-// sorted position q = perm2[j] (original point perm[q]); also as (x, y, z, t) records.
+// sorted position q = perm2[j] (original point perm[q]); also as (x, y, z, t) records.  perm2 NULL
+// (one time cell: the spatial order is that order already): the times and the records alone.
 __global__ void k_time_permute(const float* __restrict__ spts, const float* __restrict__ sf,
                                const float* __restrict__ tau, const uint32_t* __restrict__ perm,
                                const uint32_t* __restrict__ perm2, int64_t n, float* __restrict__ pts2,
                                float* __restrict__ f2, float* __restrict__ tau2, float4* __restrict__ rec) {
   for (int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; j < n; j += (int64_t)gridDim.x * blockDim.x) {
-    const uint32_t q = perm2[j];
+    const uint32_t q = perm2 ? perm2[j] : (uint32_t)j;
     const float x = spts[q], y = spts[n + q], z = spts[2 * n + q], t = tau[perm[q]];
+    tau2[j] = t;
+    rec[j] = make_float4(x, y, z, t);
+    if (!perm2) continue;
     pts2[j] = x;
     pts2[n + j] = y;
     pts2[2 * n + j] = z;
     f2[j] = sf[q];
-    tau2[j] = t;
-    rec[j] = make_float4(x, y, z, t);
   }
 }
 

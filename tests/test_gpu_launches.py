@@ -77,3 +77,19 @@ def test_small_forward_sizes(M, C, n, small):
     assert (launches(lambda: A().apmg_forward(model, pts, out=out, ws=ws)) == 1) == small
     parts = [A().apmg_forward(model, p.contiguous()) for p in pts.split(5000, dim=1)]
     assert torch.equal(out, torch.cat(parts))
+
+
+def test_one_time_cell_is_not_sorted_by_time():
+    # with two time vertices the spatial order is the (time cell, bin) order: no pass by time cell
+    # (keys and scatter) and no starts of its own
+    g = torch.Generator(device=DEV).manual_seed(2)
+    n, counts = 3000, []
+    pts = torch.rand((4, n), generator=g, device=DEV) * 2.2 - 1.1     # among them times outside
+    df = torch.randn(n, generator=g, device=DEV)
+    for Rt in (2, 3):
+        host = synth.init_model(4, 2, 4, [8, 64, 64, 1], seed=Rt, grid_range=0.3)
+        F = torch.rand((4, 2, Rt, 6, 6, 6), generator=g, device=DEV) - 0.5
+        model = A().VariantModel(A().ENC_TIME, torch.from_numpy(host["G"]).to(DEV), F,
+                                 [torch.from_numpy(w).to(DEV) for w in host["W"]])
+        counts.append(launches(lambda: A().apmg_variant_backward(model, pts, df)))
+    assert counts[0] == counts[1] - 3

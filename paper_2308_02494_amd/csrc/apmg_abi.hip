@@ -1485,7 +1485,6 @@ size_t variant_f_elems(const Shape& s, const EncArgs& ea, int kind) {
   return kind == APMG_ENC_HASH ? (size_t)s.M * ((size_t)ea.tmask + 1u) * s.C
                                : (size_t)s.M * ea.Rt * s.R * s.R * s.R * s.C;
 }
-inline int variant_nbx(int64_t n) { return (int)std::max<int64_t>(1, (n + 256 * kTgPoints - 1) / (256 * kTgPoints)); }
 // a hash level as the dense grids the block gather sees: the model's transforms, N + 1 vertices per axis
 inline Shape hash_level_shape(const Shape& s, const EncArgs& ea, int k) {
   Shape t = s;
@@ -1535,7 +1534,7 @@ size_t var_ws(const Shape& s, const EncArgs& ea, const apmg_model* m, const apmg
   if (backward) {
     w.part = cv.take<double>((size_t)bwd_blocks(n, bf) * part_layout(s, s.MC, s.H).len);
     w.dY = cv.take<float>((size_t)s.M * std::max<int64_t>(n, 1) * s.C);
-    w.dGpart = cv.take<double>((size_t)s.M * variant_nbx(n) * 12);
+    w.dGpart = cv.take<double>((size_t)s.M * tg_blocks(n, s.M) * 12);
     if (time_paper && !time_sorted(ea)) w.dFcl = cv.take<float>(variant_f_elems(s, ea, e->kind));
     take_sort(cv, n, 1, true, &w.srt);
     if (e->kind == APMG_ENC_HASH) {
@@ -1765,7 +1764,7 @@ apmg_status apmg_variant_backward(const apmg_model* m, const apmg_encoder* e, co
     }
   }
   if (dG) {
-    sa.dGpart = w.dGpart; sa.nbx = variant_nbx(n);
+    sa.dGpart = w.dGpart; sa.nbx = tg_blocks(n, s.M); sa.tgp = tg_points(n, s.M);
     if (launch_enc_transform_grad(sa, e->kind, st) != hipSuccess) return APMG_EHIP;
   }
   if (dG)

@@ -30,7 +30,8 @@ struct EncScatterArgs {
   float* dF;               // scatter: same layout as F (channel-last for time), accumulated
   int g0, gs;              // scatter: feature grid of block row y is g0 + gs y
   double* dGpart;          // transform gradient: [M][nbx][12]
-  int nbx;                 // point blocks per feature grid
+  int nbx;                 // point blocks per feature grid, of 256 tgp points
+  int tgp;
 };
 
 // dl_d = sum_c dy_c d(trilinear_c)/dw_d for corner values val and offsets w.
@@ -241,10 +242,20 @@ __global__ void __launch_bounds__(256) k_lattice_to_hash(int N, uint32_t tmask, 
 }
 
 // The transform gradient through the interpolation weights: per feature grid, sums over the
-// points of (dl_d) x^T and dl_d, in float64.  kTgPoints points per thread, so the wave
+// points of (dl_d) x^T and dl_d, in float64.  Several points per thread (a.tgp), so the wave
 // reduction of the 12 sums (a butterfly of float64 shuffles, several times the work of a
 // point) is paid once per block and not once per point.
-constexpr int kTgPoints = 16;
+constexpr int kTgPoints = 16;              // at most
+// Points per thread: 16 once that leaves four blocks per compute unit, fewer for smaller batches, whose
+// blocks would run 16 points in a row with most of the device idle (8 grids at 64^3, 4096 points, the
+// transform gradient alone: 166 us with 16, 122 with one; 65,536 points: 142 and 129).
+inline int tg_points(int64_t n, int grids) {
+  return (int)std::max<int64_t>(1, std::min<int64_t>(kTgPoints, n * grids / (256 * 1024)));
+}
+inline int tg_blocks(int64_t n, int grids) {
+  const int64_t per = 256 * tg_points(n, grids);
+  return (int)std::max<int64_t>(1, (n + per - 1) / per);
+}
 template <int C, int ENC>
 __global__ void __launch_bounds__(256) k_enc_transform_grad(EncScatterArgs a) {
   __shared__ double sred[4][12];
@@ -256,8 +267,8 @@ __global__ void __launch_bounds__(256) k_enc_transform_grad(EncScatterArgs a) {
   double acc[12];
 #pragma unroll
   for (int k = 0; k < 12; ++k) acc[k] = 0.0;
-  const int64_t p0 = (int64_t)bx * (256 * kTgPoints);
-  for (int64_t p = p0 + threadIdx.x; p < min(a.n, p0 + 256 * kTgPoints); p += 256) {
+  const int64_t p0 = (int64_t)bx * (256 * a.tgp);
+  for (int64_t p = p0 + threadIdx.x; p < min(a.n, p0 + 256 * a.tgp); p += 256) {
     const float x = a.pts[p], y = a.pts[a.ld + p], z = a.pts[2 * a.ld + p];
     const float tq = ENC == kEncTime ? a.tau[p] : 0.f;
     float dy[C];

@@ -15,18 +15,33 @@ pytestmark = [pytest.mark.gpu,
               pytest.mark.skipif(not torch.cuda.is_available(), reason="needs a GPU")]
 
 
-def launches(fn):
-    """Kernel nodes that one call of fn records (fn returns what it allocated, if anything)."""
+class KernelNode(ctypes.Structure):
+    _fields_ = [("block", ctypes.c_uint32 * 3), ("extra", ctypes.c_void_p), ("func", ctypes.c_void_p),
+                ("grid", ctypes.c_uint32 * 3), ("args", ctypes.c_void_p), ("shared", ctypes.c_uint32)]
+
+
+def kernel_grids(fn):
+    """The launch grids of the kernels that one call of fn records."""
     fn()
     torch.cuda.synchronize()
     graph = torch.cuda.CUDAGraph(keep_graph=True)
     with torch.cuda.graph(graph):
         out = fn()
-    lib = next(ln.split()[-1] for ln in open("/proc/self/maps") if "libamdhip64" in ln)
-    n = ctypes.c_size_t()
-    assert ctypes.CDLL(lib).hipGraphGetNodes(ctypes.c_void_p(graph.raw_cuda_graph()), None, ctypes.byref(n)) == 0
+    hip = ctypes.CDLL(next(ln.split()[-1] for ln in open("/proc/self/maps") if "libamdhip64" in ln))
+    g, n = ctypes.c_void_p(graph.raw_cuda_graph()), ctypes.c_size_t()
+    assert hip.hipGraphGetNodes(g, None, ctypes.byref(n)) == 0
+    nodes = (ctypes.c_void_p * n.value)()
+    assert hip.hipGraphGetNodes(g, nodes, ctypes.byref(n)) == 0
+    grids, p = [], KernelNode()
+    for node in nodes:
+        assert hip.hipGraphKernelNodeGetParams(ctypes.c_void_p(node), ctypes.byref(p)) == 0
+        grids.append(tuple(p.grid))
     del out
-    return n.value
+    return grids
+
+
+def launches(fn):
+    return len(kernel_grids(fn))
 
 
 def brick_models(R, M, bf16, half=True):
@@ -93,3 +108,24 @@ def test_one_time_cell_is_not_sorted_by_time():
                                  [torch.from_numpy(w).to(DEV) for w in host["W"]])
         counts.append(launches(lambda: A().apmg_variant_backward(model, pts, df)))
     assert counts[0] == counts[1] - 3
+
+
+# one to sixteen points a thread: four blocks per compute unit (256) over the feature grids where there
+# are points enough for them
+@pytest.mark.parametrize("n,points", [(257, 1), (5000, 1), (149797, 4), (1 << 20, 16)])
+def test_transform_gradient_blocks(n, points):
+    M, R, Rt = 7, 6, 2
+    host = synth.init_model(M, 2, 4, [2 * M, 64, 64, 1], seed=1, grid_range=0.3)
+    g = torch.Generator(device=DEV).manual_seed(n)
+    F = torch.rand((M, 2, Rt, R, R, R), generator=g, device=DEV) - 0.5
+    model = A().VariantModel(A().ENC_TIME, torch.from_numpy(host["G"]).to(DEV), F,
+                             [torch.from_numpy(w).to(DEV) for w in host["W"]])
+    pts = torch.rand((4, n), generator=g, device=DEV) * 2 - 1
+    df = torch.randn(n, generator=g, device=DEV)
+    grad = lambda x, d: A().apmg_variant_backward(model, x, d, want_dF=False, want_dW=False)[1]
+    assert (-(-n // (256 * points)), M, 1) in kernel_grids(lambda: grad(pts, df))
+    # the float64 sums of the same float32 terms: those of the two halves add up to the whole
+    h = n // 2
+    parts = grad(pts[:, :h].contiguous(), df[:h].contiguous()) + grad(pts[:, h:].contiguous(), df[h:].contiguous())
+    whole = grad(pts, df)
+    assert (whole - parts).norm() <= 1e-10 * whole.norm()

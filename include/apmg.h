@@ -201,13 +201,15 @@ apmg_status apmg_backward(const apmg_model* model, const float* pts, int64_t ld,
  * F32 or BF16 (APMG_EUNSUPPORTED otherwise).  From 2^15 points on the forward sorts the
  * points into spatial bins first and its tiles walk that order, as apmg_forward does (each
  * value is the same either way).  The backward first sorts the points into spatial bins (as
- * apmg_backward does).  Hash grids: a level of at most four vertices per point (and, when
- * hashed, of at most 1023 cells per axis and no more vertices per row than table entries,
- * both rounded up to powers of two from 64) is gathered per block of cells as apmg_backward
- * gathers dF, and the vertices of each entry are added, in a fixed order; the table gradient
- * of other levels is added with float atomics (a run of sorted points in one cell is summed
+ * apmg_backward does).  Hash grids, from 4096 points on: a level of at most four vertices per
+ * point (and, when hashed, of at most 1023 cells per axis and no more vertices per row than
+ * table entries, both rounded up to powers of two from 64) is gathered per block of cells as
+ * apmg_backward gathers dF, and the vertices of each entry are added, in a fixed order; the
+ * workspace holds the block sums of the largest such level, 1 KiB for every 7 x 3 x 3 cells
+ * or part of them and adaptive grid.  The table gradient of other levels, and of smaller
+ * batches, is added with float atomics (a run of sorted points in one cell is summed
  * in registers and added once) and is reproducible to rounding only.  4-D grids
- * with up to 513 time vertices: a further stable sort by time cell, then the grid gradient is
+ * with up to 513 time vertices: a further stable sort by time cell (beyond one), then the grid gradient is
  * gathered per (time cell, block of grid cells) as apmg_backward gathers dF, in a fixed order
  * (bitwise reproducible); with more it is added with atomics as for the hash grids.  dW and dG
  * (float64 per block, fixed order) are as in apmg_backward.

@@ -1706,17 +1706,17 @@ apmg_status apmg_variant_backward(const apmg_model* m, const apmg_encoder* e, co
   sa.pts = bpts; sa.ld = n; sa.n = n;
   sa.tau = w.tau;
   sa.dY = w.dY;
-  // hash tables, level by level: the block gather's vertex sums folded into the entries, or the
-  // atomic scatter
+  // hash tables: the levels left to the atomic scatter in one launch, the others one by one, the
+  // block gather's vertex sums folded into the entries
   if (dF && e->kind == APMG_ENC_HASH) {
     const size_t T = (size_t)ea.tmask + 1u;
+    sa.dF = dF;
+    for (int k = 0; k < s.L; ++k)
+      if (!hash_level_pull(ea, enc_level_res(ea, k), n)) sa.lev[sa.nlev++] = k;
+    if (sa.nlev > 0 && launch_enc_scatter(sa, e->kind, mt * sa.nlev, st) != hipSuccess) return APMG_EHIP;
     for (int k = 0; k < s.L; ++k) {
       const int N = enc_level_res(ea, k);
-      if (!hash_level_pull(ea, N, n)) {
-        sa.dF = dF; sa.g0 = k; sa.gs = s.L;
-        if (launch_enc_scatter(sa, e->kind, mt, st) != hipSuccess) return APMG_EHIP;
-        continue;
-      }
+      if (!hash_level_pull(ea, N, n)) continue;
       CellArgs c;
       memset(&c, 0, sizeof(c));
       c.s = hash_level_shape(s, ea, k); c.G = Gc;
@@ -1754,7 +1754,7 @@ apmg_status apmg_variant_backward(const apmg_model* m, const apmg_encoder* e, co
   }
   if (dF && !pull && e->kind == APMG_ENC_TIME) {
     // by the scatter, into the caller's dF or a channel-last buffer then laid out in the paper's order
-    sa.dF = w.dFcl ? w.dFcl : dF; sa.g0 = 0; sa.gs = 1;
+    sa.dF = w.dFcl ? w.dFcl : dF; sa.nlev = 1;
     if (w.dFcl) hipLaunchKernelGGL(k_fill_f32, dim3(grid1(nF)), dim3(256), 0, st, w.dFcl, nF, 0.f);
     if (launch_enc_scatter(sa, e->kind, s.M, st) != hipSuccess) return APMG_EHIP;
     if (w.dFcl) {

@@ -9,8 +9,8 @@
 // vertices until its vertices are mapped to entries, so its vertex sums come from the block
 // gather of the dense grids (k_block_pull), and the vertices of an entry are then added
 // (k_lattice_to_table, k_lattice_to_hash): no atomics, a fixed order.  Levels with many more
-// vertices than the batch has points (or a table smaller than a row of vertices) take the
-// scatter instead (k_enc_scatter): w_q dL/dy_c added to the corner entries with float atomics,
+// vertices than the batch has points (or a table smaller than a row of vertices), and all levels
+// of a small batch, take the scatter instead (k_enc_scatter): w_q dL/dy_c added to the corner entries with float atomics,
 // where each wave first sums the runs of lanes with the same cell and only the run's first
 // lane issues the atomics; those sums are reproducible to rounding only.  The 4-D grids take
 // the block gather per time cell, or the scatter beyond 513 time vertices.  The transform
@@ -28,7 +28,7 @@ struct EncScatterArgs {
   const float* tau;        // time: [n] time of each point
   const float* dY;         // [M][n][C], dL/dy per feature grid (M feature grids)
   float* dF;               // scatter: same layout as F (channel-last for time), accumulated
-  int g0, gs;              // scatter: feature grid of block row y is g0 + gs y
+  int nlev, lev[kMaxLevels];   // scatter: block row y is level lev[y % nlev] of adaptive grid y / nlev
   double* dGpart;          // transform gradient: [M][nbx][12]
   int nbx;                 // point blocks per feature grid, of 256 tgp points
   int tgp;
@@ -96,7 +96,7 @@ __device__ inline float run_sum(float v, const WaveRuns& r) {
 template <int C, int ENC>
 __global__ void __launch_bounds__(256) k_enc_scatter(EncScatterArgs a) {
   const Shape s = a.s;
-  const int g = a.g0 + a.gs * blockIdx.y;
+  const int g = (int)(blockIdx.y / a.nlev) * s.L + a.lev[blockIdx.y % a.nlev];
   const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const bool valid = p < a.n;
   float x = 0.f, y = 0.f, z = 0.f, tq = 0.f;
@@ -375,7 +375,7 @@ __global__ void k_cl_to_paper(int64_t nm, int64_t V, const float* __restrict__ s
   }
 }
 
-// rows: feature grids g0, g0 + gs, ...
+// rows: adaptive grids times levels taken
 hipError_t launch_enc_scatter(const EncScatterArgs& a, int enc, int rows, hipStream_t st) {
   const dim3 grid((unsigned)((a.n + 255) / 256), (unsigned)rows);
   if (a.s.C != 2) return hipErrorInvalidValue;
@@ -393,12 +393,17 @@ hipError_t launch_enc_transform_grad(const EncScatterArgs& a, int enc, hipStream
   return hipGetLastError();
 }
 
-// A hash level takes the block gather (k_block_pull + k_lattice_to_table / k_lattice_to_hash)
-// while its vertices are at most four per point: the lattices then stay within 64 bytes per
-// point and grid, and a block of 63 cells has points enough to pay for finding its candidates.
+// A hash level takes the block gather (k_block_pull + k_lattice_to_table / k_lattice_to_hash) while
+// its vertices are at most four per point: its lattices then stay small next to dL/dy and a block of
+// 63 cells has points enough to pay for finding its candidates.  (A block stores 1 KiB for up to 63
+// cells: N = 128 at four vertices a point takes 67 bytes per point and grid, N = 8 about 100.)
 // A hashed level's rows also have to fit one aligned run of entries of the table, and a
 // workgroup's registers (at most 1024 entries a run).  Measured at 2^20 points, 8 grids: the
 // gather and fold of N = 16 / 32 / 64 / 128 take 0.13 / 0.10 / 0.17 / 0.54 ms, the atomics 2.5 ms per level.
+// Below kHashPullMin points the two launches a level are the cost (20 and 5 us each) and the
+// atomics of all levels, one launch, the better: 4 grids of 3 levels, dL/dtheta alone, 1024 points
+// 200 us with the atomics and 221 with the gather; 4096 points 161 and 160; 16384 points 286 and 155.
+constexpr int64_t kHashPullMin = 4096;
 inline int hash_run_log2(int N) {   // log2 of B, the power of two >= N + 1 and >= 64
   int b = 6;
   while ((1 << b) < N + 1) ++b;
@@ -408,7 +413,7 @@ inline bool hash_level_dense(const EncArgs& e, int N) {
   return (uint64_t)(N + 1) * (N + 1) * (N + 1) <= (uint64_t)e.tmask + 1u;
 }
 inline bool hash_level_pull(const EncArgs& e, int N, int64_t n) {
-  if ((double)(N + 1) * (N + 1) * (N + 1) > 4.0 * (double)n) return false;
+  if (n < kHashPullMin || (double)(N + 1) * (N + 1) * (N + 1) > 4.0 * (double)n) return false;
   const int b = hash_run_log2(N);
   return hash_level_dense(e, N) || (b <= 10 && (1u << b) <= e.tmask + 1u);
 }

@@ -129,3 +129,24 @@ def test_transform_gradient_blocks(n, points):
     parts = grad(pts[:, :h].contiguous(), df[:h].contiguous()) + grad(pts[:, h:].contiguous(), df[h:].contiguous())
     whole = grad(pts, df)
     assert (whole - parts).norm() <= 1e-10 * whole.norm()
+
+
+# 3 levels (of 9^3 and 13^3 entries, and one hashed): the atomics take one launch for all the levels
+# that are left to them, the gather two per level from 4096 points on
+@pytest.mark.parametrize("n,res,gathered", [(100, (8, 12, 40), 0), (4095, (8, 12, 40), 0), (4096, (8, 12, 40), 2),
+                                            (4096, (30, 40, 50), 0), (20000, (8, 12, 40), 3)])
+def test_hash_levels_share_the_scatter(n, res, gathered):
+    host = synth.init_model(2, 2, 4, [12, 64, 64, 1], seed=1, grid_range=0.3)
+    g = torch.Generator(device=DEV).manual_seed(n)
+    F = torch.rand((2, 3, 1 << 12, 2), generator=g, device=DEV) - 0.5
+    model = A().VariantModel(A().ENC_HASH, torch.from_numpy(host["G"]).to(DEV)[:2], F,
+                             [torch.from_numpy(w).to(DEV) for w in host["W"]], level_res=res)
+    pts = torch.rand((3, n), generator=g, device=DEV) * 2 - 1
+    df = torch.randn(n, generator=g, device=DEV)
+    none = launches(lambda: A().apmg_variant_backward(model, pts, df, want_dF=False, want_dG=False))
+    grad = lambda: A().apmg_variant_backward(model, pts, df, want_dG=False)
+    # (the table gradient is cleared first)
+    assert launches(grad) == none + 1 + 2 * gathered + (1 if gathered < 3 else 0)
+    # the scatter adds a float32 term per corner: 1e-6 normwise between two orders
+    a, b = grad()[0].double(), grad()[0].double()
+    assert (a - b).norm() <= 1e-6 * a.norm()

@@ -370,29 +370,37 @@ hipError_t launch_step_sort(uint64_t seed, const uint64_t* step_ctr, uint32_t st
 struct CellWs { float *dY, *CC; double* dGpart; };
 inline int64_t n_cells(const Shape& s) { return (int64_t)(s.R - 1) * (s.R - 1) * (s.R - 1); }
 inline int cell_blocks(const Shape& s) { return (int)((n_cells(s) + 255) / 256); }
-// The block gather gives a block of cells to one wave, or to the four waves of a workgroup where
-// that many waves are needed to fill the device: few blocks (below two waves per SIMD) with
-// enough points each that a quarter of them is still several 64-candidate steps.  The rule looks
-// at one model alone, so a model's sums do not depend on the batch it is stepped in.
-inline bool pull_split(const Shape& s, int64_t n) {
+// The block gather gives a block of cells to one wave, or to the four waves of a workgroup, which
+// then each pay for the block's set-up (about that of 100 candidates) and share its candidates.
+// Sharing evens out and fills the device's rounds of waves, which matters the less the more blocks
+// there are: it pays from some 500 points per block for a thousand blocks in all, from 800 for 4000,
+// and from 2000 for 8000 to 16384 (beyond, the one wave).  The adjoint alone with the transform
+// gradient, one wave -> four, in us: 16 grids at 16^3 x 2 (1200 blocks), 65,536 points 131 -> 122,
+// 2^20 points 1149 -> 738; 16 at 30^3 x 2 (8000), 2^17 points 167 -> 215, 2^20 points 779 -> 767;
+// 32 at 32^3 x 1 (11616), 2^18 points 351 -> 381, 2^20 points 1120 -> 1003.  In a training step
+// (step) the density passes run beside it and other models fill the device: from 1024 points on (16
+// models of 16 grids at 16^3 x 2, 65,536 points, with the transform gradient: 641 us with one wave,
+// 787 with four; one model 149 and 154).  The rule looks at one model alone, so a model's sums do
+// not depend on the batch it is stepped in.
+inline bool pull_split(const Shape& s, int64_t n, bool step = false) {
   const int64_t nblk = pull_blocks(s.R, s.C).total();
-  return nblk * s.M < 8192 && n >= 256 * nblk;
+  return nblk * s.M < 16384 && n >= (step ? 1024 : 512) * nblk && 6 * n >= nblk * nblk * s.M;
 }
 // workgroups per grid of the block gather (four waves each)
-inline int pull_groups(const Shape& s, int64_t n) {
+inline int pull_groups(const Shape& s, int64_t n, bool step = false) {
   const int64_t nblk = pull_blocks(s.R, s.C).total();
-  return (int)(pull_split(s, n) ? nblk : (nblk + 3) / 4);
+  return (int)(pull_split(s, n, step) ? nblk : (nblk + 3) / 4);
 }
 // transform-gradient partials per grid written by the gather cell_kernel selects
-inline int dg_parts(const Shape& s, int64_t n, int cell_kernel) {
-  return cell_kernel != 1 ? pull_groups(s, n) : cell_blocks(s);
+inline int dg_parts(const Shape& s, int64_t n, bool step, int cell_kernel) {
+  return cell_kernel != 1 ? pull_groups(s, n, step) : cell_blocks(s);
 }
-void take_cell(Carver& cv, const Shape& s, int64_t n, int nb, CellWs* o) {
+void take_cell(Carver& cv, const Shape& s, int64_t n, int nb, bool step, CellWs* o) {
   o->dY = cv.take<float>((size_t)nb * s.M * std::max<int64_t>(n, 1) * s.C);
   // corner sums per cell (the per-cell gather) or vertex lattices per cell block (the block gather)
   const int64_t lat = pull_blocks(s.R, s.C).total() * pull_lat(s.C);
   o->CC = cv.take<float>((size_t)nb * s.M * std::max<int64_t>(n_cells(s) * 8, lat) * s.C);
-  o->dGpart = cv.take<double>((size_t)nb * s.M * std::max(cell_blocks(s), pull_groups(s, n)) * 12);
+  o->dGpart = cv.take<double>((size_t)nb * s.M * std::max(cell_blocks(s), pull_groups(s, n, step)) * 12);
 }
 
 // timing hooks: [0] the adjoint tile kernel, [1] the grid-gradient gather
@@ -408,8 +416,8 @@ void prof_end(hipStream_t st, int k) {
 hipError_t launch_cells(const Shape& s, bool gf16, const float* G, size_t G_stride, const void* F, size_t F_stride,
                         const SortWs& sw, int64_t n, const CellWs& cw, float* dF, size_t dF_stride, int dF_paper,
                         int accumulate, bool want_dG, double* dG, size_t dG_stride, int dG_rows, int dG_accumulate, int nb,
-                        const int32_t* active, hipStream_t st, int unroll = 4, const int32_t* dG_active = nullptr,
-                        int cell_kernel = 0) {
+                        const int32_t* active, hipStream_t st, bool step, int unroll = 4,
+                        const int32_t* dG_active = nullptr, int cell_kernel = 0) {
   CellArgs c;
   memset(&c, 0, sizeof(c));
   c.s = s; c.G = G; c.G_stride = G_stride; c.F = F; c.F_stride = F_stride;
@@ -426,9 +434,9 @@ hipError_t launch_cells(const Shape& s, bool gf16, const float* G, size_t G_stri
     else if (unroll == 8) hipLaunchKernelGGL((k_cell_pull<CC_, F16_, DG_, 8>), grid, dim3(256), 0, st, c); \
     else hipLaunchKernelGGL((k_cell_pull<CC_, F16_, DG_, 4>), grid, dim3(256), 0, st, c);           \
   }
-  const int64_t wgroups = (int64_t)pull_groups(s, n) * s.M * nb;
+  const int64_t wgroups = (int64_t)pull_groups(s, n, step) * s.M * nb;
   if (wgroups > 0x7fffffff) return hipErrorInvalidValue;
-  const bool wave_kernel = cell_kernel != 1, split = pull_split(s, n);
+  const bool wave_kernel = cell_kernel != 1, split = pull_split(s, n, step);
 #define APMG_WAVE(CC_, F16_, DG_)                                                                   \
   {                                                                                                 \
     const dim3 wg((unsigned)wgroups);                                                               \
@@ -455,7 +463,7 @@ hipError_t launch_cells(const Shape& s, bool gf16, const float* G, size_t G_stri
 #undef APMG_WAVE
 #undef APMG_PULL
   if (dG)
-    hipLaunchKernelGGL(k_reduce_cell_dG, dim3(s.M, nb), dim3(256), 0, st, cw.dGpart, s.M, dg_parts(s, n, cell_kernel), dG,
+    hipLaunchKernelGGL(k_reduce_cell_dG, dim3(s.M, nb), dim3(256), 0, st, cw.dGpart, s.M, dg_parts(s, n, step, cell_kernel), dG,
                        dG_stride, dG_rows, dG_accumulate, dG_active ? dG_active : active);
   return hipGetLastError();
 }
@@ -479,7 +487,7 @@ size_t bwd_ws(const Shape& s, const apmg_model* m, int64_t n, void* ws, BwdWs* o
   w.f.w3s = cv.take<float>(s.H);
   w.part = cv.take<double>((size_t)bwd_blocks(n, bf) * max_part_len(s, bf));
   take_sort(cv, n, 1, true, &w.srt);
-  take_cell(cv, s, n, 1, &w.cell);
+  take_cell(cv, s, n, 1, false, &w.cell);
   w.act = nullptr;
   w.gpart = nullptr;
   if (act_path(s, bf)) {
@@ -628,7 +636,7 @@ size_t step_ws(const apmg_batch* b, const Shape& s, void* ws, StepWs* o) {
   w.live = cv.take<int32_t>((size_t)nb);
   w.dlive = cv.take<int32_t>((size_t)nb);
   take_sort(cv, b->n, nb, false, &w.srt);
-  take_cell(cv, s, b->n, nb, &w.cell);
+  take_cell(cv, s, b->n, nb, true, &w.cell);
   w.act = nullptr;
   w.gpart = nullptr;
   if (act_path(s, bf)) {
@@ -918,7 +926,7 @@ apmg_status apmg_backward(const apmg_model* m, const float* pts, int64_t ld, int
   hipError_t ec = hipSuccess;
   if (want_cells)
     ec = launch_cells(s, gf16, Gc, 0, Fc, 0, w.srt, n, w.cell, dF, 0, paper_grids(m) ? 1 : 0, acc ? 1 : 0,
-                      dG != nullptr, dG, 0, grows, acc ? 1 : 0, 1, nullptr, st);
+                      dG != nullptr, dG, 0, grows, acc ? 1 : 0, 1, nullptr, st, false);
   hipError_t ej = hipSuccess;
   if (pst != st) {
     ej = hipEventRecord(side->join, pst);
@@ -1214,7 +1222,7 @@ apmg_status run_step(const apmg_batch* b, const Shape& s, void* ws, const Tune& 
     reduce_part(dst);
     if (use_act) act_products(dst);
     const hipError_t ec = launch_cells(s, gf16, b->G, nG, Fg, nF, w.srt, n, w.cell, w.dF, nF, paper ? 1 : 0, 0,
-                                       rec_dG, nullptr, 0, 3, 0, nb, w.live, st, tu.cell_unroll, nullptr,
+                                       rec_dG, nullptr, 0, 3, 0, nb, w.live, st, true, tu.cell_unroll, nullptr,
                                        tu.cell_kernel);
     hipError_t ej = hipSuccess;
     if (dst != st) {
@@ -1224,7 +1232,7 @@ apmg_status run_step(const apmg_batch* b, const Shape& s, void* ws, const Tune& 
     if (ed != hipSuccess || ec != hipSuccess || ej != hipSuccess) return APMG_EHIP;
     if (rec_dG)
       hipLaunchKernelGGL(k_reduce_cell_dG, dim3(s.M, nb), dim3(256), 0, st, w.cell.dGpart, s.M,
-                         dg_parts(s, n, tu.cell_kernel), w.dG, nG, 3, 1, w.dlive);
+                         dg_parts(s, n, true, tu.cell_kernel), w.dG, nG, 3, 1, w.dlive);
   }
   if (!update) return hip_status(hipGetLastError());
 

@@ -402,7 +402,7 @@ hipError_t launch_enc_transform_grad(const EncScatterArgs& a, int enc, hipStream
 // gather and fold of N = 16 / 32 / 64 / 128 take 0.13 / 0.10 / 0.17 / 0.54 ms, the atomics 2.5 ms per level.
 // Below kHashPullMin points the two launches a level are the cost (20 and 5 us each) and the
 // atomics of all levels, one launch, the better: 4 grids of 3 levels, dL/dtheta alone, 1024 points
-// 200 us with the atomics and 221 with the gather; 4096 points 161 and 160; 16384 points 286 and 155.
+// 183 us with the atomics and 222 with the gather; 4096 points 162 and 160; 16384 points 285 and 155.
 constexpr int64_t kHashPullMin = 4096;
 inline int hash_run_log2(int N) {   // log2 of B, the power of two >= N + 1 and >= 64
   int b = 6;

@@ -150,3 +150,25 @@ def test_hash_levels_share_the_scatter(n, res, gathered):
     # the scatter adds a float32 term per corner: 1e-6 normwise between two orders
     a, b = grad()[0].double(), grad()[0].double()
     assert (a - b).norm() <= 1e-6 * a.norm()
+
+
+# four waves share a block of cells (a workgroup per block instead of per four) where the points per
+# block pay for the set-up of each: the more the more blocks, and from twice as many in a step
+@pytest.mark.parametrize("M,C,R,n,step,groups", [
+    (16, 2, 16, 75 * 512 - 1, False, 19), (16, 2, 16, 75 * 512, False, 75),
+    (16, 2, 16, 75 * 1024 - 1, True, 19), (16, 2, 16, 75 * 1024, True, 75),
+    (16, 2, 30, 1 << 17, False, 125), (16, 2, 30, 666667, False, 500), (16, 2, 30, 1 << 17, True, 125),
+    (32, 1, 32, 1 << 18, False, 91), (32, 1, 32, 1 << 20, False, 363), (32, 2, 32, 1 << 21, False, 152),
+])
+def test_gather_waves_per_block(M, C, R, n, step, groups):
+    host = synth.init_model(M, C, R, [M * C, 64, 64, 1], seed=M, grid_range=0.3)
+    if step:
+        vol = synth.make_volume("blobs_sine", (24, 24, 24)).to(DEV)
+        tr = A().Trainer([host], vol, A().apmg_make_bricks(24, 24, 24, 24, 0)[1], n)
+        call = tr.step
+    else:
+        model = A().Model.from_host(host, DEV)
+        pts = torch.rand((3, n), device=DEV) * 2 - 1
+        df = torch.full((n,), 1.0 / n, device=DEV)
+        call = lambda: A().apmg_backward(model, pts, df, want_dG=False, want_dW=False)
+    assert (groups * M, 1, 1) in kernel_grids(call)

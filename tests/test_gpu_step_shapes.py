@@ -47,3 +47,24 @@ def test_default_tile_blocks_match_one_block(nb, bf16):
         out.append([t.cpu().numpy() for t in (tr.losses, tr.mF, tr.mW, tr.mG)])
     for name, a, b in zip(("losses", "mF", "mW", "mG"), *out):
         assert_close(name, a, b)
+
+
+# 4 blocks of cells a grid: one wave a block below 1024 points per block, four from there on
+@pytest.mark.parametrize("C", [1, 2, 4])
+@pytest.mark.parametrize("n", [4095, 4096, 20001])
+def test_step_gathers_agree_on_both_sides_of_the_split(C, n):
+    vol = synth.make_volume("blobs_sine", (24, 24, 48)).to(DEV)
+    _, bricks = A().apmg_make_bricks(48, 24, 24, 24, 0)
+    hosts = [synth.init_model(3, C, 6, [3 * C, 64, 64, 1], seed=b, grid_range=0.3) for b in range(2)]
+    out = []
+    for tuning in ({"cell_kernel": 2}, {"cell_kernel": 1}, {"cell_kernel": 1, "cell_group": 8}):
+        tr = A().Trainer(hosts, vol, bricks, n, tuning=tuning, flags=A().ADD_REC_DG)
+        tr.density_active.fill_(1)
+        tr.step()
+        torch.cuda.synchronize()
+        out.append([t.clone() for t in (tr.mF, tr.mG, tr.mW, tr.losses)])
+    cells, blocks, group = out
+    assert all(torch.equal(a, b) for a, b in zip(blocks, group))   # the lanes per run have no effect
+    assert torch.equal(cells[2], blocks[2]) and torch.equal(cells[3], blocks[3])
+    for a, b in zip(cells[:2], blocks[:2]):
+        assert (a - b).norm() <= 1e-5 * b.norm()

@@ -121,9 +121,10 @@ int device_cus() {
   return cus;
 }
 // apmg_backward: one round of the adjoint kernel's blocks (one per CU), at most one per 4 tiles.
-// (two rounds when the tiled adjoint runs four-wave blocks, two per CU)
-int bwd_blocks(int64_t n, bool bf) {
-  const int cap = adjoint_waves(0, bf) == 4 ? 2 * device_cus() : device_cus();
+// (two per CU where blocks of four waves run two on a CU: the tiled adjoint's, and (act) those of
+// the activation path for either dtype)
+int bwd_blocks(int64_t n, bool act, bool bf) {
+  const int cap = act || adjoint_waves(0, bf) == 4 ? 2 * device_cus() : device_cus();
   return std::max(1, std::min(tile_blocks(n), cap));
 }
 int step_default_blocks(int64_t n, int nb) {
@@ -153,13 +154,14 @@ int step_rule_blocks(int64_t n, int nb, int waves) {
   }
   return (int)best;
 }
-bool resolve_tune(const apmg_tuning* t, int64_t n, int nb, bool bf, Tune* out) {
+bool resolve_tune(const apmg_tuning* t, int64_t n, int nb, bool act, bool bf, Tune* out) {
   out->cell_unroll = 4;
   out->cell_kernel = 0;
   out->adjoint = 0;
-  // (the one-wave-per-SIMD kernel, adjoint 3, also runs one four-wave block per compute unit)
+  // (the one-wave-per-SIMD kernel, adjoint 3, also runs one four-wave block per compute unit; the
+  // activation path has four-wave blocks, two per compute unit)
   const auto rule = [&]() {
-    const int waves = out->adjoint < 3 ? adjoint_waves(out->adjoint, bf) : 8;
+    const int waves = act ? 4 : out->adjoint < 3 ? adjoint_waves(out->adjoint, bf) : 8;
     out->tile_blocks = step_rule_blocks(n, nb, waves);
   };
   if (!t) {
@@ -485,7 +487,7 @@ size_t bwd_ws(const Shape& s, const apmg_model* m, int64_t n, void* ws, BwdWs* o
   take_ops(cv, s, 1, g_rows(m) == 4, paper_grids(m), m->grid_dtype == APMG_F16, &w.ops);
   w.f.swz = cv.take<char>(swz_sizes(s).total() * esz);
   w.f.w3s = cv.take<float>(s.H);
-  w.part = cv.take<double>((size_t)bwd_blocks(n, bf) * max_part_len(s, bf));
+  w.part = cv.take<double>((size_t)bwd_blocks(n, act_path(s, bf), bf) * max_part_len(s, bf));
   take_sort(cv, n, 1, true, &w.srt);
   take_cell(cv, s, n, 1, false, &w.cell);
   w.act = nullptr;
@@ -861,7 +863,7 @@ apmg_status apmg_backward(const apmg_model* m, const float* pts, int64_t ld, int
   if (e != hipSuccess) return APMG_EHIP;
   e = launch_swizzle(s, bf, m->W[0], m->W[1], m->W[2], 0, w.f.swz, 0, w.f.w3s, 1, st);
   if (e != hipSuccess) return APMG_EHIP;
-  const int nblk = bwd_blocks(n, bf);
+  const int nblk = bwd_blocks(n, use_act, bf);
   const bool want_cells = dF || dG;
   const int kb = (!use_act && passes.size() == 1) ? register_kb(s) : 0;
   for (const Pass& ps : passes) {
@@ -1253,7 +1255,8 @@ extern "C" apmg_status apmg_batched_step(const apmg_batch* b, void* ws, size_t w
   apmg_status rc = check_batch(b, &s);
   if (rc != APMG_OK) return rc;
   Tune tu;
-  if (!resolve_tune(b->tuning, b->n, b->nb, b->shape.mlp_dtype == APMG_BF16, &tu)) return APMG_EINVAL;
+  const bool bf = b->shape.mlp_dtype == APMG_BF16;
+  if (!resolve_tune(b->tuning, b->n, b->nb, act_path(s, bf), bf, &tu)) return APMG_EINVAL;
   if (!ws || ws_bytes < step_ws(b, s, nullptr, nullptr)) return APMG_EWORKSPACE;
   return run_step(b, s, ws, tu, true, st);
 }
@@ -1540,7 +1543,7 @@ size_t var_ws(const Shape& s, const EncArgs& ea, const apmg_model* m, const apmg
     w.fsorted = true;
   }
   if (backward) {
-    w.part = cv.take<double>((size_t)bwd_blocks(n, bf) * part_layout(s, s.MC, s.H).len);
+    w.part = cv.take<double>((size_t)bwd_blocks(n, false, bf) * part_layout(s, s.MC, s.H).len);
     w.dY = cv.take<float>((size_t)s.M * std::max<int64_t>(n, 1) * s.C);
     w.dGpart = cv.take<double>((size_t)s.M * tg_blocks(n, s.M) * 12);
     if (time_paper && !time_sorted(ea)) w.dFcl = cv.take<float>(variant_f_elems(s, ea, e->kind));
@@ -1688,7 +1691,7 @@ apmg_status apmg_variant_backward(const apmg_model* m, const apmg_encoder* e, co
     hipLaunchKernelGGL(k_gather_f32, dim3(grid1(n)), dim3(256), 0, st, pts + 3 * ld, w.srt.v0, n, w.tau);
   }
   const bool want_enc = dF || dG;
-  const int nblk = bwd_blocks(n, bf);
+  const int nblk = bwd_blocks(n, false, bf);
   const PartLayout pl = part_layout(s, s.MC, s.H);
   TileArgs a;
   memset(&a, 0, sizeof(a));

@@ -172,3 +172,17 @@ def test_gather_waves_per_block(M, C, R, n, step, groups):
         df = torch.full((n,), 1.0 / n, device=DEV)
         call = lambda: A().apmg_backward(model, pts, df, want_dG=False, want_dW=False)
     assert (groups * M, 1, 1) in kernel_grids(call)
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+def test_activation_path_runs_two_blocks_per_compute_unit(bf16):
+    # H = 128: blocks of four waves, two on each of the 256 compute units (512 blocks of 4 tiles here)
+    n, mlp = 1 << 16, A().BF16 if bf16 else A().F32
+    host = synth.init_model(9, 2, 6, [18, 128, 128, 1], seed=1, grid_range=0.3)
+    model = A().Model.from_host(host, DEV, mlp_dtype=mlp)
+    pts = torch.rand((3, n), device=DEV) * 2 - 1
+    df = torch.full((n,), 1.0 / n, device=DEV)
+    assert (512, 1, 1) in kernel_grids(lambda: A().apmg_backward(model, pts, df))
+    vol = synth.make_volume("blobs_sine", (24, 24, 24)).to(DEV)
+    tr = A().Trainer([host], vol, A().apmg_make_bricks(24, 24, 24, 24, 0)[1], n, mlp_dtype=mlp)
+    assert (512, 1, 1) in kernel_grids(tr.step)

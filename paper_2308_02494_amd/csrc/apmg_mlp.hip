@@ -138,6 +138,15 @@ template <int C> struct GridTap<C, kEncTime> {
   bool in;
 };
 
+// Bytes of one model's dense grids, for a resource's 32-bit size (grids of 2 GiB and more have it in
+// the upper half of the unsigned range).
+__host__ __device__ constexpr uint32_t grid_bytes(int M, int C, int R, int esz) {
+  const uint32_t r = (uint32_t)R;
+  return (uint32_t)M * (uint32_t)C * (uint32_t)esz * r * r * r;
+}
+static_assert(grid_bytes(2, 4, 511, 4) == 4269850592u && grid_bytes(250, 1, 200, 2) == 4000000000u,
+              "no overflow for grids of 2 to 4 GiB");
+
 // The grids of one model: a buffer resource, or a pointer (grids past a resource's 4 GiB, the
 // encoder variants, and one-channel binary16 grids, see enc_tap).
 template <int ENC> struct GridSrc {
@@ -148,7 +157,7 @@ template <> struct GridSrc<kEncDense> {
   __amdgpu_buffer_rsrc_t r;
   const void* F;
   __device__ inline GridSrc(const Shape& s, const void* f, int esz)
-      : r(__builtin_amdgcn_make_buffer_rsrc((void*)f, (short)0, s.M * s.C * s.R * s.R * s.R * esz, kBufferRsrcWord3)),
+      : r(__builtin_amdgcn_make_buffer_rsrc((void*)f, (short)0, grid_bytes(s.M, s.C, s.R, esz), kBufferRsrcWord3)),
         F(f) {}
 };
 // whether the dense grids of one model take the buffer resource

@@ -150,3 +150,57 @@ def test_grids_of_four_gib(M, C, R, dtype):
     ((Wd[2] @ h)[0] * 3.0 * df.double()).sum().backward()     # the output's scale: vmax - vmin
     for got, want in zip(dW, Wd):
         assert (got.double() - want.grad).norm() <= 1e-3 * want.grad.norm()
+
+
+@pytest.mark.parametrize("R,H", [(511, 64), (512, 64), (511, 128), (512, 128)])
+def test_gradients_of_four_gib_grids(R, H):
+    # 2 grids of R^3 x 4 in float32, below and at 4 GiB, with the narrow and the wide (activation path)
+    # decoder: every gradient against float64 from the float32 cell decision and offsets.  Points whose
+    # hidden units lie within 1e-4 of a kink have dL/df = 0, so no ReLU turns; the rest are the float32
+    # bars, 1e-5 normwise
+    M, C, n = 2, 4, 20000
+    g = torch.Generator(device=DEV).manual_seed(R + H)
+    F = torch.empty((M, R, R, R, C), device=DEV).normal_(generator=g)
+    G = torch.zeros((M, 3, 4), device=DEV)
+    for m in range(M):
+        G[m, :, :3] = torch.eye(3, device=DEV) * (0.97 - 0.1 * m)
+        G[m, :, 3] = 0.01
+    W = [torch.randn(s, generator=g, device=DEV) / s[1] ** 0.5 for s in ((H, M * C), (H, H), (1, H))]
+    model = A().Model(G, F, W, -1.0, 2.0, A().F32, A().GRIDS_MRRRC)
+    x = torch.rand((3, n), generator=g, device=DEV) * 2 - 1
+    fma = lambda a, b, c: (a.double() * b.double() + c.double()).float()
+    G64, W64 = G.double().requires_grad_(), [w.double().requires_grad_() for w in W]
+    feats, corners, weights = [], [], []
+    for m in range(M):
+        g4, hr = G[m], torch.tensor(0.5 * (R - 1), device=DEV)
+        loc = torch.stack([fma(g4[d, 2], x[2], fma(g4[d, 1], x[1], fma(g4[d, 0], x[0], g4[d, 3]))) for d in range(3)])
+        inside = ((loc >= -1) & (loc <= 1)).all(0)
+        u = fma(loc, hr, hr)
+        i0 = u.floor().clamp(0, R - 2)
+        u64 = (G64[m, :, :3] @ x.double() + G64[m, :, 3:] + 1) * (0.5 * (R - 1))
+        w, i0 = (u - i0).double() + (u64 - u64.detach()), i0.long()     # the float32 offsets, with a gradient
+        e = 0.0
+        for q in range(8):
+            b = [(q >> d) & 1 for d in range(3)]
+            wq = torch.stack([w[d] if b[d] else 1 - w[d] for d in range(3)]).prod(0) * inside
+            v = ((i0[2] + b[2]) * R + i0[1] + b[1]) * R + i0[0] + b[0]
+            e = e + wq * F[m].view(-1, C)[v].double().T
+            corners.append(v)
+            weights.append(wq.detach())
+        feats.append(e)
+    y = torch.cat(feats)
+    y.retain_grad()
+    z1 = W64[0] @ y
+    z2 = W64[1] @ torch.relu(z1)
+    near = torch.minimum(z1.abs().min(0).values, z2.abs().min(0).values) < 1e-4
+    df = torch.where(near, 0.0, torch.randn(n, generator=g, device=DEV))
+    ((W64[2] @ torch.relu(z2))[0] * 3.0 * df.double()).sum().backward()
+    dF, dG, dW = A().apmg_backward(model, x, df)
+    for got, want in zip(dW, W64):
+        assert (got.double() - want.grad).norm() <= 1e-5 * want.grad.norm()
+    assert (dG - G64.grad).norm() <= 1e-5 * G64.grad.norm()
+    for m in range(M):
+        want = torch.zeros((R ** 3, C), dtype=torch.float64, device=DEV)
+        for v, wq in zip(corners[8 * m:8 * m + 8], weights[8 * m:8 * m + 8]):
+            want.index_add_(0, v, (wq * y.grad[4 * m:4 * m + 4]).T.contiguous())
+        assert (dF[m].view(-1, C).double() - want).norm() <= 1e-5 * want.norm()

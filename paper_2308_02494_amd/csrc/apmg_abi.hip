@@ -24,7 +24,6 @@ struct Carver {
 
 constexpr int kMaxTileBlocks = 512;
 constexpr int kDensBlocks = 1024;
-constexpr size_t kLdsLimit = 160 * 1024;
 
 apmg_status check_model(const apmg_model* m, bool need_params, Shape* out) {
   if (!m) return APMG_EINVAL;
@@ -180,40 +179,6 @@ bool resolve_tune(const apmg_tuning* t, int64_t n, int nb, bool act, bool bf, Tu
   out->adjoint = t->adjoint_kernel;
   if (t->tile_blocks == 0) rule();
   return true;
-}
-
-// Adjoint passes: each accumulates a block of second-layer gradient rows and a slice of
-// first-layer gradient columns in LDS; the first pass also scatters dF, reduces dG and
-// the output-layer gradient.  Chosen so that every pass fits the LDS.
-struct Pass { int c1_lo, c1_hi, w2_lo, w2_hi; bool first; };
-std::vector<Pass> plan_passes(const Shape& s, bool bf, bool want_w) {
-  std::vector<Pass> out;
-  if (!want_w) { out.push_back({0, 0, 0, 0, true}); return out; }
-  int r0 = 0, c0 = 0;
-  while (r0 < s.H || c0 < s.MC) {
-    int r = 0;
-    while (r0 + r + 32 <= s.H && backward_lds_bytes(s, 0, r + 32, bf, 0) <= kLdsLimit) r += 32;
-    int c = 0;
-    if (r0 + r >= s.H) {  // rows done in this pass: give the rest of the budget to columns
-      int lo = 0, hi = s.MC - c0;
-      while (lo < hi) {
-        const int mid = (lo + hi + 1) / 2;
-        if (backward_lds_bytes(s, mid, r, bf, 0) <= kLdsLimit) lo = mid; else hi = mid - 1;
-      }
-      c = lo;
-    }
-    if (r == 0 && c == 0) return {};
-    out.push_back({c0, c0 + c, r0, r0 + r, out.empty()});
-    r0 += r;
-    c0 += c;
-  }
-  return out;
-}
-int max_part_len(const Shape& s, bool bf) {
-  int len = part_layout(s, 0, 0).len;
-  for (const Pass& p : plan_passes(s, bf, true))
-    len = std::max(len, part_layout(s, p.c1_hi - p.c1_lo, p.w2_hi - p.w2_lo).len);
-  return len;
 }
 
 // ---------------------------------------------------------------- model operands
@@ -471,9 +436,13 @@ hipError_t launch_cells(const Shape& s, bool gf16, const float* G, size_t G_stri
 }
 
 // Shapes outside the register-resident adjoint (H != 64 or more than 64 input features) take
-// their weight gradients from stored per-point activations and k_dw_gemm, in one adjoint pass
-// with no LDS accumulators (deterministic, no multi-pass recomputation of the forward).
-bool act_path(const Shape& s, bool bf) { return !(plan_passes(s, bf, true).size() == 1 && register_kb(s) > 0); }
+// their weight gradients from stored per-point activations and k_dw_gemm, with no accumulators
+// in the adjoint kernel.
+bool act_path(const Shape& s) { return register_kb(s) == 0; }
+// doubles of an adjoint block's partial sums: of the weight gradients the kernel accumulates
+inline int adj_part_len(const Shape& s) {
+  return (act_path(s) ? part_layout(s, 0, 0) : part_layout(s, s.MC, s.H)).len;
+}
 inline int64_t act_ld(int64_t n) { return (std::max<int64_t>(n, 1) + 31) / 32 * 32; }
 inline int gemm_chunks(int64_t n) { return (int)((act_ld(n) + kGemmChunk - 1) / kGemmChunk); }
 inline int gemm_part_len(const Shape& s) { return s.H * s.MC + s.H * s.H; }
@@ -487,12 +456,12 @@ size_t bwd_ws(const Shape& s, const apmg_model* m, int64_t n, void* ws, BwdWs* o
   take_ops(cv, s, 1, g_rows(m) == 4, paper_grids(m), m->grid_dtype == APMG_F16, &w.ops);
   w.f.swz = cv.take<char>(swz_sizes(s).total() * esz);
   w.f.w3s = cv.take<float>(s.H);
-  w.part = cv.take<double>((size_t)bwd_blocks(n, act_path(s, bf), bf) * max_part_len(s, bf));
+  w.part = cv.take<double>((size_t)bwd_blocks(n, act_path(s), bf) * adj_part_len(s));
   take_sort(cv, n, 1, true, &w.srt);
   take_cell(cv, s, n, 1, false, &w.cell);
   w.act = nullptr;
   w.gpart = nullptr;
-  if (act_path(s, bf)) {
+  if (act_path(s)) {
     w.act = cv.take<char>((size_t)(s.MC + 3 * s.H) * act_ld(n) * esz);
     w.gpart = cv.take<double>((size_t)gemm_chunks(n) * gemm_part_len(s));
   }
@@ -634,14 +603,14 @@ size_t step_ws(const apmg_batch* b, const Shape& s, void* ws, StepWs* o) {
   w.adam = cv.take<float>((size_t)nb * 2);
   w.adam_g = cv.take<float>((size_t)nb * 2);
   w.step = cv.take<uint64_t>(1);
-  w.part = cv.take<double>((size_t)nb * step_max_blocks(b->n, nb) * max_part_len(s, bf));
+  w.part = cv.take<double>((size_t)nb * step_max_blocks(b->n, nb) * adj_part_len(s));
   w.live = cv.take<int32_t>((size_t)nb);
   w.dlive = cv.take<int32_t>((size_t)nb);
   take_sort(cv, b->n, nb, false, &w.srt);
   take_cell(cv, s, b->n, nb, true, &w.cell);
   w.act = nullptr;
   w.gpart = nullptr;
-  if (act_path(s, bf)) {
+  if (act_path(s)) {
     w.act = cv.take<char>((size_t)nb * (s.MC + 3 * s.H) * act_ld(b->n) * (bf ? 2 : 4));
     w.gpart = cv.take<double>((size_t)nb * gemm_chunks(b->n) * gemm_part_len(s));
   }
@@ -841,9 +810,7 @@ apmg_status apmg_backward(const apmg_model* m, const float* pts, int64_t ld, int
   const bool bf = m->mlp_dtype == APMG_BF16, gf16 = m->grid_dtype == APMG_F16;
   if (ws_bytes < bwd_ws(s, m, n, nullptr, nullptr) || !ws) return APMG_EWORKSPACE;
   const int grows = g_rows(m);
-  const bool use_act = dW != nullptr && act_path(s, bf);
-  const std::vector<Pass> passes = use_act ? std::vector<Pass>{{0, 0, 0, 0, true}} : plan_passes(s, bf, dW != nullptr);
-  if (passes.empty()) return APMG_EUNSUPPORTED;
+  const bool use_act = dW != nullptr && act_path(s);
   const bool acc = flags & APMG_ACCUMULATE;
   const size_t nF = (size_t)s.M * s.R * s.R * s.R * s.C;
   if (!acc && n == 0) {
@@ -865,8 +832,8 @@ apmg_status apmg_backward(const apmg_model* m, const float* pts, int64_t ld, int
   if (e != hipSuccess) return APMG_EHIP;
   const int nblk = bwd_blocks(n, use_act, bf);
   const bool want_cells = dF || dG;
-  const int kb = (!use_act && passes.size() == 1) ? register_kb(s) : 0;
-  for (const Pass& ps : passes) {
+  const int kb = use_act ? 0 : register_kb(s);
+  {
     TileArgs a;
     memset(&a, 0, sizeof(a));
     a.s = s;
@@ -876,22 +843,20 @@ apmg_status apmg_backward(const apmg_model* m, const float* pts, int64_t ld, int
     a.vscale = m->vmax - m->vmin; a.voff = m->vmin;
     a.pts = w.srt.spts; a.ld = n; a.n = n;
     a.df = w.srt.sf;
-    a.dY = (ps.first && want_cells) ? w.cell.dY : nullptr;
-    a.c1_lo = ps.c1_lo; a.c1_hi = ps.c1_hi;
-    a.w2_lo = ps.w2_lo; a.w2_hi = ps.w2_hi;
-    a.do_w3 = (ps.first && dW) ? 1 : 0;
+    a.dY = want_cells ? w.cell.dY : nullptr;
+    a.ncols = dW && !use_act ? s.MC : 0;
+    a.nrows2 = dW && !use_act ? s.H : 0;
+    a.do_w3 = dW ? 1 : 0;
     a.part = w.part;
-    const int ncols = ps.c1_hi - ps.c1_lo, nrows = ps.w2_hi - ps.w2_lo;
-    const PartLayout pl = part_layout(s, ncols, nrows);
+    const PartLayout pl = part_layout(s, a.ncols, a.nrows2);
     a.part_len = pl.len;
-    if (ps.first) prof_begin(st, 0);
+    prof_begin(st, 0);
     e = kb > 0 ? launch_adjoint(a, gf16, bf, 0, dim3(nblk, 1), st)
-               : launch_tile(true, kb, a, gf16, bf, dim3(nblk, 1), backward_lds_bytes(s, ncols, nrows, bf, kb), st);
+               : launch_tile(true, kb, a, gf16, bf, dim3(nblk, 1), backward_lds_bytes(s, a.ncols, a.nrows2, bf, kb), st);
     if (e != hipSuccess) return APMG_EHIP;
-    if (&ps == &passes.back()) prof_end(st, 0);
-    // (without the activation path the one pass holds every column and row)
-    if (dW && !use_act) reduce_dw(s, s.MC, s.H, true, w.part, nblk, pl.len, dW[0], dW[1], dW[2], acc ? 1 : 0, st);
-    if (dW && use_act) reduce_dw(s, 0, 0, true, w.part, nblk, pl.len, nullptr, nullptr, dW[2], acc ? 1 : 0, st);
+    prof_end(st, 0);
+    if (dW)
+      reduce_dw(s, a.ncols, a.nrows2, true, w.part, nblk, pl.len, dW[0], dW[1], dW[2], acc ? 1 : 0, st);
   }
   // the weight-gradient products (activation path) and the grid-gradient gather both read
   // what the adjoint kernel wrote and write disjoint outputs: the products run on the
@@ -1132,7 +1097,7 @@ apmg_status run_step(const apmg_batch* b, const Shape& s, void* ws, const Tune& 
 
   // 3. forward + adjoint of L_rec (part 1 of the step)
   const int nblk = tu.tile_blocks;
-  const bool use_act = act_path(s, bf);
+  const bool use_act = act_path(s);
   // (one pass: the register-resident shapes accumulate every column and row, the others store
   // their activations)
   const int kb = use_act ? 0 : register_kb(s);
@@ -1183,8 +1148,7 @@ apmg_status run_step(const apmg_batch* b, const Shape& s, void* ws, const Tune& 
     a.df = nullptr; a.v = w.v; a.v_stride = n; a.err = w.err; a.err_stride = n;
     a.err_abs = (b->flags & APMG_ERR_ABS) ? 1 : 0;
     a.dY = w.cell.dY;
-    a.c1_lo = 0; a.c1_hi = ncols;
-    a.w2_lo = 0; a.w2_hi = nrows;
+    a.ncols = ncols; a.nrows2 = nrows;
     a.do_w3 = 1;
     a.want_loss = 1;
     a.part = w.part;
@@ -1256,7 +1220,7 @@ extern "C" apmg_status apmg_batched_step(const apmg_batch* b, void* ws, size_t w
   if (rc != APMG_OK) return rc;
   Tune tu;
   const bool bf = b->shape.mlp_dtype == APMG_BF16;
-  if (!resolve_tune(b->tuning, b->n, b->nb, act_path(s, bf), bf, &tu)) return APMG_EINVAL;
+  if (!resolve_tune(b->tuning, b->n, b->nb, act_path(s), bf, &tu)) return APMG_EINVAL;
   if (!ws || ws_bytes < step_ws(b, s, nullptr, nullptr)) return APMG_EWORKSPACE;
   return run_step(b, s, ws, tu, true, st);
 }
@@ -1703,8 +1667,7 @@ apmg_status apmg_variant_backward(const apmg_model* m, const apmg_encoder* e, co
   a.tau = w.tau;
   a.df = bdf;
   a.dY = want_enc ? w.dY : nullptr;
-  a.c1_lo = 0; a.c1_hi = s.MC;
-  a.w2_lo = 0; a.w2_hi = s.H;
+  a.ncols = s.MC; a.nrows2 = s.H;
   a.do_w3 = dW ? 1 : 0;
   a.part = w.part;
   a.part_len = pl.len;

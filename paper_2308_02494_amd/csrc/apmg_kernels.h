@@ -79,8 +79,8 @@ struct TileArgs {
   float* err; size_t err_stride;          // h(x) out (training)
   int err_abs;
   float* dY;                              // [model][M][n][C] dL/dy per grid (sorted points) or NULL
-  int c1_lo, c1_hi;                       // first-layer gradient columns accumulated by this launch
-  int w2_lo, w2_hi;                       // second-layer gradient rows (multiples of 32)
+  int ncols, nrows2;                      // first-layer gradient columns and second-layer gradient rows the
+                                          // kernel accumulates: all (M C, H) or none
   int do_w3;                              // accumulate the output layer gradient
   int want_loss;                          // accumulate sum (f - v)^2 and the sum of the errors
   double* part; int part_len;             // per-block partials [model][block][part_len]

@@ -713,8 +713,7 @@ __device__ inline f32x16 tt_mma(const typename TT<BF>::T* Ta, int ia, const type
 }
 
 // KB > 0: register-resident weight-gradient accumulators (H = 64, KB = KHP/16 dy blocks,
-// every column and row in one launch).  KB == 0: per-tile LDS accumulation, any shape,
-// gradient rows/columns split across launches.
+// every column and row).  KB == 0: any shape, no first or second layer's gradient in the kernel.
 // ACT (KB == 0 only): the activation path, the per-point activations are stored (a.act) and
 // no weight gradient is accumulated in the kernel.  Bound by latency: two waves per SIMD although
 // some 40 values then go to scratch (64 grids at 64^3 x 4, 256-128-128-1 BF16 MLP, 2^19 points, the
@@ -732,8 +731,7 @@ __global__ void __launch_bounds__(kBlock, ACT ? 2 : 1) k_backward(TileArgs a) {
   const int64_t lbl = xcd_logical(blockIdx.x + (int64_t)gridDim.x * blockIdx.y, (int64_t)gridDim.x * gridDim.y);
   const int model = (int)(lbl / gridDim.x), lb = (int)(lbl % gridDim.x);
   const Shape s = a.s;
-  const int ncols = a.c1_hi - a.c1_lo;
-  const int nrows2 = a.w2_hi - a.w2_lo;
+  const int ncols = a.ncols, nrows2 = a.nrows2;
   const PartLayout pl = part_layout(s, ncols, nrows2);
   double* part = a.part + ((size_t)model * gridDim.x + lb) * pl.len;
   const bool act = !a.active || a.active[model];
@@ -905,7 +903,7 @@ __global__ void __launch_bounds__(kBlock, ACT ? 2 : 1) k_backward(TileArgs a) {
           ha.put(4 * hf, 2 * H + 32 * b + 8 * (r >> 2) + (r & 3), d2[b][r]);
     }
 
-    // dW2 rows [w2_lo, w2_hi) = sum_j delta2_j h1_j^T, one 32-row block of h1 at a time
+    // dW2 = sum_j delta2_j h1_j^T, one 32-row block of h1 at a time
     // (the register path only: other shapes take the activation path or want no dW)
     if (REG && nrows2 > 0) {
 #pragma unroll
@@ -975,17 +973,6 @@ __global__ void __launch_bounds__(kBlock, ACT ? 2 : 1) k_backward(TileArgs a) {
       for (int b = 0; b < NB; ++b)
 #pragma unroll
         for (int r = 0; r < 16; ++r) tt_put<BF>(Ta, 32 * b + acc_row(r, hf), j, d1[b][r]);
-    }
-
-    bf16x8 d1b[BF ? H / 16 : 1];
-    if constexpr (BF) {
-#pragma unroll
-      for (int st = 0; st < H / 16; ++st) {
-        float Bv[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) Bv[e] = d1[st >> 1][8 * (st & 1) + e];
-        d1b[st] = bf16_pack8(Bv);
-      }
     }
 
     // dL/dy per block of 16 features of each half: stored per grid for the cell pass,
@@ -1224,7 +1211,7 @@ hipError_t launch_tile(bool backward, int kb, const TileArgs& a, bool grid_f16, 
                        size_t shmem, hipStream_t st) {
   const int C = a.s.C, H = a.s.H;
   // only the register-resident adjoint accumulates weight gradients in the kernel
-  if (backward && kb == 0 && (a.c1_hi > a.c1_lo || a.w2_hi > a.w2_lo)) return hipErrorInvalidValue;
+  if (backward && kb == 0 && (a.ncols > 0 || a.nrows2 > 0)) return hipErrorInvalidValue;
 #define APMG_DISPATCH(CC, HH)                                                                  \
   if (C == CC && H == HH) {                                                                    \
     if (!grid_f16 && !mlp_bf16) return launch_tile_kernels<CC, HH, false, false>(backward, kb, a, grid, shmem, st); \

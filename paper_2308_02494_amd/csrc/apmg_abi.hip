@@ -727,7 +727,7 @@ apmg_status forward_impl(const apmg_model* m, const float* pts, int64_t ld, int6
   const bool bf = m->mlp_dtype == APMG_BF16, gf16 = m->grid_dtype == APMG_F16;
   if (ws_bytes < fwd_ws(s, m, n, nullptr, nullptr, sortable) || !ws) return APMG_EWORKSPACE;
   if (n == 0) return APMG_OK;
-  if (forward_small_applies(s, n)) {
+  if (forward_small_applies(s, n, !paper_grids(m))) {
     SmallArgs a;
     a.s = s;
     a.G = m->G; a.grows = g_rows(m);
@@ -1310,17 +1310,21 @@ struct DdWs {
 };
 int key_bits(int nseg) { int b = 1; while ((1 << b) < nseg) ++b; return b; }
 // Whether a brick query also orders the points by bins inside their bricks.  The order costs a
-// second radix pass (15 to 25 us; nothing where the brick ids take two passes themselves) and saves
-// cache misses of the lookups: the more points, lookups a point and bytes of grids, and the less of
-// them the MLP's matrix products hide.  Measured, unordered -> ordered, in us:
+// second radix pass (10 to 25 us; nothing where the brick ids take two passes themselves) and saves
+// cache misses of the lookups: the more points, lookups a point and bytes of grids there are, in
+// all and per brick, and the less of them the MLP's matrix products hide.  Measured, unordered ->
+// ordered, in us:
 //   16 grids at 16^3 x 2 binary16, 27 bricks, 2^18 points: BF16 MLP 86 -> 101, float32 109 -> 128;
 //   2^20 points: BF16 178 -> 170, float32 244 -> 260; 16 grids at 32^3 x 2, float32, 2^19 points:
-//   BF16 248 -> 177, float32 257 -> 205; 32 grids at 24^3 x 2 binary16, 128 wide float32 MLP, 2^18
-//   points: 406 -> 425; 64 grids at 32^3 x 2 binary16, 2^16 points: 306 -> 278.
-bool dd_orders_bins(const Shape& s, bool bf, bool gf16, int64_t n, int brick_bits) {
+//   BF16 248 -> 177, float32 257 -> 205; 8 grids at 16^3 x 2, float32, BF16 MLP, 125 bricks, 2^21
+//   points 320 -> 332, 8 bricks, 2^19 points 142 -> 131; 24 grids at 23^3 x 1, BF16 MLP, 6 bricks, 49,564
+//   points 62 -> 53; 32 grids at 24^3 x 2 binary16, 128 wide float32 MLP, 2^18 points: 406 -> 425;
+//   64 grids at 32^3 x 2 binary16, 2^16 points: 306 -> 278.
+bool dd_orders_bins(const Shape& s, bool bf, bool gf16, int64_t n, int nb, int brick_bits) {
   if (n < kFwdSortMin) return false;
   const double lookups = (double)n * s.M * (double)f_elems(s) * (gf16 ? 2 : 4);
-  return brick_bits > kRadixBits || lookups >= (bf ? 1.6e12 : s.H == 64 ? 4.2e12 : 1.6e13);
+  return brick_bits > kRadixBits ||
+         (lookups >= (bf ? 1.05e12 : s.H == 64 ? 4.2e12 : 1.6e13) && lookups >= 6.5e10 * nb);
 }
 size_t dd_ws(const Shape& s, const apmg_model* shape, int nb, int64_t n, void* ws, DdWs* o) {
   Carver cv(ws);
@@ -1362,7 +1366,7 @@ extern "C" apmg_status apmg_dd_forward(const apmg_dd_models* d, const apmg_brick
     return APMG_EHIP;
   // brick ids (and, where it pays, bins inside the bricks: as many bits as two radix passes
   // leave), then a stable radix sort of the points by them
-  const int kb = key_bits(nb), sb = dd_orders_bins(s, bf, gf16, n, kb) ? std::max(0, kBinBits - kb) : 0;
+  const int kb = key_bits(nb), sb = dd_orders_bins(s, bf, gf16, n, nb, kb) ? std::max(0, kBinBits - kb) : 0;
   const int3 bits = sb >= 3 ? make_int3((sb + 2) / 3, (sb + 1) / 3, sb / 3) : make_int3(0, 0, 0);
   const int sbits = bits.x + bits.y + bits.z;
   radix_sort(DdKey{*t, d->bricks, bits, pts, ld, w.rec}, n, 1, kb + sbits, w.srt, st);

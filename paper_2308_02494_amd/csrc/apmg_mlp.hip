@@ -1233,19 +1233,20 @@ hipError_t launch_tile(bool backward, int kb, const TileArgs& a, bool grid_f16, 
 // (every block lays them out again) take the one-launch kernel.  Up to 2^13 points its blocks are
 // one per compute unit and it is always faster (24 grids at 16^3 x 4, float32, 8192 points: 21 us
 // against 29 through k_forward, channel-last 14 against 18).  Beyond, the blocks queue, and their
-// cost grows with the features and, by lookups, with the channels: at 2^14 points 32 grids at
-// 16^3 x 2 take 18 us against 21 (channel-last 16 and 16) and 128 grids at 12^3 x 1 25 against 33,
-// but 16 grids at 16^3 x 4 22 against 21 (20 both at 12288 points), 64 grids at 16^3 x 2 channel-last
-// 26 against 24 (24 both at 12288), 24 grids at 16^3 x 4 31 against 27 and 40 grids at 16^3 x 4 47
-// against 37.
+// cost grows with the features and, by lookups, with the channels, above all in paper order; the
+// general path's grows with the grids.  2^14 points, float32, one launch against the general path:
+// 32 grids at 16^3 x 2 18 and 21 us (channel-last 16 and 16), 128 at 12^3 x 1 25 and 33, 48 at 24^3 x
+// 2 35 and 40 (27 and 33), 64 at 16^3 x 2 31 and 32 (26 and 24; 12288 points 24 and 24), 16 at 16^3 x 4
+// 22 and 21 (15 and 15; 12288 points 20 and 22), 24 at 16^3 x 4 31 and 27, 40 at 16^3 x 4 47 and 37.
 constexpr size_t kFwdSmallWeights = 16384;
-inline int64_t fwd_small_max(const Shape& s) {
+inline int64_t fwd_small_max(const Shape& s, bool last) {
   if (s.C == 1 || s.MC * s.C <= 128) return 16384;
-  return s.MC * s.C <= 256 ? 12288 : 8192;
+  if (s.MC * s.C > 256) return 8192;
+  return (s.C == 4 ? last : s.R >= 24) ? 16384 : 12288;
 }
-bool forward_small_applies(const Shape& s, int64_t n) {
+bool forward_small_applies(const Shape& s, int64_t n, bool last) {
   const SwzSizes z = swz_sizes(s);
-  return n <= fwd_small_max(s) && z.w1 + z.w2 <= kFwdSmallWeights;
+  return n <= fwd_small_max(s, last) && z.w1 + z.w2 <= kFwdSmallWeights;
 }
 hipError_t launch_forward_small(const SmallArgs& a, bool grid_f16, bool bf, bool last, hipStream_t st) {
   const Shape& s = a.s;

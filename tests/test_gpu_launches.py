@@ -76,15 +76,20 @@ def test_brick_queries_order_bins_where_it_pays(R, M, bf16, half, n, order):
     assert torch.equal(A().apmg_dd_forward(dd, pts), torch.cat(parts))
 
 
-# one launch up to 2^13 points, and beyond while the blocks that queue stay cheap: few features and channels
-@pytest.mark.parametrize("M,C,n,small", [
-    (40, 4, 8192, True), (40, 4, 8193, False), (24, 4, 10000, False), (96, 2, 12288, False),
-    (16, 4, 12288, True), (16, 4, 12289, False), (64, 2, 12288, True), (64, 2, 16384, False),
-    (32, 2, 16384, True), (128, 1, 16384, True), (8, 4, 16384, True), (32, 2, 16385, False),
+# one launch up to 2^13 points, and beyond while the blocks that queue stay cheap: few features and channels,
+# channel-last grids where they have four channels, large ones where they have two
+@pytest.mark.parametrize("M,C,R,last,n,small", [
+    (40, 4, 5, False, 8192, True), (40, 4, 5, True, 8193, False), (24, 4, 5, True, 10000, False),
+    (96, 2, 5, False, 12288, False), (16, 4, 5, False, 12288, True), (16, 4, 5, False, 12289, False),
+    (16, 4, 5, True, 16384, True), (64, 2, 5, True, 12288, True), (64, 2, 23, False, 16384, False),
+    (64, 2, 24, False, 16384, True), (32, 2, 5, False, 16384, True), (128, 1, 5, False, 16384, True),
+    (8, 4, 5, False, 16384, True), (32, 2, 5, False, 16385, False),
 ])
-def test_small_forward_sizes(M, C, n, small):
-    host = synth.init_model(M, C, 5, [M * C, 64, 64, 1], seed=M, grid_range=0.5)
+def test_small_forward_sizes(M, C, R, last, n, small):
+    host = synth.init_model(M, C, R, [M * C, 64, 64, 1], seed=M, grid_range=0.5)
     model = A().Model.from_host(host, DEV)
+    if last:
+        model = A().Model(model.G, model.F.permute(0, 2, 3, 4, 1).contiguous(), model.W, layout=A().GRIDS_MRRRC)
     pts = torch.rand((3, n), device=DEV) * 2 - 1
     out = torch.empty(n, device=DEV)
     ws = torch.empty(A()._lib.apmg_workspace_bytes(A().OP_FORWARD, ctypes.byref(model.struct()), n),

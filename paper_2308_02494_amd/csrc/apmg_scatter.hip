@@ -361,8 +361,12 @@ __device__ inline double lane_f64(double v, int k) {
 // SPLIT: the four waves of a workgroup share one block (wave w takes steps w, w + 4, ... and the
 // four lattices are added in wave order); otherwise each wave has a block of its own.
 // Output: lattices CC[model][g][block][vz 4][vy 4][vx][channel + C slice].
+// Waves per SIMD: six where the accumulators allow it, four with the transform gradient or four values
+// a vertex.  One channel takes six there too, with 8 values in scratch: its matrix work per match is
+// that of two channels, so its gather is bound by latency (64 grids at 32^3, 2^19 points, BF16, the whole
+// adjoint: 752 us in the gather per cell owner that this one replaced, 830 with four waves, 740 with six).
 template <int C, bool GF16, bool DG, int TS, bool SPLIT>
-__global__ void __launch_bounds__(256, DG || C * TS > 2 ? 4 : 6) k_block_pull(CellArgs a) {
+__global__ void __launch_bounds__(256, C > 1 && (DG || C * TS > 2) ? 4 : 6) k_block_pull(CellArgs a) {
   static_assert(TS == 1 || (TS == 2 && !DG), "the 4-D pass has no transform gradient");
   constexpr int VX = pull_vx(C), CT = C * TS;
   constexpr int NT = VX * CT / 16;           // 16-column tiles; column = vx CT + channel (+ C slice)

@@ -61,6 +61,12 @@ def test_brick_forward_keeps_four_waves_per_simd(kernels):
     assert not few
 
 
+def test_one_channel_gather_keeps_six_waves_per_simd(kernels):
+    pull = {n: v for n, (v, _) in kernels.items() if n.startswith("apmg::k_block_pull<1, ")}
+    assert len(pull) == 8
+    assert not {n: v for n, v in pull.items() if 512 // (-(-v // 8) * 8) < 6}
+
+
 def test_one_channel_half_grids_load_pairs_at_once(code_object):
     # the two binary16 values of an x-adjacent vertex pair come in one 4-byte load
     syms = [ln.split()[-1] for ln in run(LLVM + "llvm-readelf", "-sW", code_object).splitlines() if " FUNC " in ln]

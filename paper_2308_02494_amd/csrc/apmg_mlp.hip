@@ -401,9 +401,11 @@ __host__ __device__ inline size_t fwd_weight_bytes(const Shape& s, bool bf) {
 // accumulators in the registers that four waves leave (left to the compiler it takes 12 more than
 // four waves have: 125 models of 8 grids at 16^3 x 2, binary16 grids, 2^19 points: 185 us against
 // 167); only with a BF16 MLP over float32 grids of two channels it does run three.
-constexpr int fwd_waves_per_simd(int C, int H, bool bf, bool wl, int enc, bool dd) {
+// One-channel binary16 grids have room for four without a bound, and their unaligned loads are
+// scheduled worse with it (unsorted, 2^20 points, 40 grids at 24^3, float32 MLP: 394 us against 357).
+constexpr int fwd_waves_per_simd(int C, int H, bool f16, bool bf, bool wl, int enc, bool dd) {
   if (H != 64 || C > 2 || !wl || enc == kEncTime || (enc == kEncHash && bf)) return 1;
-  return dd ? 3 : 4;
+  return dd ? 3 : f16 && C == 1 ? 1 : 4;
 }
 
 // WL: the swizzled weights are staged in LDS (after the transforms).
@@ -415,7 +417,7 @@ constexpr int fwd_waves_per_simd(int C, int H, bool bf, bool wl, int enc, bool d
 // model, mapped into each model's brick here: one pass less over the points than mapping them
 // into an array of their own first, and none to scatter the outputs back.
 template <int C, int H, bool GF16, bool BF, bool WL, int ENC = kEncDense, int NWF = kWavesPerBlock, bool DD = false>
-__global__ void __launch_bounds__(NWF * kWave, fwd_waves_per_simd(C, H, BF, WL, ENC, DD)) k_forward(TileArgs a) {
+__global__ void __launch_bounds__(NWF * kWave, fwd_waves_per_simd(C, H, GF16, BF, WL, ENC, DD)) k_forward(TileArgs a) {
   extern __shared__ float smem[];
   // logical block: models in order, each model's blocks over contiguous runs of its
   // (spatially sorted) tiles, dealt to the XCDs in slabs

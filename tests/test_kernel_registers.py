@@ -61,6 +61,12 @@ def test_brick_forward_keeps_four_waves_per_simd(kernels):
     assert not few
 
 
+def test_one_channel_half_forward_takes_the_registers_of_four_waves(kernels):
+    # more than the 98 it is squeezed into under a bound, at most the 128 of four waves
+    for bf16 in ("true", "false"):
+        assert 104 < kernels[f"apmg::k_forward<1, 64, true, {bf16}, true, 0, 4, false>"][0] <= 128
+
+
 def test_one_channel_gather_keeps_six_waves_per_simd(kernels):
     pull = {n: v for n, (v, _) in kernels.items() if n.startswith("apmg::k_block_pull<1, ")}
     assert len(pull) == 8

@@ -1314,17 +1314,21 @@ int key_bits(int nseg) { int b = 1; while ((1 << b) < nseg) ++b; return b; }
 // cache misses of the lookups: the more points, lookups a point and bytes of grids there are, in
 // all and per brick, and the less of them the MLP's matrix products hide.  Measured, unordered ->
 // ordered, in us:
-//   16 grids at 16^3 x 2 binary16, 27 bricks, 2^18 points: BF16 MLP 86 -> 101, float32 109 -> 128;
-//   2^20 points: BF16 178 -> 170, float32 244 -> 260; 16 grids at 32^3 x 2, float32, 2^19 points:
-//   BF16 248 -> 177, float32 257 -> 205; 8 grids at 16^3 x 2, float32, BF16 MLP, 125 bricks, 2^21
-//   points 320 -> 332, 8 bricks, 2^19 points 142 -> 131; 24 grids at 23^3 x 1, BF16 MLP, 6 bricks, 49,564
-//   points 62 -> 53; 32 grids at 24^3 x 2 binary16, 128 wide float32 MLP, 2^18 points: 406 -> 425;
-//   64 grids at 32^3 x 2 binary16, 2^16 points: 306 -> 278.
+//   BF16 MLP: 16 grids at 16^3 x 2 binary16, 27 bricks, 2^18 points 86 -> 101, 2^20 points 178 -> 170; 8
+//   grids at 16^3 x 2 float32, 125 bricks, 2^21 points 320 -> 332, 8 bricks, 2^19 points 142 -> 131; 24
+//   grids at 23^3 x 1 float32, 6 bricks, 49,564 points 62 -> 53;
+//   float32 MLP: 16 grids at 16^3 x 2 float32, 27 bricks, 2^18 points 119 -> 126, 2^19 points 176 -> 172;
+//   24 grids at 22^3 x 2 float32, 12 bricks, 50,121 points 79 -> 70; 16 grids at 32^3 x 2, 27 bricks,
+//   2^19 points 257 -> 205; 16 grids at 16^3 x 4 binary16, 27 bricks, 2^20 points 338 -> 348, 16 at
+//   24^3 x 1 binary16, 2^21 points 399 -> 368;
+//   float32 MLP 128 wide, 27 bricks: 32 grids at 24^3 x 2 binary16, 2^18 points 406 -> 425, 64 at
+//   32^3 x 2 binary16, 2^16 points 306 -> 278.
 bool dd_orders_bins(const Shape& s, bool bf, bool gf16, int64_t n, int nb, int brick_bits) {
   if (n < kFwdSortMin) return false;
   const double lookups = (double)n * s.M * (double)f_elems(s) * (gf16 ? 2 : 4);
-  return brick_bits > kRadixBits ||
-         (lookups >= (bf ? 1.05e12 : s.H == 64 ? 4.2e12 : 1.6e13) && lookups >= 6.5e10 * nb);
+  if (bf) return lookups >= 1.05e12 && lookups >= 6.5e10 * nb;
+  if (s.H == 128) return lookups >= 5e12 && lookups >= 6e11 * nb;
+  return gf16 ? lookups >= 4.2e12 && lookups >= 5e11 * nb : lookups >= 2.4e12 && lookups >= 1.5e11 * nb;
 }
 size_t dd_ws(const Shape& s, const apmg_model* shape, int nb, int64_t n, void* ws, DdWs* o) {
   Carver cv(ws);

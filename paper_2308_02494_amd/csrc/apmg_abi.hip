@@ -340,18 +340,20 @@ inline int cell_blocks(const Shape& s) { return (int)((n_cells(s) + 255) / 256);
 // The block gather gives a block of cells to one wave, or to the four waves of a workgroup, which
 // then each pay for the block's set-up (about that of 100 candidates) and share its candidates.
 // Sharing evens out and fills the device's rounds of waves, which matters the less the more blocks
-// there are: it pays from some 500 points per block for a thousand blocks in all, from 800 for 4000,
-// and from 2000 for 8000 to 16384 (beyond, the one wave).  The adjoint alone with the transform
+// there are: it pays from 256 points per block for fewer than a thousand blocks in all, from 800 for
+// 4000, and from 2000 for 8000 to 16384 (beyond, the one wave).  The adjoint alone with the transform
 // gradient, one wave -> four, in us: 16 grids at 16^3 x 2 (1200 blocks), 65,536 points 131 -> 122,
 // 2^20 points 1149 -> 738; 16 at 30^3 x 2 (8000), 2^17 points 167 -> 215, 2^20 points 779 -> 767;
 // 32 at 32^3 x 1 (11616), 2^18 points 351 -> 381, 2^20 points 1120 -> 1003.  In a training step
 // (step) the density passes run beside it and other models fill the device: from 1024 points on (16
 // models of 16 grids at 16^3 x 2, 65,536 points, with the transform gradient: 641 us with one wave,
-// 787 with four; one model 149 and 154).  The rule looks at one model alone, so a model's sums do
-// not depend on the batch it is stepped in.
+// 787 with four; one model 149 and 154), but for models so small that a few of them leave most
+// of the device idle (4 models of 7 grids at 10^3 x 4, 126 blocks, 14,780 points: 174 and 157).  The
+// rule looks at one model alone, so a model's sums do not depend on the batch it is stepped in.
 inline bool pull_split(const Shape& s, int64_t n, bool step = false) {
-  const int64_t nblk = pull_blocks(s.R, s.C).total();
-  return nblk * s.M < 16384 && n >= (step ? 1024 : 512) * nblk && 6 * n >= nblk * nblk * s.M;
+  const int64_t nblk = pull_blocks(s.R, s.C).total(), all = nblk * s.M;
+  const int64_t least = step ? (all < 192 ? 256 : 1024) : (all < 1024 ? 256 : 512);   // points per block
+  return all < 16384 && n >= least * nblk && 6 * n >= nblk * all;
 }
 // workgroups per grid of the block gather (four waves each)
 inline int pull_groups(const Shape& s, int64_t n, bool step = false) {
@@ -1325,6 +1327,7 @@ int key_bits(int nseg) { int b = 1; while ((1 << b) < nseg) ++b; return b; }
 //   32^3 x 2 binary16, 2^16 points 306 -> 278.
 bool dd_orders_bins(const Shape& s, bool bf, bool gf16, int64_t n, int nb, int brick_bits) {
   if (n < kFwdSortMin) return false;
+  if (brick_bits > kRadixBits) return true;
   const double lookups = (double)n * s.M * (double)f_elems(s) * (gf16 ? 2 : 4);
   if (bf) return lookups >= 1.05e12 && lookups >= 6.5e10 * nb;
   if (s.H == 128) return lookups >= 5e12 && lookups >= 6e11 * nb;

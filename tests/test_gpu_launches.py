@@ -163,6 +163,8 @@ def test_hash_levels_share_the_scatter(n, res, gathered):
     (16, 2, 16, 75 * 512 - 1, False, 19), (16, 2, 16, 75 * 512, False, 75),
     (16, 2, 16, 75 * 1024 - 1, True, 19), (16, 2, 16, 75 * 1024, True, 75),
     (16, 2, 30, 1 << 17, False, 125), (16, 2, 30, 666667, False, 500), (16, 2, 30, 1 << 17, True, 125),
+    (7, 4, 10, 18 * 256 - 1, True, 5), (7, 4, 10, 18 * 256, True, 18), (3, 2, 24, (1 << 16) - 1, False, 64),
+    (3, 2, 24, 1 << 16, False, 256),
     (32, 1, 32, 1 << 18, False, 91), (32, 1, 32, 1 << 20, False, 363), (32, 2, 32, 1 << 21, False, 152),
 ])
 def test_gather_waves_per_block(M, C, R, n, step, groups):

@@ -49,9 +49,9 @@ def test_default_tile_blocks_match_one_block(nb, bf16):
         assert_close(name, a, b)
 
 
-# 4 blocks of cells a grid: one wave a block below 1024 points per block, four from there on
+# 4 blocks of cells a grid: one wave a block below 256 points per block, four from there on
 @pytest.mark.parametrize("C", [1, 2, 4])
-@pytest.mark.parametrize("n", [4095, 4096, 20001])
+@pytest.mark.parametrize("n", [1023, 1024, 20001])
 def test_step_gathers_agree_on_both_sides_of_the_split(C, n):
     vol = synth.make_volume("blobs_sine", (24, 24, 48)).to(DEV)
     _, bricks = A().apmg_make_bricks(48, 24, 24, 24, 0)

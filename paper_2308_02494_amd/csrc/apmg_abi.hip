@@ -385,7 +385,7 @@ void prof_end(hipStream_t st, int k) {
 hipError_t launch_cells(const Shape& s, bool gf16, const float* G, size_t G_stride, const void* F, size_t F_stride,
                         const SortWs& sw, int64_t n, const CellWs& cw, float* dF, size_t dF_stride, int dF_paper,
                         int accumulate, bool want_dG, double* dG, size_t dG_stride, int dG_rows, int dG_accumulate, int nb,
-                        const int32_t* active, hipStream_t st, bool step, int unroll = 4,
+                        const int32_t* active, hipStream_t st, bool step, bool products, int unroll = 4,
                         const int32_t* dG_active = nullptr, int cell_kernel = 0) {
   CellArgs c;
   memset(&c, 0, sizeof(c));
@@ -410,6 +410,8 @@ hipError_t launch_cells(const Shape& s, bool gf16, const float* G, size_t G_stri
   {                                                                                                 \
     const dim3 wg((unsigned)wgroups);                                                               \
     if (split) hipLaunchKernelGGL((k_block_pull<CC_, F16_, DG_, 1, true>), wg, dim3(256), 0, st, c); \
+    else if (CC_ == 1 && DG_ && !products)                                                          \
+      hipLaunchKernelGGL((k_block_pull<CC_, F16_, DG_, 1, false, !DG_ || CC_ == 1>), wg, dim3(256), 0, st, c);\
     else hipLaunchKernelGGL((k_block_pull<CC_, F16_, DG_, 1, false>), wg, dim3(256), 0, st, c);      \
   }
 #define APMG_CELL(CC_, F16_)                                                                        \
@@ -895,7 +897,7 @@ apmg_status apmg_backward(const apmg_model* m, const float* pts, int64_t ld, int
   hipError_t ec = hipSuccess;
   if (want_cells)
     ec = launch_cells(s, gf16, Gc, 0, Fc, 0, w.srt, n, w.cell, dF, 0, paper_grids(m) ? 1 : 0, acc ? 1 : 0,
-                      dG != nullptr, dG, 0, grows, acc ? 1 : 0, 1, nullptr, st, false);
+                      dG != nullptr, dG, 0, grows, acc ? 1 : 0, 1, nullptr, st, false, use_act);
   hipError_t ej = hipSuccess;
   if (pst != st) {
     ej = hipEventRecord(side->join, pst);
@@ -1190,7 +1192,7 @@ apmg_status run_step(const apmg_batch* b, const Shape& s, void* ws, const Tune& 
     reduce_part(dst);
     if (use_act) act_products(dst);
     const hipError_t ec = launch_cells(s, gf16, b->G, nG, Fg, nF, w.srt, n, w.cell, w.dF, nF, paper ? 1 : 0, 0,
-                                       rec_dG, nullptr, 0, 3, 0, nb, w.live, st, true, tu.cell_unroll, nullptr,
+                                       rec_dG, nullptr, 0, 3, 0, nb, w.live, st, true, use_act, tu.cell_unroll, nullptr,
                                        tu.cell_kernel);
     hipError_t ej = hipSuccess;
     if (dst != st) {

@@ -362,11 +362,14 @@ __device__ inline double lane_f64(double v, int k) {
 // four lattices are added in wave order); otherwise each wave has a block of its own.
 // Output: lattices CC[model][g][block][vz 4][vy 4][vx][channel + C slice].
 // Waves per SIMD: six where the accumulators allow it, four with the transform gradient or four values
-// a vertex.  One channel takes six there too, with 8 values in scratch: its matrix work per match is
-// that of two channels, so its gather is bound by latency (64 grids at 32^3, 2^19 points, BF16, the whole
-// adjoint: 752 us in the gather per cell owner that this one replaced, 830 with four waves, 740 with six).
-template <int C, bool GF16, bool DG, int TS, bool SPLIT>
-__global__ void __launch_bounds__(256, C > 1 && (DG || C * TS > 2) ? 4 : 6) k_block_pull(CellArgs a) {
+// a vertex.  With one channel and the transform gradient (SIX) six hold it too, with 8 values in
+// scratch: its matrix work per match is that of two channels, so the gather by itself is bound by
+// latency (64 grids at 32^3, 2^19 points, BF16, the whole adjoint: 752 us in the gather per cell owner
+// that this one replaced, 830 with four waves, 740 with six).  Four where the waves of a block share it
+// (5 grids at 8^3, 43,260 points: 169 us, with six 176) and where the weight products of the 128-wide
+// MLP run beside it and take the matrix cores (38 grids at 38^3 binary16, 66,236 points: 320 and 350).
+template <int C, bool GF16, bool DG, int TS, bool SPLIT, bool SIX = !DG>
+__global__ void __launch_bounds__(256, C == 1 ? (SIX ? 6 : 4) : DG || C * TS > 2 ? 4 : 6) k_block_pull(CellArgs a) {
   static_assert(TS == 1 || (TS == 2 && !DG), "the 4-D pass has no transform gradient");
   constexpr int VX = pull_vx(C), CT = C * TS;
   constexpr int NT = VX * CT / 16;           // 16-column tiles; column = vx CT + channel (+ C slice)

@@ -340,8 +340,8 @@ inline int cell_blocks(const Shape& s) { return (int)((n_cells(s) + 255) / 256);
 // The block gather gives a block of cells to one wave, or to the four waves of a workgroup, which
 // then each pay for the block's set-up (about that of 100 candidates) and share its candidates.
 // Sharing evens out and fills the device's rounds of waves, which matters the less the more blocks
-// there are: it pays from 256 points per block for fewer than a thousand blocks in all, from 800 for
-// 4000, and from 2000 for 8000 to 16384 (beyond, the one wave).  The adjoint alone with the transform
+// there are: it pays from 256 points per block (512 from a thousand blocks in all on) and from a sixth
+// as many points per block as there are blocks in all, up to 16384.  The adjoint alone with the transform
 // gradient, one wave -> four, in us: 16 grids at 16^3 x 2 (1200 blocks), 65,536 points 131 -> 122,
 // 2^20 points 1149 -> 738; 16 at 30^3 x 2 (8000), 2^17 points 167 -> 215, 2^20 points 779 -> 767;
 // 32 at 32^3 x 1 (11616), 2^18 points 351 -> 381, 2^20 points 1120 -> 1003.  In a training step
